@@ -70,6 +70,9 @@ struct lbm_ctx {
   double* rec_bc = nullptr;
   void* lk_c = nullptr;        // [3][nlinks] in the compute type
   uint32_t* rec_mb = nullptr;  // [nrec] bit j: link j has q >= 1/2
+  int32_t* lk_node = nullptr;  // [nlinks] node of each link
+  uint8_t* lk_w = nullptr;     // [nlinks] its direction, branch and available neighbours
+  int lds_links[3] = {0, 0, 0};  // most links of a block of 64, 128, 256 records
   int nlinks_rec = 0;
   int32_t* tile_list = nullptr;
   int32_t* bulk_list = nullptr;  // list form: the bulk nodes in order (built on first use)
@@ -324,6 +327,7 @@ extern "C" lbm_status lbm_create(const lbm_desc* d, void* hip_stream, lbm_ctx** 
   std::vector<uint8_t> r_face;
   std::vector<double> r_bc;  // 4 per record, transposed later
   std::vector<double> l_c;  // 5 per link, transposed below
+  std::vector<uint8_t> l_av;  // per link: neighbours available to the rule
   long long n_inlet_seen = 0;
   for (int z = 0; z < nz; z++)
     for (int y = 0; y < ny; y++)
@@ -416,6 +420,7 @@ extern "C" lbm_status lbm_create(const lbm_desc* d, void* hip_stream, lbm_ctx** 
             c[3] = (2.0 * q - 1.0) / (2.0 * q);
           }
           for (int k = 0; k < 5; k++) l_c.push_back(c[k]);
+          l_av.push_back((uint8_t)((a1 ? 64 : 0) | (a2 ? 128 : 0)));
         }
       }
   for (const auto& kv : links)
@@ -445,7 +450,6 @@ extern "C" lbm_status lbm_create(const lbm_desc* d, void* hip_stream, lbm_ctx** 
   CHK(upload(&ctx->rec_of, rec_of));
   CHK(upload(&ctx->rec_node, r_node));
   CHK(upload(&ctx->rec_mask, r_mask));
-  CHK(upload(&ctx->rec_link0, r_link0));
   CHK(upload(&ctx->rec_face, r_face));
   CHK(upload(&ctx->rec_bc, bcT));
   ctx->rec_bc_h = bcT;
@@ -456,6 +460,16 @@ extern "C" lbm_status lbm_create(const lbm_desc* d, void* hip_stream, lbm_ctx** 
   const size_t nl = l_c.size() / 5;
   std::vector<double> lcT(std::max<size_t>(3 * nl, 3), 0.0);  // entry 0 always exists
   std::vector<uint32_t> mb((size_t)std::max(ctx->nrec, 1), 0u);
+  std::vector<int32_t> ln(std::max<size_t>(nl, 1), 0);
+  // (entry 0 is read where a lattice has open faces and no links: node 0, direction 1)
+  std::vector<uint8_t> lw(std::max<size_t>(nl, 1), 1);
+  r_link0.push_back((int32_t)nl);
+  CHK(upload(&ctx->rec_link0, r_link0));
+  for (int k = 0; k < 3; k++) {
+    const int bs = 64 << k;
+    for (int r = 0; r < ctx->nrec; r += bs)
+      ctx->lds_links[k] = std::max(ctx->lds_links[k], r_link0[std::min(r + bs, ctx->nrec)] - r_link0[r]);
+  }
   for (int r = 0; r < ctx->nrec; r++) {
     int lk = r_link0[r];
     for (int j = 1; j < 19; j++) {
@@ -463,6 +477,8 @@ extern "C" lbm_status lbm_create(const lbm_desc* d, void* hip_stream, lbm_ctx** 
       const double* c = &l_c[5 * (size_t)lk];
       const bool hq = c[1] == 0.0 && c[2] == 0.0 && (c[3] != 0.0 || c[4] != 0.0);
       if (hq) mb[r] |= 1u << j;
+      ln[lk] = r_node[r];
+      lw[lk] = (uint8_t)(j | (hq ? 32 : 0) | l_av[lk]);
       lcT[lk] = c[0];
       lcT[nl + lk] = hq ? c[3] : c[1];
       lcT[2 * nl + lk] = hq ? c[4] : c[2];
@@ -477,6 +493,8 @@ extern "C" lbm_status lbm_create(const lbm_desc* d, void* hip_stream, lbm_ctx** 
     CHK(upload((float**)&ctx->lk_c, lcf));
   }
   CHK(upload(&ctx->rec_mb, mb));
+  CHK(upload(&ctx->lk_node, ln));
+  CHK(upload(&ctx->lk_w, lw));
   CHK(upload(&ctx->tile_list, tiles));
   CHK(hipMalloc(&ctx->flags, sizeof(DevFlags) + 64));
   CHK(hipMemset(ctx->flags, 0, sizeof(DevFlags) + 64));
@@ -504,7 +522,7 @@ extern "C" lbm_status lbm_destroy(lbm_ctx* ctx) {
   free_graphs(ctx);
   free_bodies(ctx);
   void* ptrs[] = {ctx->f_alloc[0], ctx->f_alloc[1], ctx->ncls, ctx->rec_of, ctx->rec_node, ctx->rec_mask,
-                  ctx->rec_link0, ctx->rec_face, ctx->rec_bc, ctx->lk_c, ctx->rec_mb,
+                  ctx->rec_link0, ctx->rec_face, ctx->rec_bc, ctx->lk_c, ctx->rec_mb, ctx->lk_node, ctx->lk_w,
                   ctx->tile_list, ctx->bulk_list, ctx->fx[0], ctx->fx[1], ctx->tf[0], ctx->tf[1], ctx->fx_api,
                   ctx->api_flags, ctx->mac, ctx->flags, ctx->gdiag};
   for (void* p : ptrs)
@@ -1038,6 +1056,9 @@ static FluidArgs fluid_args(lbm_ctx* ctx, int p) {
   a.rec_bc = ctx->rec_bc;
   a.lk_c = ctx->lk_c;
   a.rec_mb = ctx->rec_mb;
+  a.lk_node = ctx->lk_node;
+  a.lk_w = ctx->lk_w;
+  for (int k = 0; k < 3; k++) a.lds_links[k] = ctx->lds_links[k];
   a.nlinks = ctx->nlinks_rec;
   a.tile_list = ctx->tile_list;
   a.nbulk_blocks = ctx->nbulk_blocks;
@@ -1408,6 +1429,9 @@ static BatchFluid batch_fluid(const lbm_batch* b) {
   f.n_rec = b->n_rec;
   f.map_bulk = b->m_bulk;
   f.n_bulk = b->n_bulk;
+  f.lds_links = 0;
+  for (const lbm_ctx* c : b->ctx)
+    f.lds_links = std::max(f.lds_links, c->lds_links[b->block == 64 ? 0 : (b->block == 128 ? 1 : 2)]);
   return f;
 }
 

@@ -76,11 +76,14 @@ struct FluidArgs {
   int nrec;
   const int32_t* rec_node;   // padded index
   const uint32_t* rec_mask;  // bit j: pulled direction j comes from a wall link
-  const int32_t* rec_link0;
+  const int32_t* rec_link0;  // [nrec + 1] first link of each record (then the number of links)
   const uint8_t* rec_face;   // 0xff: none; else face | (kind << 4) (kind 1 = density)
   const double* rec_bc;      // [4][nrec]: ux, uy, uz, rho
   const void* lk_c;          // [3][nlinks] interpolated bounce-back coefficients (compute type)
   const uint32_t* rec_mb;    // [nrec] bit j: the link of direction j has q >= 1/2
+  const int32_t* lk_node;    // [nlinks] node of each link
+  const uint8_t* lk_w;       // [nlinks] pulled direction j | (q >= 1/2) << 5 | x + e_j fluid << 6 | x + 2 e_j fluid << 7
+  int lds_links[3];          // most links of a block of 64, 128, 256 consecutive records
   int nlinks;
   const int32_t* tile_list;  // blocks of the bulk part (tile form)
   int nbulk_blocks;
@@ -354,6 +357,7 @@ struct BatchFluid {
   const int2* map_all; int n_all;
   const int2* map_rec; int n_rec;
   const int2* map_bulk; int n_bulk;
+  int lds_links;  // most links of a record block of any instance
 };
 
 // Batched phases: n blocks (units) each, map[g] = (instance, unit).

@@ -286,39 +286,17 @@ __device__ void zouhe(C (&g)[19], int face, int kind, C bx, C by, C bz, C brho) 
 // bbouzidi): k0 f*_i(x) + k1 t1 + k2 t2 with i the opposite of j and, by the
 // link's branch, t1 = f*_i(x - e_i), t2 = f*_i(x - 2e_i) (q < 1/2) or
 // t1 = f*_j(x), t2 = f*_j(x - e_i) (q >= 1/2); k1, k2 are zero where the
-// fluid neighbours are missing.  The loads carry no branch (they go out in
-// one batch with the rest of the node's loads); for a direction without a
-// link they read the node's own values (no traffic) and the caller drops
-// the result.
+// fluid neighbours are missing.
 template <class S>
 struct Bfl {
   typename Store<S>::C k0, k1, k2, s, t1, t2;
 };
 
-template <class S>
-__device__ __forceinline__ Bfl<S> bfl_load(const FluidArgs& a, int j, bool linked, int lk, bool hq,
-                                           int node, const Hood& h) {
-  typedef typename Store<S>::C C;
-  const Grid& G = a.g;
-  const C* lc = (const C*)a.lk_c;
-  const S* A = (const S*)a.A;
-  const long long nl = a.nlinks;
-  const int i = OPP[j];
-  const int l = linked ? lk : 0;
-  const int n1 = linked ? h.at(EX[j], EY[j], EZ[j]) : node;  // x - e_i
-  const int n2 = linked ? h.at(2 * EX[j], 2 * EY[j], 2 * EZ[j]) : node;
-  Bfl<S> r;
-  r.k0 = lc[l];
-  r.k1 = lc[nl + l];
-  r.k2 = lc[2 * nl + l];
-  r.s = ldA<S>(a, i, node);
-  r.t1 = to_c(A[hq ? (long long)j * G.plane + node : (long long)i * G.plane + n1]);
-  r.t2 = to_c(A[hq ? (long long)j * G.plane + n1 : (long long)i * G.plane + n2]);
-  return r;
-}
-
-// The same loads with each neighbour index formed on its own (fewer values
-// live at once: used where registers are scarce, in the IB kernels).
+// The IB kernels' form, one node per thread.  The loads carry no branch (they
+// go out in one batch with the rest of the node's loads); for a direction
+// without a link they read the node's own values (no traffic) and the caller
+// drops the result.  Each neighbour index is formed on its own (few values
+// live at once: registers are scarce there).
 template <class S>
 __device__ __forceinline__ Bfl<S> bfl_load_nb(const FluidArgs& a, int j, bool linked, int lk, bool hq,
                                               long long node, int x, int y, int z) {
@@ -345,52 +323,163 @@ __device__ __forceinline__ typename Store<S>::C bfl_value(const Bfl<S>& b) {
   return b.k0 * b.s + b.k1 * b.t1 + b.k2 * b.t2;
 }
 
-// Streamed populations of a boundary record: plain pulls (periodic wrap),
-// interpolated bounce-back on wall links, and Zou-He for the populations
-// entering through an open face.  Addresses are formed with periodic wrap,
-// so they lie in the box; after the record's header every load is issued
-// in one batch, then the arithmetic follows.  A pull from a solid node or
-// from outside the box reads the node's own rest value (no traffic) and is
-// not used.
-template <class S>
-__device__ void pull_general(const FluidArgs& a, int r, typename Store<S>::C (&g)[19], bool zh = true) {
+// Direction arithmetic for a direction known only at run time: the
+// components of e_j (two bits each, biased by one) and the opposite.
+constexpr unsigned long long dir_bits(const int (&e)[19]) {
+  unsigned long long b = 0;
+  for (int j = 0; j < 19; j++) b |= (unsigned long long)(e[j] + 1) << (2 * j);
+  return b;
+}
+__device__ __forceinline__ int dir_of(unsigned long long bits, int j) { return (int)((bits >> (2 * j)) & 3u) - 1; }
+__device__ __forceinline__ int opp_of(int j) {
+  return j < 7 ? ((j - 1) ^ 1) + 1 : (j < 15 ? 7 + ((j - 7) ^ 5) : 15 + ((j - 15) ^ 3));
+}
+
+// Streamed populations of a block of boundary records, one record per thread
+// (record r0 + threadIdx.x; every thread of the block calls, those past the
+// last record repeat it): plain pulls (periodic wrap), interpolated
+// bounce-back on wall links, and Zou-He for the populations entering through
+// an open face.
+//
+// A record has 4 to 5 links on average out of 18 directions.  Issued per
+// record and direction, the rule's six loads made 133 loads per thread (and
+// the registers to hold them) where about 45 are needed.  Here the links of
+// the block's records, which are consecutive, are spread over its threads,
+// one link per thread and pass: the link's node and word (direction, branch),
+// then its coefficients and three populations, its value out to LDS, where
+// the record picks it up.  The words of LINK_PASSES passes are loaded in one
+// batch ahead of the plain pulls, and their populations in one batch after
+// them, so that a block waits for the same few rounds of loads whatever its
+// number of links.  A plain pull from a solid node or from outside the box
+// reads the node's own rest value (no traffic) and is not used.
+// Measured against the per-record form (record launch of the D = 96 pipe in
+// FP16S 73 -> 49 us; the merged launch of a ten-instance sweep 77 -> 69 us,
+// of the 16-capsule channel 52.6 -> 50.3 us, of the bifurcation with one
+// capsule 15.0 -> 14.5 us).  Links in padded groups per wave, whose words
+// need no start index, were slower (15.6 us there): the padding costs more
+// passes than the saved wait.
+//
+// s_dyn (dynamic LDS): the links of the fullest block of this size.
+extern __shared__ double s_dyn[];
+constexpr int LINK_PASSES = 5;
+
+template <class S, int NP>
+__device__ __forceinline__ void link_values(const FluidArgs& a, int l0, int l1, int first, const int (&nd)[NP],
+                                            const unsigned int (&w)[NP], typename Store<S>::C* s_link) {
   typedef typename Store<S>::C C;
   const Grid& G = a.g;
   const S* A = (const S*)a.A;
-  const int node = a.rec_node[r];
+  const C* lc = (const C*)a.lk_c;
+  const long long nl = a.nlinks;
+  int n1[NP], n2[NP];  // x - e_i, x - 2 e_i where they are fluid nodes, else x
+  const bool per = G.per[0] | G.per[1] | G.per[2];
+#pragma unroll
+  for (int p = 0; p < NP; p++) {
+    const int j = w[p] & 31u;
+    const int ex = dir_of(dir_bits(EX), j), ey = dir_of(dir_bits(EY), j), ez = dir_of(dir_bits(EZ), j);
+    const int d = ex + G.px * (ey + G.ny * ez);
+    n1[p] = nd[p] + d;
+    n2[p] = nd[p] + 2 * d;
+  }
+  if (per) {
+#pragma unroll 1
+    for (int p = 0; p < NP; p++) {
+      const int j = w[p] & 31u;
+      const int ex = dir_of(dir_bits(EX), j), ey = dir_of(dir_bits(EY), j), ez = dir_of(dir_bits(EZ), j);
+      int x, y, z;
+      coords(G, nd[p], x, y, z);
+      n1[p] = (int)nbr(G, x, y, z, ex, ey, ez);
+      n2[p] = (int)nbr(G, x, y, z, 2 * ex, 2 * ey, 2 * ez);
+    }
+  }
+  C k0[NP], k1[NP], k2[NP], v0[NP], v1[NP], v2[NP];
+#pragma unroll
+  for (int p = 0; p < NP; p++) {
+    const int l = max(min(first + p * (int)blockDim.x, l1 - 1), 0);
+    const int j = w[p] & 31u, i = opp_of(j);
+    const bool hq = (w[p] >> 5) & 1u, h1 = (w[p] >> 6) & 1u, h2 = (w[p] >> 7) & 1u;
+    const int m1 = h1 ? n1[p] : nd[p], m2 = h2 ? n2[p] : nd[p];
+    const S* Ai = A + (long long)i * G.plane;
+    const S* At = hq ? A + (long long)j * G.plane : Ai;
+    v0[p] = to_c(Ai[nd[p]]);
+    v1[p] = to_c(At[hq ? nd[p] : m1]);
+    v2[p] = to_c(At[hq ? m1 : m2]);
+    k0[p] = lc[l];
+    k1[p] = lc[nl + l];
+    k2[p] = lc[2 * nl + l];
+  }
+#pragma unroll
+  for (int p = 0; p < NP; p++) {
+    const int l = first + p * (int)blockDim.x;
+    if (l < l1) s_link[l - l0] = k0[p] * v0[p] + k1[p] * v1[p] + k2[p] * v2[p];
+  }
+}
+
+template <class S>
+__device__ __forceinline__ void pull_records(const FluidArgs& a, int r0, typename Store<S>::C (&g)[19], int& node,
+                                             bool& on, bool& flagged) {
+  typedef typename Store<S>::C C;
+  const Grid& G = a.g;
+  const S* A = (const S*)a.A;
+  const int t = threadIdx.x, nt = (int)blockDim.x;
+  C* s_link = (C*)s_dyn;
+  on = r0 + t < a.nrec;
+  const int r = on ? r0 + t : a.nrec - 1;
+  const int l0 = a.rec_link0[r0], l1 = a.rec_link0[min(r0 + nt, a.nrec)];
+  node = a.rec_node[r];
   const uint32_t mask = a.rec_mask[r];
-  const uint32_t hqm = a.rec_mb[r];
   const int lk0 = a.rec_link0[r];
   const int fc = a.rec_face[r];
+  int nd[LINK_PASSES];
+  unsigned int w[LINK_PASSES];
+#pragma unroll
+  for (int p = 0; p < LINK_PASSES; p++) {
+    const int l = max(min(l0 + t + p * nt, l1 - 1), 0);
+    nd[p] = a.lk_node[l];
+    w[p] = a.lk_w[l];
+  }
+  // what comes after the pulls is loaded with them: the node's force flag and
+  // the imposed values of an open face
+  const uint8_t tfl = a.tflag ? a.tflag[node >> TILE_SHIFT] : 0;
+  double bc[4] = {0.0, 0.0, 0.0, 0.0};
+  if (fc != 0xff) {
+#pragma unroll
+    for (int k = 0; k < 4; k++) bc[k] = a.rec_bc[(long long)k * a.nrec + r];
+  }
   int x, y, z;
   coords(G, node, x, y, z);
-  const Hood h = hood(G, x, y, z);
   const int face = fc & 7, kind = (fc >> 4) & 1;
   const int ax = face >> 1, s = (face & 1) ? -1 : 1;
   C pl[19];
-  Bfl<S> bb[19];
-  pl[0] = ldA<S>(a, 0, node);
+  {
+    const Hood h = hood(G, x, y, z);
+    pl[0] = ldA<S>(a, 0, node);
 #pragma unroll
-  for (int j = 1; j < 19; j++) {
-    const int e[3] = {EX[j], EY[j], EZ[j]};
-    const bool linked = (mask >> j) & 1u;
-    const bool unknown = fc != 0xff && s * (ax == 0 ? e[0] : (ax == 1 ? e[1] : e[2])) == 1;
-    const bool plain = !linked && !unknown;
-    pl[j] = to_c(A[plain ? (long long)j * G.plane + h.at(-EX[j], -EY[j], -EZ[j]) : (long long)node]);
-    bb[j] = bfl_load<S>(a, j, linked, lk0 + __popc(mask & ((1u << j) - 1u)), (hqm >> j) & 1u, node, h);
+    for (int j = 1; j < 19; j++) {
+      const bool unknown = fc != 0xff && s * (ax == 0 ? EX[j] : (ax == 1 ? EY[j] : EZ[j])) == 1;
+      const bool plain = !((mask >> j) & 1u) && !unknown;
+      pl[j] = to_c(A[plain ? (long long)j * G.plane + h.at(-EX[j], -EY[j], -EZ[j]) : (long long)node]);
+    }
   }
+  link_values<S, LINK_PASSES>(a, l0, l1, l0 + t, nd, w, s_link);
+  for (int l = l0 + t + LINK_PASSES * nt; l < l1; l += nt) {  // a block with more links than the batch holds
+    const int nd1[1] = {a.lk_node[l]};
+    const unsigned int w1[1] = {a.lk_w[l]};
+    link_values<S, 1>(a, l0, l1, l, nd1, w1, s_link);
+  }
+  __syncthreads();
   g[0] = pl[0];
 #pragma unroll
   for (int j = 1; j < 19; j++) {
-    const int e[3] = {EX[j], EY[j], EZ[j]};
     const bool linked = (mask >> j) & 1u;
-    const bool unknown = fc != 0xff && s * (ax == 0 ? e[0] : (ax == 1 ? e[1] : e[2])) == 1;
-    g[j] = linked ? bfl_value<S>(bb[j]) : (unknown ? C(0) : pl[j]);
+    const bool unknown = fc != 0xff && s * (ax == 0 ? EX[j] : (ax == 1 ? EY[j] : EZ[j])) == 1;
+    g[j] = unknown ? C(0) : pl[j];
+    if (linked) g[j] = s_link[lk0 - l0 + __popc(mask & ((1u << j) - 1u))];
   }
-  if (fc != 0xff && zh) {
-    zouhe<C>(g, face, kind, (C)a.rec_bc[r], (C)a.rec_bc[a.nrec + r], (C)a.rec_bc[2 * a.nrec + r],
-             (C)a.rec_bc[3 * a.nrec + r]);
+  if (fc != 0xff) {
+    zouhe<C>(g, face, kind, (C)bc[0], (C)bc[1], (C)bc[2], (C)bc[3]);
   }
+  flagged = tfl != 0;
 }
 
 struct Moments {
@@ -469,22 +558,6 @@ __device__ __forceinline__ Moments streamed_moments(const FluidArgs& a, long lon
   return out;
 }
 
-// Streamed populations at any non-solid node.
-template <class S>
-__device__ __forceinline__ void pull_node(const FluidArgs& a, long long node,
-                                          typename Store<S>::C (&g)[19]) {
-  if (a.ncls[node] == CLS_BULK) {
-    const Grid& G = a.g;
-    int x, y, z;
-    coords(G, node, x, y, z);
-    const Hood h = hood(G, x, y, z);
-#pragma unroll
-    for (int j = 0; j < 19; j++) g[j] = ldA<S>(a, j, h.at(-EX[j], -EY[j], -EZ[j]));
-  } else {
-    pull_general<S>(a, a.rec_of[node], g);
-  }
-}
-
 template <class C>
 __device__ __forceinline__ void node_force(const FluidArgs& a, long long node, bool flagged, C& Fx,
                                            C& Fy, C& Fz) {
@@ -540,7 +613,7 @@ __device__ __forceinline__ bool last_block(unsigned int* counter, unsigned int n
 // stay inside the allocation for any group; values pulled for solid or
 // boundary-record nodes are computed and discarded.
 template <class S, int V, bool PERX>
-__device__ void fluid_bulk(const FluidArgs& a, int blk) {
+__device__ void fluid_bulk(const FluidArgs& a, int blk, unsigned int stop) {
   typedef typename Store<S>::C C;
   typedef typename Vec<S, V>::a vec;
   typedef typename Vec<S, V>::u vecu;
@@ -557,17 +630,21 @@ __device__ void fluid_bulk(const FluidArgs& a, int blk) {
     base = tile * ((long long)blockDim.x * V) + (long long)threadIdx.x * V;
   }
   if (base >= G.Np) return;
-  const typename ClsWord<V>::T cw = *(const typename ClsWord<V>::T*)(a.ncls + base);
   bool isb[V];
   bool all = true, any = false;
+  if (V == 1 && a.bulk_list) {
+    isb[0] = any = true;  // the list holds bulk nodes only
+  } else {
+    const typename ClsWord<V>::T cw = *(const typename ClsWord<V>::T*)(a.ncls + base);
 #pragma unroll
-  for (int k = 0; k < V; k++) {
-    isb[k] = ((cw >> (8 * k)) & 0xff) == CLS_BULK;
-    all = all && isb[k];
-    any = any || isb[k];
+    for (int k = 0; k < V; k++) {
+      isb[k] = ((cw >> (8 * k)) & 0xff) == CLS_BULK;
+      all = all && isb[k];
+      any = any || isb[k];
+    }
   }
   if (!any) return;
-  const bool flagged = a.tflag && a.tflag[base >> TILE_SHIFT];
+  const uint8_t tfl = a.tflag ? a.tflag[base >> TILE_SHIFT] : 0;
   const S* A = (const S*)a.A;
   S* B = (S*)a.B;
   const C omega = (C)a.omega;
@@ -612,6 +689,8 @@ __device__ void fluid_bulk(const FluidArgs& a, int blk) {
       for (int k = 0; k < V; k++) in[j][k] = pl[wrap2(x0 + k - EX[j], G.nx)];
     }
   }
+  if (stop) return;
+  const bool flagged = tfl != 0;
   bool bad = false;
 #pragma unroll
   for (int k = 0; k < V; k++) {
@@ -665,16 +744,17 @@ __device__ __forceinline__ void load_mac(const FluidArgs& a, long long node, dou
   uz = (double)v.w;
 }
 
-// Boundary record, one thread: all loads in one batch (pull_general), then
-// the forced collision; consecutive records are consecutive nodes, so the
+// A block of boundary records: pull_records, then the forced collision, one
+// record per thread.  Consecutive records are consecutive nodes, so the
 // loads of a wave are coalesced along x.
 template <class S>
-__device__ void fluid_record_thread(const FluidArgs& a, int r) {
+__device__ void fluid_record_block(const FluidArgs& a, int blk, unsigned int stop) {
   typedef typename Store<S>::C C;
   C g[19];
-  pull_general<S>(a, r, g);
-  const long long node = a.rec_node[r];
-  const bool flagged = a.tflag && a.tflag[node >> TILE_SHIFT];
+  int node;
+  bool on, flagged;
+  pull_records<S>(a, blk * (int)blockDim.x, g, node, on, flagged);
+  if (!on || stop) return;
   C Fx, Fy, Fz, drho, ux, uy, uz;
   node_force<C>(a, node, flagged, Fx, Fy, Fz);
   collide<C>(g, Fx, Fy, Fz, (C)a.omega, drho, ux, uy, uz);
@@ -691,15 +771,12 @@ __device__ void fluid_record_thread(const FluidArgs& a, int r) {
 // read A and write disjoint nodes of B and may run concurrently.
 template <class S, int V, bool PERX>
 __global__ __launch_bounds__(256) void k_fluid_bulk(FluidArgs a) {
-  if (a.flags->stop) return;
-  fluid_bulk<S, V, PERX>(a, xcd_remap(blockIdx.x, a.nbulk_blocks));
+  fluid_bulk<S, V, PERX>(a, xcd_remap(blockIdx.x, a.nbulk_blocks), a.flags->stop);
 }
 
 template <class S>
 __global__ __launch_bounds__(256) void k_fluid_rec(FluidArgs a) {
-  if (a.flags->stop) return;
-  const int r = xcd_remap(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
-  if (r < a.nrec) fluid_record_thread<S>(a, r);
+  fluid_record_block<S>(a, xcd_remap(blockIdx.x, gridDim.x), a.flags->stop);
 }
 
 // Small (cache-resident, latency-bound) grids: records and bulk tiles in one
@@ -707,20 +784,16 @@ __global__ __launch_bounds__(256) void k_fluid_rec(FluidArgs a) {
 // no fork and join between two streams.  Both parts use blocks of the same
 // size.
 template <class S, int V, bool PERX>
-__device__ __forceinline__ void fluid_unit(const FluidArgs& a, int nrb, int u) {
-  if (u < nrb) {
-    const int r = u * blockDim.x + threadIdx.x;
-    if (r < a.nrec) fluid_record_thread<S>(a, r);
-  } else {
-    fluid_bulk<S, V, PERX>(a, u - nrb);
-  }
+__device__ __forceinline__ void fluid_unit(const FluidArgs& a, int nrb, int u, unsigned int stop) {
+  if (u < nrb) fluid_record_block<S>(a, u, stop);
+  else fluid_bulk<S, V, PERX>(a, u - nrb, stop);
 }
 
 template <class S, int V, bool PERX>
 __global__ __launch_bounds__(256) void k_fluid_all(FluidArgs a, int nrb) {
-  if (a.flags->stop) return;
   const int b = blockIdx.x;
-  fluid_unit<S, V, PERX>(a, nrb, b < nrb ? xcd_remap(b, nrb) : nrb + xcd_remap(b - nrb, a.nbulk_blocks));
+  fluid_unit<S, V, PERX>(a, nrb, b < nrb ? xcd_remap(b, nrb) : nrb + xcd_remap(b - nrb, a.nbulk_blocks),
+                         a.flags->stop);
 }
 
 // Closes a fluid-only step (one thread).
@@ -2443,8 +2516,7 @@ template <class S, int V, bool PERX>
 __global__ __launch_bounds__(256) void kb_fluid_all(const BatchItem* items, const int2* map) {
   const int2 m = batch_unit(map);
   const FluidArgs a = batch_item(items, m.x).a;
-  if (a.flags->stop) return;
-  fluid_unit<S, V, PERX>(a, batch_item(items, m.x).nrb, m.y);
+  fluid_unit<S, V, PERX>(a, batch_item(items, m.x).nrb, m.y, a.flags->stop);
 }
 
 // Persistent form (its own kernel: holding an instance's arguments across
@@ -2467,7 +2539,8 @@ __global__ __launch_bounds__(256) void kb_fluid_all_persist(const BatchItem* ite
       nrb = batch_item(items, m.x).nrb;
       stop = a.flags->stop != 0u;
     }
-    if (!stop) fluid_unit<S, V, PERX>(a, nrb, m.y);
+    if (!stop) fluid_unit<S, V, PERX>(a, nrb, m.y, 0u);
+    __syncthreads();  // the next unit reuses the records' LDS
   }
 }
 
@@ -2475,9 +2548,7 @@ template <class S>
 __global__ __launch_bounds__(256) void kb_fluid_rec(const BatchItem* items, const int2* map) {
   const int2 m = batch_unit(map);
   const FluidArgs a = batch_item(items, m.x).a;
-  if (a.flags->stop) return;
-  const int r = m.y * blockDim.x + threadIdx.x;
-  if (r < a.nrec) fluid_record_thread<S>(a, r);
+  fluid_record_block<S>(a, m.y, a.flags->stop);
 }
 
 // Bulk tiles; per_xcd > 0 is the persistent form: per_xcd blocks on each of
@@ -2487,8 +2558,7 @@ template <class S, int V, bool PERX>
 __global__ __launch_bounds__(256) void kb_fluid_bulk(const BatchItem* items, const int2* map) {
   const int2 m = batch_unit(map);
   const FluidArgs a = batch_item(items, m.x).a;
-  if (a.flags->stop) return;
-  fluid_bulk<S, V, PERX>(a, m.y);
+  fluid_bulk<S, V, PERX>(a, m.y, a.flags->stop);
 }
 
 template <class S, int V, bool PERX>
@@ -2506,7 +2576,7 @@ __global__ __launch_bounds__(256) void kb_fluid_bulk_persist(const BatchItem* it
       a = batch_item(items, m.x).a;
       stop = a.flags->stop != 0u;
     }
-    if (!stop) fluid_bulk<S, V, PERX>(a, m.y);
+    if (!stop) fluid_bulk<S, V, PERX>(a, m.y, 0u);
   }
 }
 
@@ -2664,6 +2734,13 @@ __global__ void k_flush_fx(Grid G, long long* fx, double* fib) {
 
 static inline unsigned cdiv(long long a, long long b) { return (unsigned)((a + b - 1) / b); }
 
+// Dynamic LDS of a launch whose record blocks have this many threads.
+template <class S>
+static unsigned link_lds(const FluidArgs& a, int block) {
+  return (unsigned)((block == 64 ? a.lds_links[0] : (block == 128 ? a.lds_links[1] : a.lds_links[2])) *
+                    sizeof(typename Store<S>::C));
+}
+
 hipError_t launch_init(int prec, const Grid& g, void* f, const uint8_t* ncls, const double* rho,
                        const double* u, hipStream_t s) {
   const long long N = (long long)g.nx * g.ny * g.nz;
@@ -2704,20 +2781,24 @@ hipError_t launch_fluid_rec(int prec, const FluidArgs& a, hipStream_t s) {
   const unsigned grid = cdiv(a.nrec, a.rec_block);
   const unsigned blk = (unsigned)a.rec_block;
   switch (prec) {
-    case 0: k_fluid_rec<double><<<grid, blk, 0, s>>>(a); break;
-    case 1: k_fluid_rec<float><<<grid, blk, 0, s>>>(a); break;
-    default: k_fluid_rec<_Float16><<<grid, blk, 0, s>>>(a); break;
+    case 0: k_fluid_rec<double><<<grid, blk, link_lds<double>(a, blk), s>>>(a); break;
+    case 1: k_fluid_rec<float><<<grid, blk, link_lds<float>(a, blk), s>>>(a); break;
+    default: k_fluid_rec<_Float16><<<grid, blk, link_lds<_Float16>(a, blk), s>>>(a); break;
   }
   return hipGetLastError();
 }
 
 template <class S, int V>
 static void all_launch(const FluidArgs& a, int nrb, unsigned grid, hipStream_t s) {
-  if (a.g.per[0]) k_fluid_all<S, V, true><<<grid, a.bulk_block, 0, s>>>(a, nrb);
-  else k_fluid_all<S, V, false><<<grid, a.bulk_block, 0, s>>>(a, nrb);
+  const unsigned lds = nrb > 0 ? link_lds<S>(a, a.bulk_block) : 0u;
+  if (a.g.per[0]) k_fluid_all<S, V, true><<<grid, a.bulk_block, lds, s>>>(a, nrb);
+  else k_fluid_all<S, V, false><<<grid, a.bulk_block, lds, s>>>(a, nrb);
 }
 
 hipError_t launch_fluid_all(int prec, const FluidArgs& a, hipStream_t s) {
+  // no boundary records (an all-fluid periodic box): the bulk kernel, which
+  // has the smaller register budget (FP64: 76 registers against 131)
+  if (a.nrec == 0) return launch_fluid_bulk(prec, a, s);
   const int nrb = a.nrec > 0 ? (int)cdiv(a.nrec, a.bulk_block) : 0;
   const unsigned grid = (unsigned)(nrb + a.nbulk_blocks);
   if (grid == 0) return hipSuccess;
@@ -2785,14 +2866,15 @@ hipError_t launch_batch_ib_force(int prec, const BatchItem* items, const int2* m
 
 template <class S, int V>
 static void batch_fluid_launch(const BatchFluid& f, const BatchItem* items, hipStream_t s) {
+  const unsigned lds = (unsigned)(f.lds_links * sizeof(typename Store<S>::C));
   if (f.mode == 0) {
     if (f.n_all && f.per_xcd > 0)
-      kb_fluid_all_persist<S, V, false><<<8u * f.per_xcd, f.block, 0, s>>>(items, f.map_all, f.n_all, f.per_xcd);
+      kb_fluid_all_persist<S, V, false><<<8u * f.per_xcd, f.block, lds, s>>>(items, f.map_all, f.n_all, f.per_xcd);
     else if (f.n_all)
-      kb_fluid_all<S, V, false><<<f.n_all, f.block, 0, s>>>(items, f.map_all);
+      kb_fluid_all<S, V, false><<<f.n_all, f.block, lds, s>>>(items, f.map_all);
     return;
   }
-  if (f.n_rec) kb_fluid_rec<S><<<f.n_rec, f.block, 0, s>>>(items, f.map_rec);
+  if (f.n_rec) kb_fluid_rec<S><<<f.n_rec, f.block, lds, s>>>(items, f.map_rec);
   if (f.n_bulk && f.per_xcd > 0)
     kb_fluid_bulk_persist<S, V, false><<<8u * f.per_xcd, f.block, 0, s>>>(items, f.map_bulk, f.n_bulk, f.per_xcd);
   else if (f.n_bulk)
@@ -2926,16 +3008,19 @@ __device__ __forceinline__ void adj_fwd_bulk_one(const FluidArgs& a, int t) {
 }
 
 template <class S>
-__device__ __forceinline__ void adj_fwd_rec_one(const FluidArgs& a, double* hrec, int r) {
+__device__ __forceinline__ void adj_fwd_rec_block(const FluidArgs& a, double* hrec, int blk) {
   typedef typename Store<S>::C C;
   C g[19], dr, ux, uy, uz, Fx, Fy, Fz;
-  pull_general<S>(a, r, g);
+  int n;
+  bool on, flagged;
+  pull_records<S>(a, blk * (int)blockDim.x, g, n, on, flagged);
+  if (!on) return;
   if (hrec) {
+    const int r = blk * (int)blockDim.x + threadIdx.x;
 #pragma unroll
     for (int j = 0; j < 19; j++) hrec[(long long)j * a.nrec + r] = (double)g[j];
   }
-  const long long n = a.rec_node[r];
-  node_force<C>(a, n, a.tflag && a.tflag[n >> TILE_SHIFT], Fx, Fy, Fz);
+  node_force<C>(a, n, flagged, Fx, Fy, Fz);
   collide<C>(g, Fx, Fy, Fz, (C)a.omega, dr, ux, uy, uz);
   if (a.mac) store_mac<C>(a, n, dr, ux, uy, uz);
   S* B = (S*)a.B;
@@ -2955,8 +3040,7 @@ __global__ __launch_bounds__(256) void k_adj_fwd_bulk(FluidArgs a) {
 
 template <class S>
 __global__ __launch_bounds__(256) void k_adj_fwd_rec(FluidArgs a, double* hrec) {
-  const int r = blockIdx.x * 256 + threadIdx.x;
-  if (r < a.nrec) adj_fwd_rec_one<S>(a, hrec, r);
+  adj_fwd_rec_block<S>(a, hrec, blockIdx.x);
 }
 
 // Block b of a merged launch -> record block or bulk block, each part's
@@ -2970,8 +3054,7 @@ template <class S>
 __global__ __launch_bounds__(256) void k_adj_fwd_all(FluidArgs a, double* hrec, int rec_blocks) {
   const int u = adj_unit(blockIdx.x, rec_blocks, gridDim.x);
   if (u < rec_blocks) {
-    const int r = u * 256 + threadIdx.x;
-    if (r < a.nrec) adj_fwd_rec_one<S>(a, hrec, r);
+    adj_fwd_rec_block<S>(a, hrec, u);
   } else {
     const int t = (u - rec_blocks) * 256 + threadIdx.x;
     if (t < a.nbulk_nodes) adj_fwd_bulk_one<S>(a, t);
@@ -3381,11 +3464,12 @@ __global__ void k_adj_grad_final(const double* part, int nblk, double omega, con
 template <class S>
 static void adj_forward(const FluidArgs& a, double* hrec, int merged, hipStream_t s) {
   const int rb = (int)cdiv(a.nrec, 256), bb = (int)cdiv(a.nbulk_nodes, 256);
+  const unsigned lds = link_lds<S>(a, 256);
   if (merged) {
-    if (rb + bb > 0) k_adj_fwd_all<S><<<rb + bb, 256, 0, s>>>(a, hrec, rb);
+    if (rb + bb > 0) k_adj_fwd_all<S><<<rb + bb, 256, lds, s>>>(a, hrec, rb);
   } else {
     if (bb > 0) k_adj_fwd_bulk<S><<<bb, 256, 0, s>>>(a);
-    if (rb > 0) k_adj_fwd_rec<S><<<rb, 256, 0, s>>>(a, hrec);
+    if (rb > 0) k_adj_fwd_rec<S><<<rb, 256, lds, s>>>(a, hrec);
   }
 }
 
