@@ -124,8 +124,7 @@ struct lbm_ctx {
     }                                                                                \
   } while (0)
 
-// Block counters live after the flags word: 0 k_ib_force, 1 k_body_post,
-// 2 k_fluid (fluid-only steps), 3 k_check.
+// Block counters live after the flags word: 0 k_ib_force, 3 k_check.
 static unsigned int* counter(lbm_ctx* ctx, int k) { return (unsigned int*)(ctx->flags + 1) + k; }
 
 static lbm_status fail(lbm_ctx* ctx, lbm_status st, const std::string& msg) {
@@ -540,6 +539,9 @@ extern "C" const char* lbm_last_error(const lbm_ctx* ctx) { return ctx ? ctx->er
 static lbm_status read_flags(lbm_ctx* ctx, DevFlags* h) {
   CHK(hipStreamSynchronize(ctx->stream));
   CHK(hipMemcpy(h, ctx->flags, sizeof(DevFlags), hipMemcpyDeviceToHost));
+  // bits of the last step, which the next one would have moved
+  h->stop |= h->pend0 | h->pend1;
+  h->pend0 = h->pend1 = 0u;
   return LBM_OK;
 }
 
@@ -658,8 +660,14 @@ static lbm_status build_body_arrays(lbm_ctx* ctx, int cur, const std::vector<dou
   ctx->ne = e0;
   ctx->nh = e0;
   ctx->nsoft_v = (int)soft.size();
-  // vertex incidence tables, slot-major [VT_SLOTS][nv]
-  std::vector<int32_t> vtab((size_t)VT_SLOTS * v0, 0);
+  // vertex incidence tables, slot-major [nslot][nv]
+  int valence = 0;
+  {
+    std::vector<int> cnt(v0, 0);
+    for (int32_t v : edges) valence = std::max(valence, ++cnt[v]);
+  }
+  const int vt = valence <= VT_LOW ? VT_LOW : VT_MAX, nslot = 4 * vt;
+  std::vector<int32_t> vtab((size_t)nslot * v0, 0);
   // and the slot each (element, vertex role) writes its force into
   std::vector<int> ne_cnt(v0, 0), nh_cnt(v0, 0), nf_cnt(v0, 0);
   std::vector<int32_t> sl_edge(2 * (size_t)e0), sl_hinge(4 * (size_t)e0), sl_face(3 * (size_t)f0);
@@ -670,17 +678,17 @@ static lbm_status build_body_arrays(lbm_ctx* ctx, int cur, const std::vector<dou
     return true;
   };
   for (int e = 0; e < e0; e++) {
-    if (!put(edges[2 * e], 0, VT_E, ne_cnt, e + 1, sl_edge[2 * e]) ||
-        !put(edges[2 * e + 1], 0, VT_E, ne_cnt, -(e + 1), sl_edge[2 * e + 1]))
+    if (!put(edges[2 * e], 0, vt, ne_cnt, e + 1, sl_edge[2 * e]) ||
+        !put(edges[2 * e + 1], 0, vt, ne_cnt, -(e + 1), sl_edge[2 * e + 1]))
       return fail(ctx, LBM_E_INVAL, "vertex valence above 10");
   }
   for (int h = 0; h < e0; h++)
     for (int r = 0; r < 4; r++)
-      if (!put(hinges[4 * h + r], VT_E, VT_H, nh_cnt, 4 * h + r + 1, sl_hinge[4 * h + r]))
+      if (!put(hinges[4 * h + r], vt, 2 * vt, nh_cnt, 4 * h + r + 1, sl_hinge[4 * h + r]))
         return fail(ctx, LBM_E_INVAL, "vertex in more than 20 hinges");
   for (int f = 0; f < f0; f++)
     for (int r = 0; r < 3; r++)
-      if (!put(faces[3 * f + r], VT_E + VT_H, VT_F, nf_cnt, f + 1, sl_face[3 * f + r]))
+      if (!put(faces[3 * f + r], 3 * vt, vt, nf_cnt, f + 1, sl_face[3 * f + r]))
         return fail(ctx, LBM_E_INVAL, "vertex valence above 10");
   auto up = [&](auto** p, const auto& v) -> hipError_t {
     hipError_t e = upload(p, v);
@@ -770,14 +778,16 @@ static lbm_status build_body_arrays(lbm_ctx* ctx, int cur, const std::vector<dou
   int32_t *d_sle, *d_slh, *d_slf, *d_cbox;
   CHK(up(&d_cen, zf));
   CHK(up(&d_cbox, std::vector<int32_t>(6 * (size_t)B.n_marker_blocks, 0)));
-  CHK(up(&d_fext, zf));
+  CHK(up(&d_fext, std::vector<double>(6 * (size_t)f0, 0.0)));
   CHK(up(&d_u0v, zv));
   // slots nobody writes stay zero
-  CHK(up(&d_fslot, std::vector<double>((size_t)VT_SLOTS * 3 * v0, 0.0)));
+  CHK(up(&d_fslot, std::vector<double>((size_t)nslot * 3 * v0, 0.0)));
   CHK(up(&d_sle, sl_edge));
   CHK(up(&d_slh, sl_hinge));
   CHK(up(&d_slf, sl_face));
   B.f_slot = d_fslot;
+  B.nslot = nslot;
+  B.n_rigid = (int)std::count_if(brig.begin(), brig.end(), [](int32_t r) { return r != 0; });
   B.sl_edge = d_sle;
   B.sl_hinge = d_slh;
   B.sl_face = d_slf;
@@ -858,6 +868,7 @@ static lbm_status build_body_arrays(lbm_ctx* ctx, int cur, const std::vector<dou
     ctx->bargs[p] = B;
     ctx->bargs[p].Xcur = ctx->X[p];
     ctx->bargs[p].Xnext = ctx->X[p ^ 1];
+    ctx->bargs[p].par = p;
   }
   // force buffers (once)
   if (!ctx->fx[0]) {
@@ -1073,6 +1084,8 @@ static FluidArgs fluid_args(lbm_ctx* ctx, int p) {
   a.tflag = ib ? ctx->tf[p] : nullptr;
   a.mac = ib ? ctx->mac : nullptr;
   a.flags = ctx->flags;
+  a.par = p;
+  a.close_step = ib ? 0 : (ctx->nbulk_blocks > 0 ? 1 : 2);
   a.rec_block = ctx->rec_block;
   a.bulk_v = ctx->bulk_v;
   a.bulk_block = ctx->bulk_block;
@@ -1106,7 +1119,9 @@ static hipError_t enqueue_step(lbm_ctx* ctx, int p, hipStream_t s, hipEvent_t ev
   if (ev0 && (e = hipEventRecord(ev0, s)) != hipSuccess) return e;
   // (fluid_reps > 1 only for timing: the phase rewrites B and the macro field
   // from the same inputs, so repeating it leaves the step unchanged)
+  const int closes = a.close_step;
   for (int r = 0; r < fluid_reps; r++) {
+    a.close_step = r + 1 == fluid_reps ? closes : 0;
     if (ctx->fluid_merged) {
       if ((e = launch_fluid_all(ctx->prec, a, s)) != hipSuccess) return e;
     } else {
@@ -1125,11 +1140,8 @@ static hipError_t enqueue_step(lbm_ctx* ctx, int p, hipStream_t s, hipEvent_t ev
   if (ib) {
     const BodyArgs& b = ctx->bargs[p];
     if ((e = launch_mls_post(ctx->prec, a, b, ctx->fx[p ^ 1], ctx->tf[p ^ 1], s)) != hipSuccess) return e;
-    // a few tens of blocks close the step in their last one; more: k_close
-    const bool fold = body_post_blocks(b) <= 128;
-    if ((e = launch_body_post(b, ctx->flags, fold ? counter(ctx, 1) : nullptr, s)) != hipSuccess) return e;
-    if (!fold && (e = launch_close(ctx->flags, s)) != hipSuccess) return e;
-  } else {
+    if ((e = launch_body_post(b, ctx->flags, 1, s)) != hipSuccess) return e;
+  } else if (ctx->n_fluid == 0) {
     if ((e = launch_close(ctx->flags, s)) != hipSuccess) return e;
   }
   return hipSuccess;
@@ -1429,6 +1441,7 @@ static BatchFluid batch_fluid(const lbm_batch* b) {
   f.n_rec = b->n_rec;
   f.map_bulk = b->m_bulk;
   f.n_bulk = b->n_bulk;
+  f.close = 1;
   f.lds_links = 0;
   for (const lbm_ctx* c : b->ctx)
     f.lds_links = std::max(f.lds_links, c->lds_links[b->block == 64 ? 0 : (b->block == 128 ? 1 : 2)]);
@@ -1442,8 +1455,13 @@ static hipError_t batch_enqueue(lbm_batch* b, int q, hipStream_t s) {
   if ((e = launch_batch_ib_force(b->prec, it, b->m_ib, b->n_ib, s)) != hipSuccess) return e;
   if ((e = launch_batch_fluid(b->prec, batch_fluid(b), it, s)) != hipSuccess) return e;
   if ((e = launch_batch_mls_post(b->prec, it, b->m_mls, b->n_mls, s)) != hipSuccess) return e;
-  if ((e = launch_batch_body_post(it, b->m_body, b->n_body, s)) != hipSuccess) return e;
-  return launch_batch_close(it, (int)b->ctx.size(), s);
+  int block = 64;  // rigid bodies take 256 threads
+  for (const lbm_ctx* c : b->ctx)
+    if (c->nf > 0 && c->bargs[0].n_rigid) block = 256;
+  if ((e = launch_batch_body_post(it, b->m_body, b->n_body, block, s)) != hipSuccess) return e;
+  for (const lbm_ctx* c : b->ctx)
+    if (c->nf == 0 && c->n_fluid == 0 && (e = launch_close(c->flags, s)) != hipSuccess) return e;
+  return hipSuccess;
 }
 
 static lbm_status batch_ready(lbm_batch* b) {
@@ -1569,7 +1587,8 @@ static lbm_status batch_time_fluid(lbm_batch* b, int reps, double* ms) {
   if (st) return st;
   const int q = (int)(b->enq & 1);
   const BatchItem* it = b->items + (size_t)q * b->ctx.size();
-  const BatchFluid f = batch_fluid(b);
+  BatchFluid f = batch_fluid(b);
+  f.close = 0;
   hipEvent_t e0, e1;
   CHKB(hipEventCreate(&e0));
   CHKB(hipEventCreate(&e1));
@@ -1582,8 +1601,9 @@ static lbm_status batch_time_fluid(lbm_batch* b, int reps, double* ms) {
   CHKB(hipEventElapsedTime(&t, e0, e1));
   CHKB(hipEventDestroy(e0));
   CHKB(hipEventDestroy(e1));
-  for (lbm_ctx* c : b->ctx)
-    CHKB(hipMemsetAsync((char*)c->flags + offsetof(DevFlags, pending), 0, sizeof(uint32_t), b->stream));
+  for (lbm_ctx* c : b->ctx)  // (this parity's bits; those of the step before stay)
+    CHKB(hipMemsetAsync((char*)c->flags + ((c->enq & 1) ? offsetof(DevFlags, pend1) : offsetof(DevFlags, pend0)), 0,
+                        sizeof(uint32_t), b->stream));
   CHKB(hipStreamSynchronize(b->stream));
   *ms = (double)t / reps;
   return LBM_OK;
@@ -2000,7 +2020,7 @@ static lbm_status adjoint_sweep(lbm_ctx* ctx, int32_t n_steps, int32_t every, co
     if ((e = launch_ib_force(ctx->prec, fa, b2, q.fx[0], q.tf[0], q.fx[1], q.tf[1], q.cnt, s)) != hipSuccess) return e;
     if ((e = launch_adjoint_forward(ctx->prec, fa, hrec, merged, s)) != hipSuccess) return e;
     if ((e = launch_mls_post(ctx->prec, fa, b2, q.fx[1], q.tf[1], s)) != hipSuccess) return e;
-    if ((e = launch_body_post(b2, q.flags, nullptr, s)) != hipSuccess) return e;
+    if ((e = launch_body_post(b2, q.flags, 0, s)) != hipSuccess) return e;
     if ((e = launch_close(q.flags, s)) != hipSuccess) return e;
     // this step's force field is not needed again: clear it (the forcing of
     // the next step spreads into the same buffer)

@@ -39,14 +39,22 @@ constexpr int CHUNK_CAP = 3;        // marker chunks per 64 faces of a body
 // MLS point, outer and inner probe) or 16 vertices.
 constexpr int MLS_FACES_PER_WAVE = 8, MLS_VERTS_PER_WAVE = 16;
 
-// Vertex incidence table widths (largest vertex valence accepted: 10).
-constexpr int VT_E = 10, VT_H = 20, VT_F = 10, VT_SLOTS = VT_E + VT_H + VT_F;
+// Vertex incidence table widths (largest vertex valence accepted: VT_MAX).
+// A mesh whose vertices have at most VT_LOW neighbours (an icosphere) uses
+// the narrow table (24 slots instead of 40: the unused ones hold zeros, and
+// the vertex update reads them all).
+constexpr int VT_MAX = 10, VT_LOW = 6;
+constexpr int VT_SLOTS = 4 * VT_MAX, VT_SLOTS_LOW = 4 * VT_LOW;  // edges, hinges (two per neighbour), faces
 
+// A step of parity p raises bits in pend0 (p = 0) or pend1: they do not stop
+// its own launches, and stop every launch of the next step, whose closing
+// launch moves them to stop.  Closing a step is then one thread of its last
+// launch counting it, with nothing to wait for.
 struct DevFlags {
-  uint32_t stop;      // sticky stop bits (checked at every kernel entry)
-  uint32_t pending;   // bits raised during the current step
+  uint32_t stop;      // sticky stop bits
+  uint32_t pend0;     // bits raised during a step of parity 0
   uint32_t overflow;  // a spread contribution exceeded +-1 (also raises ST_UNSTABLE)
-  uint32_t pad;
+  uint32_t pend1;     // bits raised during a step of parity 1
   long long steps_done;
   int mls_singular;
   int pad2;
@@ -95,8 +103,8 @@ struct FluidArgs {
   const uint8_t* tflag;      // tile flags of this step (may be null)
   void* mac;                 // [Np][4] rho - 1, u of this step in the compute type (null: not kept)
   DevFlags* flags;
-  unsigned int* counter;     // block counter used when this launch closes the step
-  int close_step;            // 1: no bodies, this launch is the whole step
+  int par;                   // parity of the step
+  int close_step;            // no bodies, the step closes here: 1 in the first bulk block, 2 in the first record block
   int rec_block;             // threads per block of the record kernel
   int bulk_v;                // nodes per thread of the bulk kernel (0: list form, one)
   int bulk_block;            // threads per block of the bulk kernel
@@ -119,10 +127,13 @@ struct BodyArgs {
   const int32_t* hinges;       // [nh][4]
   const double* theta0;        // [nh]
   const double* kb;            // [nh]
-  // Forces on vertices by incidence slot, [VT_SLOTS][3][nv]: VT_E edge slots,
-  // VT_H hinge slots, VT_F face slots per vertex (unused slots hold 0); the
-  // element of slot-major index sl_*[...] writes there.
+  // Forces on vertices by incidence slot, [nslot][3][nv]: edge slots, hinge
+  // slots, face slots of each vertex (unused slots hold 0); the element of
+  // slot-major index sl_*[...] writes there.
   double* f_slot;
+  int nslot;                   // VT_SLOTS or VT_SLOTS_LOW
+  int n_rigid;                 // rigid (or fixed) bodies
+  int par;                     // parity of the step
   const int32_t* sl_edge;      // [ne][2] slot of the edge's force at its two ends
   const int32_t* sl_hinge;     // [nh][4] slot of the hinge's force at its four vertices
   const int32_t* sl_face;      // [nf][3] slot of a third of the face force at its vertices
@@ -159,7 +170,7 @@ struct BodyArgs {
   const long long* b_key0;     // [nbody] offset of each body's part of bin_keys
   // per face / vertex work arrays
   double* centroid;            // [nf][3] by slot
-  double* fext;                // [nf][3] hydrodynamic + repulsion force
+  double* fext;                // [nf][6] hydrodynamic + repulsion force and centroid (rigid bodies)
   int* chunk_box;              // [n_marker_blocks][6] box of stencil bases of each chunk
   // Two-pass spread (null: one pass with atomics): each marker block's box
   // sums, [n_marker_blocks][BOX_CELLS][3] fixed point, and the node of each
@@ -197,10 +208,9 @@ hipError_t launch_ib_force(int prec, const FluidArgs& a, const BodyArgs& b, long
                            unsigned int* counter, hipStream_t s);
 hipError_t launch_mls_post(int prec, const FluidArgs& a, const BodyArgs& b, long long* fxp, uint8_t* tfp,
                            hipStream_t s);
-// with a counter (zeroed; left zeroed) it closes the step (steps_done, stop
-// from pending) in its last block; with null, launch_close must follow
-hipError_t launch_body_post(const BodyArgs& b, DevFlags* flags, unsigned int* counter, hipStream_t s);
-// blocks of launch_body_post (the host's choice of closing in it)
+// close: it also closes the step; else launch_close must follow
+hipError_t launch_body_post(const BodyArgs& b, DevFlags* flags, int close, hipStream_t s);
+// units of the vertex update: one per body (rigid ones), then 64 soft vertices each
 inline unsigned body_post_blocks(const BodyArgs& b) { return (unsigned)b.nbody + (unsigned)((b.nsoft_v + 63) / 64); }
 // Mass and momentum sums of the last completed step into out[5] (non-solid
 // node count, sum of deviations, momentum); part holds 5 x 1024 doubles.
@@ -357,6 +367,7 @@ struct BatchFluid {
   const int2* map_all; int n_all;
   const int2* map_rec; int n_rec;
   const int2* map_bulk; int n_bulk;
+  int close;      // 0: timing only, no step is counted
   int lds_links;  // most links of a record block of any instance
 };
 
@@ -366,7 +377,6 @@ hipError_t launch_batch_ib_force(int prec, const BatchItem* items, const int2* m
 hipError_t launch_batch_fluid(int prec, const BatchFluid& f, const BatchItem* items, hipStream_t s);
 hipError_t launch_batch_mls_post(int prec, const BatchItem* items, const int2* map, int n,
                                  hipStream_t s);
-hipError_t launch_batch_body_post(const BatchItem* items, const int2* map, int n, hipStream_t s);
-hipError_t launch_batch_close(const BatchItem* items, int n, hipStream_t s);
+hipError_t launch_batch_body_post(const BatchItem* items, const int2* map, int n, int block, hipStream_t s);
 
 }  // namespace lbm
