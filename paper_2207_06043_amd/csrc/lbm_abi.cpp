@@ -882,6 +882,7 @@ static lbm_status build_body_arrays(lbm_ctx* ctx, int cur, const std::vector<dou
     const size_t macb = 4 * (size_t)ctx->g.Np * (ctx->prec == 0 ? sizeof(double) : sizeof(float));
     CHK(hipMalloc(&ctx->mac, macb));
     CHK(hipMemset(ctx->mac, 0, macb));
+    CHK(launch_mac_solid(ctx->prec, ctx->g, ctx->mac, ctx->ncls, ctx->stream));
   }
   // marker order of the current positions, and their diagnostics
   CHK(launch_bin_faces(ctx->bargs[cur], ctx->stream));

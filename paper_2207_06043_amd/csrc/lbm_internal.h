@@ -196,7 +196,12 @@ struct BatchItem {
   int pad;
 };
 
+// rho - 1 of a solid node in the macro field (no fluid node comes near it).
+constexpr double MAC_SOLID = -1e30;
+
 // Launchers (lbm_kernels.hip)
+// Writes MAC_SOLID at the solid nodes of a new macro field.
+hipError_t launch_mac_solid(int prec, const Grid& g, void* mac, const uint8_t* ncls, hipStream_t s);
 hipError_t launch_init(int prec, const Grid& g, void* f, const uint8_t* ncls, const double* rho,
                        const double* u, hipStream_t s);
 hipError_t launch_fluid_bulk(int prec, const FluidArgs& a, hipStream_t s);

@@ -730,6 +730,14 @@ __device__ void fluid_bulk(const FluidArgs& a, int blk, unsigned int halt) {
   if (bad) raise_pending(a.flags, a.par, ST_UNSTABLE);
 }
 
+// Marks the solid nodes of the macro field (and the padding), which the
+// fluid launches never write: the fits tell them by it.
+template <class C>
+__global__ void k_mac_solid(Grid G, C* mac, const uint8_t* ncls) {
+  const long long p = blockIdx.x * (long long)blockDim.x + threadIdx.x;
+  if (p < G.Np && ncls[p] == CLS_SOLID) mac[4 * p] = C(MAC_SOLID);
+}
+
 // This step's rho - 1 and u at a node (what the probes and the vertex
 // velocities interpolate), [Np][4] in the compute type.
 template <class C>
@@ -992,11 +1000,12 @@ __device__ __forceinline__ void face_geom_pts(const double (&pa)[3], const doubl
   double u[3] = {pb[0] - pa[0], pb[1] - pa[1], pb[2] - pa[2]};
   double v[3] = {pd[0] - pa[0], pd[1] - pa[1], pd[2] - pa[2]};
   double N[3] = {u[1] * v[2] - u[2] * v[1], u[2] * v[0] - u[0] * v[2], u[0] * v[1] - u[1] * v[0]};
-  double l = sqrt(N[0] * N[0] + N[1] * N[1] + N[2] * N[2]);
+  const double q = N[0] * N[0] + N[1] * N[1] + N[2] * N[2];
+  const double l = sqrt(q), il = 1.0 / l;
 #pragma unroll
   for (int k = 0; k < 3; k++) {
-    c[k] = (pa[k] + pb[k] + pd[k]) / 3.0;
-    n[k] = N[k] / l;
+    c[k] = (pa[k] + pb[k] + pd[k]) * (1.0 / 3.0);
+    n[k] = N[k] * il;
   }
   area = 0.5 * l;
 }
@@ -1314,8 +1323,7 @@ __device__ __forceinline__ bool chol4(const double (&A)[10], Chol4& c) {
 #pragma unroll
     for (int k = 0; k < j; k++) d -= c.L[j][k] * c.L[j][k];
     if (!(d > 1e-10 * dmax)) ok = false;
-    c.L[j][j] = ok ? sqrt(d) : 1.0;
-    c.r[j] = 1.0 / c.L[j][j];
+    c.r[j] = ok ? rsqrt(d) : 1.0;
 #pragma unroll
     for (int i = j + 1; i < 4; i++) {
       double v = M[i][j];
@@ -1367,11 +1375,136 @@ __device__ __forceinline__ double sel3(int i, const double (&w)[3]) {
   return i == 0 ? w[0] : (i == 1 ? w[1] : w[2]);
 }
 
+// Exchanges inside a quad of lanes as DPP moves (a shuffle would go through
+// the LDS pipe): lane i takes the value of lane SEL_i, two bits each in CTRL.
+template <int CTRL>
+__device__ __forceinline__ double quad_perm(double v) {
+  const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xf, 0xf, true);
+  return __hiloint2double(hi, lo);
+}
 __device__ __forceinline__ double quad_sum(double v) {
-  v += __shfl_xor(v, 1, 4);
-  v += __shfl_xor(v, 2, 4);
+  v += quad_perm<0xB1>(v);  // lanes 1 0 3 2
+  v += quad_perm<0x4E>(v);  // lanes 2 3 0 1
   return v;
 }
+template <int L>
+__device__ __forceinline__ double quad_lane(double v) {
+  return quad_perm<0x55 * L>(v);
+}
+
+// The nine per-axis weights of a quad's point, three exponentials per lane
+// (sub: lane in the quad) instead of nine.
+__device__ __forceinline__ void quad_weights(int sub, const double (&p)[3], const int (&base)[3], double (&wx)[3],
+                                             double (&wy)[3], double (&wz)[3]) {
+  auto w = [](double pa, int ba, int off) {
+    const double d = (double)(ba + off - 1) - pa;
+    return exp(-(d * d) * MLS_K);
+  };
+  const double e0 = sub == 3 ? w(p[1], base[1], 0) : w(p[0], base[0], sub);
+  const double e1 = w(sub < 2 ? p[1] : p[2], sub < 2 ? base[1] : base[2], sub < 2 ? sub + 1 : sub - 2);
+  const double e2 = w(p[2], base[2], 2);
+  wx[0] = quad_lane<0>(e0);
+  wx[1] = quad_lane<1>(e0);
+  wx[2] = quad_lane<2>(e0);
+  wy[0] = quad_lane<3>(e0);
+  wy[1] = quad_lane<0>(e1);
+  wy[2] = quad_lane<1>(e1);
+  wz[0] = quad_lane<2>(e1);
+  wz[1] = quad_lane<3>(e1);
+  wz[2] = e2;
+}
+
+// A quad's share of the 27 supports: nine rows of three along x, row r at
+// (y, z) offsets (r % 3, r / 3).  Lane sub takes rows sub and sub + 4 and, of
+// row 8, the support at x offset sub (lane 3: none).  A row is summed along x
+// first, then enters the sums of the fit with its weight in y and z: half the
+// operations of adding support by support.
+__device__ __forceinline__ void row_yz(int r, int& ky, int& kz) {
+  kz = (r >= 3) + (r >= 6);
+  ky = r - 3 * kz;
+}
+
+// Sums of one row: wx, wx dx, wx dx^2 over its usable supports, and per field
+// f the sums of wx f, wx dx f.
+template <int NF>
+struct RowSums {
+  double m0, m1, m2, f0[NF], f1[NF];
+  __device__ __forceinline__ void clear() {
+    m0 = m1 = m2 = 0.0;
+#pragma unroll
+    for (int q = 0; q < NF; q++) f0[q] = f1[q] = 0.0;
+  }
+  __device__ __forceinline__ void add(double w, double d, const double (&f)[NF]) {
+    const double wd = w * d;
+    m0 += w;
+    m1 += wd;
+    m2 += wd * d;
+#pragma unroll
+    for (int q = 0; q < NF; q++) {
+      f0[q] += w * f[q];
+      f1[q] += wd * f[q];
+    }
+  }
+};
+
+// The moment matrix (packed as in mls_add) and the right-hand sides of a fit.
+template <int NF>
+struct FitSums {
+  double A[10], b[NF][4];
+  __device__ __forceinline__ void clear() {
+#pragma unroll
+    for (int k = 0; k < 10; k++) A[k] = 0.0;
+#pragma unroll
+    for (int q = 0; q < NF; q++)
+#pragma unroll
+      for (int k = 0; k < 4; k++) b[q][k] = 0.0;
+  }
+  __device__ __forceinline__ void add(const RowSums<NF>& s, double w, double dy, double dz) {
+    const double wy = w * dy, wz = w * dz;
+    A[0] += w * s.m0;
+    A[1] += w * s.m1;
+    A[2] += wy * s.m0;
+    A[3] += wz * s.m0;
+    A[4] += w * s.m2;
+    A[5] += wy * s.m1;
+    A[6] += wz * s.m1;
+    A[7] += wy * dy * s.m0;
+    A[8] += wy * dz * s.m0;
+    A[9] += wz * dz * s.m0;
+#pragma unroll
+    for (int q = 0; q < NF; q++) {
+      b[q][0] += w * s.f0[q];
+      b[q][1] += w * s.f1[q];
+      b[q][2] += wy * s.f0[q];
+      b[q][3] += wz * s.f0[q];
+    }
+  }
+  __device__ __forceinline__ void quad() {
+#pragma unroll
+    for (int k = 0; k < 10; k++) A[k] = quad_sum(A[k]);
+#pragma unroll
+    for (int q = 0; q < NF; q++)
+#pragma unroll
+      for (int k = 0; k < 4; k++) b[q][k] = quad_sum(b[q][k]);
+  }
+};
+
+// The three coordinates base - 1 .. base + 1 on an axis of n nodes as terms
+// of a padded index (stride st), and whether they lie in the box (a periodic
+// axis wraps; positions may have left the box by any number of periods).
+__device__ __forceinline__ void axis_nodes(int base, int n, int periodic, int st, int (&o)[3], bool (&in)[3]) {
+  if (periodic && (base < 0 || base >= n)) base = ((base % n) + n) % n;
+#pragma unroll
+  for (int i = 0; i < 3; i++) {
+    int c = base + i - 1;
+    in[i] = periodic || (c >= 0 && c < n);
+    if (periodic) c = c < 0 ? c + n : (c >= n ? c - n : c);
+    o[i] = in[i] ? st * c : 0;
+  }
+}
+__device__ __forceinline__ int sel3i(int i, const int (&w)[3]) { return i == 0 ? w[0] : (i == 1 ? w[1] : w[2]); }
+__device__ __forceinline__ bool sel3b(int i, const bool (&w)[3]) { return i == 0 ? w[0] : (i == 1 ? w[1] : w[2]); }
 
 template <class S>
 __device__ void marker_block(const FluidArgs& a, const BodyArgs& b, int blk, long long* fxc,
@@ -2040,94 +2173,105 @@ __global__ __launch_bounds__(256) void k_check(BodyArgs b, const double* X0, con
 }
 
 // ---------------------------------------------------------- k_mls_post
-// One MLS point per lane, supports read from this step's rho - 1 and u.
-// Face waves (32 faces each): lanes 0-31 take the probe 1.2 dx outside
-// their face, lanes 32-63 the probe inside the same face; each fits rho
+// One MLS point per quad of lanes, supports read from this step's rho - 1
+// and u.  Face waves (8 faces each): lanes 0-31 take the probes 1.2 dx outside
+// their faces, lanes 32-63 the probes inside the same faces; each fits rho
 // (value) and u (gradient) by moving least squares (the linear-fit
 // coefficients), then the outer lane forms the traction: pressure p = rho/3
 // and viscous stress rho nu (grad u + grad u^T) (Eqs. hydroForP,
 // hydroForNu), the repulsion of centroids of other bodies closer than dx
 // (Eq. collision) and, for soft bodies, the volume penalty
 // k_v (1 - V/V0) A n (Eq. volFor, outward n).  A singular fit gives 0.
-// Vertex waves (64 soft vertices each): the MLS velocity u_v,0 at x_v^n.
-template <class S>
-__device__ __forceinline__ void fit_point(const FluidArgs& a, int sub, double px, double py, double pz,
-                                          bool want_grad, double& rfit, double (&val)[3],
-                                          double (&grad)[3][3]) {
+// Vertex waves (16 soft vertices each): the MLS velocity u_v,0 at x_v^n.
+// Bound by waiting for dependent loads and, with many faces, by instruction
+// issue: the tables a face needs are loaded in two rounds ahead of the fit (the
+// traction's among them), solid nodes are told by the macro field itself, a
+// quad shares its nine exponentials and adds its partial sums by DPP moves, and
+// supports are summed row by row.  Measured per launch, before -> after: one
+// capsule 10.3 -> 7.6 us, a train of three 14.4 -> 10.9, a small sphere in
+// FP64 8.5 -> 6.7, 16 capsules 72 -> 52, a sweep of ten instances 24.7 -> 17.9.
+template <class S, bool GRAD>
+__device__ __forceinline__ void fit_point(const FluidArgs& a, unsigned int halt, int sub, const double (&p)[3],
+                                          double& rfit, double (&val)[3], double (&grad)[3][3]) {
   typedef typename Store<S>::C C;
   typedef C C4 __attribute__((ext_vector_type(4)));
   const Grid& G = a.g;
-  const int bx = (int)floor(px + 0.5), by = (int)floor(py + 0.5), bz = (int)floor(pz + 0.5);
-  // this lane's supports k = sub, sub + 4, ... : loads first, all together
-  // (out-of-box supports read node 0 and are not used; solid nodes hold
-  // zeros and get W = 0)
-  bool use[7];
+  const int bs[3] = {(int)floor(p[0] + 0.5), (int)floor(p[1] + 0.5), (int)floor(p[2] + 0.5)};
+  // this lane's seven supports: loads first, all together (out-of-box supports
+  // read a node of the box and are not used; solid nodes hold MAC_SOLID)
+  int ox[3], oy[3], oz[3];
+  bool ix[3], iy[3], iz[3];
+  axis_nodes(bs[0], G.nx, G.per[0], 1, ox, ix);
+  axis_nodes(bs[1], G.ny, G.per[1], G.px, oy, iy);
+  axis_nodes(bs[2], G.nz, G.per[2], G.px * G.ny, oz, iz);
+  const C4* mac = (const C4*)a.mac;
   C4 mv[7];
-  uint8_t cls[7];
+  bool in[7];
+  int ky[3], kz[3];
 #pragma unroll
-  for (int i = 0; i < 7; i++) {
-    const int k = sub + 4 * i;
-    long long node = 0;
-    int c[3] = {bx + k % 3 - 1, by + (k / 3) % 3 - 1, bz + k / 9 - 1};
-    const int dim[3] = {G.nx, G.ny, G.nz};
-    bool in = k < 27;
+  for (int i = 0; i < 2; i++) {
+    row_yz(sub + 4 * i, ky[i], kz[i]);
+    const int row = sel3i(ky[i], oy) + sel3i(kz[i], oz);
+    const bool rin = sel3b(ky[i], iy) && sel3b(kz[i], iz);
 #pragma unroll
-    for (int q = 0; q < 3; q++)
-      if (c[q] < 0 || c[q] >= dim[q]) {
-        if (G.per[q]) c[q] = ((c[q] % dim[q]) + dim[q]) % dim[q];
-        else in = false;
-      }
-    if (in) node = c[0] + (long long)G.px * (c[1] + (long long)G.ny * c[2]);
-    use[i] = in;
-    cls[i] = a.ncls[node];
-    mv[i] = ((const C4*)a.mac)[node];
+    for (int k = 0; k < 3; k++) {
+      mv[3 * i + k] = mac[ox[k] + row];
+      in[3 * i + k] = rin && ix[k];
+    }
   }
-  double wx[3], wy[3], wz[3];
-  axis_weights(px, bx, wx);
-  axis_weights(py, by, wy);
-  axis_weights(pz, bz, wz);
-  double A[10] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0}, br[4] = {0, 0, 0, 0};
-  double bu[3][4] = {{0, 0, 0, 0}, {0, 0, 0, 0}, {0, 0, 0, 0}};
+  ky[2] = kz[2] = 2;
+  mv[6] = mac[sel3i(sub, ox) + oy[2] + oz[2]];
+  in[6] = sub < 3 && sel3b(sub, ix) && iy[2] && iz[2];
+  double wx[3], wy[3], wz[3], dx[3];
+  quad_weights(sub, p, bs, wx, wy, wz);
 #pragma unroll
-  for (int i = 0; i < 7; i++) {
-    const int k = sub + 4 * i;
-    const int kx = k % 3, ky = (k / 3) % 3, kz = k / 9;
-    const double dx = (bx + kx - 1) - px, dy = (by + ky - 1) - py, dz = (bz + kz - 1) - pz;
-    const bool u = use[i] && cls[i] != CLS_SOLID;
-    const double W = u ? sel3(kx, wx) * sel3(ky, wy) * sel3(kz, wz) : 0.0;
-    const double dr = u ? (double)mv[i].x : 0.0;
-    const double u3[3] = {u ? (double)mv[i].y : 0.0, u ? (double)mv[i].z : 0.0, u ? (double)mv[i].w : 0.0};
-    mls_add(A, W, dx, dy, dz);
-    mls_rhs(br, W, dx, dy, dz, dr);
+  for (int k = 0; k < 3; k++) dx[k] = (double)(bs[0] + k - 1) - p[0];
+  constexpr int NF = GRAD ? 4 : 3;  // u and, at the probes, rho - 1
+  FitSums<NF> fs;
+  fs.clear();
 #pragma unroll
-    for (int q = 0; q < 3; q++) mls_rhs(bu[q], W, dx, dy, dz, u3[q]);
+  for (int i = 0; i < 3; i++) {
+    RowSums<NF> rs;
+    rs.clear();
+#pragma unroll
+    for (int k = 0; k < (i < 2 ? 3 : 1); k++) {
+      const C4& v = mv[3 * i + k];
+      const bool u = in[3 * i + k] && !(v.x <= C(MAC_SOLID));
+      const double w = u ? (i < 2 ? wx[k] : sel3(sub, wx)) : 0.0, d = i < 2 ? dx[k] : sel3(sub, dx);
+      double f[NF];
+      f[0] = u ? (double)v.y : 0.0;
+      f[1] = u ? (double)v.z : 0.0;
+      f[2] = u ? (double)v.w : 0.0;
+      if (GRAD) f[NF - 1] = u ? (double)v.x : 0.0;
+      rs.add(w, d, f);
+    }
+    const double dy = (double)(bs[1] + ky[i] - 1) - p[1], dz = (double)(bs[2] + kz[i] - 1) - p[2];
+    fs.add(rs, sel3(ky[i], wy) * sel3(kz[i], wz), dy, dz);
   }
-  // the quad's four partial sums, in a fixed order
-#pragma unroll
-  for (int k = 0; k < 10; k++) A[k] = quad_sum(A[k]);
-#pragma unroll
-  for (int k = 0; k < 4; k++) br[k] = quad_sum(br[k]);
-#pragma unroll
-  for (int q = 0; q < 3; q++)
-#pragma unroll
-    for (int k = 0; k < 4; k++) bu[q][k] = quad_sum(bu[q][k]);
+  fs.quad();  // the quad's four partial sums, in a fixed order
   Chol4 ch;
-  const bool ok = chol4(A, ch);
-  if (!ok && sub == 0) atomicAdd(&a.flags->mls_singular, 1);
+  const bool ok = chol4(fs.A, ch);
+  if (!ok && sub == 0 && !halt) atomicAdd(&a.flags->mls_singular, 1);
   double cc[4] = {0.0, 0.0, 0.0, 0.0};
   if (ok) {
     const double e0[4] = {1.0, 0.0, 0.0, 0.0};
     chol_solve(ch, e0, cc);
   }
   // the weights add up to 1, so the fit of rho is 1 + the fit of rho - 1
-  rfit = ok ? 1.0 + (cc[0] * br[0] + cc[1] * br[1] + cc[2] * br[2] + cc[3] * br[3]) : 0.0;
+  if (GRAD) {
+    const double (&br)[4] = fs.b[NF - 1];
+    rfit = ok ? 1.0 + (cc[0] * br[0] + cc[1] * br[1] + cc[2] * br[2] + cc[3] * br[3]) : 0.0;
+  }
 #pragma unroll
   for (int q = 0; q < 3; q++) {
-    val[q] = cc[0] * bu[q][0] + cc[1] * bu[q][1] + cc[2] * bu[q][2] + cc[3] * bu[q][3];
-    double x[4] = {0.0, 0.0, 0.0, 0.0};
-    if (ok && want_grad) chol_solve(ch, bu[q], x);
+    const double (&bu)[4] = fs.b[q];
+    if (!GRAD) val[q] = cc[0] * bu[0] + cc[1] * bu[1] + cc[2] * bu[2] + cc[3] * bu[3];
+    if (GRAD) {
+      double x[4] = {0.0, 0.0, 0.0, 0.0};
+      if (ok) chol_solve(ch, bu, x);
 #pragma unroll
-    for (int c = 0; c < 3; c++) grad[q][c] = x[1 + c];
+      for (int c = 0; c < 3; c++) grad[q][c] = x[1 + c];
+    }
   }
 }
 
@@ -2136,7 +2280,7 @@ __device__ __forceinline__ void fit_point(const FluidArgs& a, int sub, double px
 // soft vertices, one quad each.
 
 template <class S>
-__device__ __forceinline__ void mls_post_block(const FluidArgs& a, const BodyArgs& b, int blk) {
+__device__ __forceinline__ void mls_post_block(const FluidArgs& a, const BodyArgs& b, int blk, unsigned int halt) {
   const int gw = (blk * 256 + threadIdx.x) >> 6;
   const int l = threadIdx.x & 63, sub = l & 3;
   const int nfw = (b.nf + MLS_FACES_PER_WAVE - 1) / MLS_FACES_PER_WAVE;
@@ -2144,12 +2288,41 @@ __device__ __forceinline__ void mls_post_block(const FluidArgs& a, const BodyArg
     const int f = gw * MLS_FACES_PER_WAVE + ((l & 31) >> 2);
     const bool valid = f < b.nf;
     const int fv = valid ? f : b.nf - 1;  // spare lanes repeat a face and write nothing
+    // two rounds of loads ahead of the fit: the face's tables, then everything
+    // that they lead to (what the traction needs at the end among it)
+    const int fvx[3] = {b.faces[3 * fv], b.faces[3 * fv + 1], b.faces[3 * fv + 2]};
+    const int fsl[3] = {b.sl_face[3 * fv], b.sl_face[3 * fv + 1], b.sl_face[3 * fv + 2]};
+    const int body = b.face_body[fv];
+    double pa[3], pb[3], pd[3];
+#pragma unroll
+    for (int k = 0; k < 3; k++) {
+      pa[k] = b.Xcur[3 * fvx[0] + k];
+      pb[k] = b.Xcur[3 * fvx[1] + k];
+      pd[k] = b.Xcur[3 * fvx[2] + k];
+    }
+    const double V0 = b.b_param[8 * body], kv = b.b_param[8 * body + 2], V = b.b_diag[16 * body];
+    const int rigid = b.b_rigid[body];
+    // a wave whose faces belong to one body, and up to 64 bodies: lane o tests
+    // body o's box against theirs, so that a body with no neighbour near it
+    // (the rule) leaves the repulsion at once
+    bool near = b.nbody > 1;
+    if (near && b.nbody <= 64) {
+      const int q0 = __builtin_amdgcn_readfirstlane(body), o = l < b.nbody ? l : 0;
+      const double* bb = b.b_diag + 16 * q0 + 2;
+      const double* ob = b.b_diag + 16 * o + 2;
+      bool close = l < b.nbody && o != q0;
+#pragma unroll
+      for (int k = 0; k < 3; k++)
+        if (bb[k] > ob[3 + k] + 1.0 || ob[k] > bb[3 + k] + 1.0) close = false;
+      near = __ballot(close) != 0ull || __ballot(body != q0) != 0ull;
+    }
     double cen[3], nrm[3], area;
-    face_geom(b.Xcur, b.faces, fv, cen, nrm, area);
+    face_geom_pts(pa, pb, pd, cen, nrm, area);
     const double sg = l < 32 ? 1.2 : -1.2;
     double rfit, val[3], G[3][3];
-    fit_point<S>(a, sub, cen[0] + sg * nrm[0], cen[1] + sg * nrm[1], cen[2] + sg * nrm[2], true, rfit,
-                 val, G);
+    const double probe[3] = {cen[0] + sg * nrm[0], cen[1] + sg * nrm[1], cen[2] + sg * nrm[2]};
+    fit_point<S, true>(a, halt, sub, probe, rfit, val, G);
+    if (halt) return;
     // the inner probe of this lane's face
     const double r_in = __shfl(rfit, l + 32, 64);
     double Gin[3][3];
@@ -2157,9 +2330,8 @@ __device__ __forceinline__ void mls_post_block(const FluidArgs& a, const BodyArg
     for (int i = 0; i < 3; i++)
 #pragma unroll
       for (int c = 0; c < 3; c++) Gin[i][c] = __shfl(G[i][c], l + 32, 64);
-    const int body = b.face_body[fv];
     double acc = 0.0;
-    if (b.nbody > 1) {
+    if (near) {
       // repulsion.  First the lanes test the (face q of the wave, other body
       // o) pairs in parallel: o's box must come within dx of q's body's box
       // and of the face itself, and its bounding sphere within dx of the
@@ -2253,11 +2425,7 @@ __device__ __forceinline__ void mls_post_block(const FluidArgs& a, const BodyArg
         F[i] = (-dp * nrm[i] + tn) * area;
       }
       const double pref = b.umax / (8.0 * sqrt(2.0));
-      double cv = 0.0;
-      if (!b.b_rigid[body]) {
-        const double V0 = b.b_param[8 * body], kv = b.b_param[8 * body + 2];
-        cv = kv * (1.0 - b.b_diag[16 * body] / V0) * area;
-      }
+      const double cv = rigid ? 0.0 : kv * (1.0 - V / V0) * area;
       double Ft[3];
 #pragma unroll
       for (int i = 0; i < 3; i++) {
@@ -2268,10 +2436,10 @@ __device__ __forceinline__ void mls_post_block(const FluidArgs& a, const BodyArg
       // a third of the face force at each of its vertices
 #pragma unroll
       for (int r = 0; r < 3; r++) {
-        const long long sl = b.sl_face[3 * f + r];
-        const int vr = b.faces[3 * f + r];
+        const long long sl = fsl[r];
+        const int vr = fvx[r];
 #pragma unroll
-        for (int i = 0; i < 3; i++) b.f_slot[(sl * 3 + i) * b.nv + vr] = Ft[i] / 3.0;
+        for (int i = 0; i < 3; i++) b.f_slot[(sl * 3 + i) * b.nv + vr] = Ft[i] * (1.0 / 3.0);
       }
     }
     return;
@@ -2281,8 +2449,9 @@ __device__ __forceinline__ void mls_post_block(const FluidArgs& a, const BodyArg
   const bool valid = idx < b.nsoft_v;
   const int v = b.soft_vlist[valid ? idx : b.nsoft_v - 1];
   double rfit, U[3], G[3][3];
-  fit_point<S>(a, sub, b.Xcur[3 * v], b.Xcur[3 * v + 1], b.Xcur[3 * v + 2], false, rfit, U, G);
-  if (valid && sub == 0) {
+  const double xv[3] = {b.Xcur[3 * v], b.Xcur[3 * v + 1], b.Xcur[3 * v + 2]};
+  fit_point<S, false>(a, halt, sub, xv, rfit, U, G);
+  if (valid && sub == 0 && !halt) {
     b.u0v[3 * v] = U[0];
     b.u0v[3 * v + 1] = U[1];
     b.u0v[3 * v + 2] = U[2];
@@ -2303,14 +2472,14 @@ __host__ __device__ __forceinline__ int mls_post_blocks(const BodyArgs& b) {
 template <class S>
 __device__ __forceinline__ void mls_post_unit(const FluidArgs& a, const BodyArgs& b, long long* fxp,
                                               uint8_t* tfp, int blk) {
+  const unsigned int halt = halted(a.flags, a.par);
   const int nm = mls_post_blocks(b);
-  if (blk < nm) mls_post_block<S>(a, b, blk);
-  else clear_tiles(a.g, fxp, tfp, blk - nm, b.n_clear_blocks);
+  if (blk < nm) mls_post_block<S>(a, b, blk, halt);
+  else if (!halt) clear_tiles(a.g, fxp, tfp, blk - nm, b.n_clear_blocks);
 }
 
 template <class S>
 __global__ __launch_bounds__(256) void k_mls_post(FluidArgs a, BodyArgs b, long long* fxp, uint8_t* tfp) {
-  if (halted(a.flags, a.par)) return;
   mls_post_unit<S>(a, b, fxp, tfp, blockIdx.x);
 }
 
@@ -2637,7 +2806,6 @@ template <class S>
 __global__ __launch_bounds__(256) void kb_mls_post(const BatchItem* items, const int2* map) {
   const int2 m = batch_unit(map);
   const BatchItem& it = batch_item(items, m.x);
-  if (halted(it.a.flags, it.a.par)) return;
   mls_post_unit<S>(it.a, it.b, it.fxp, it.tfp, m.y);
 }
 
@@ -2814,6 +2982,12 @@ hipError_t launch_fluid_bulk(int prec, const FluidArgs& a, hipStream_t s) {
     case 2 * 16 + 8: bulk_launch<_Float16, 8>(a, grid, s); break;
     default: return hipErrorInvalidValue;
   }
+  return hipGetLastError();
+}
+
+hipError_t launch_mac_solid(int prec, const Grid& g, void* mac, const uint8_t* ncls, hipStream_t s) {
+  if (prec == 0) k_mac_solid<double><<<cdiv(g.Np, 256), 256, 0, s>>>(g, (double*)mac, ncls);
+  else k_mac_solid<float><<<cdiv(g.Np, 256), 256, 0, s>>>(g, (float*)mac, ncls);
   return hipGetLastError();
 }
 
