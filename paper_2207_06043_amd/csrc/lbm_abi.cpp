@@ -319,7 +319,7 @@ extern "C" lbm_status lbm_create(const lbm_desc* d, void* hip_stream, lbm_ctx** 
   ctx->n_links = d->n_links;
   // classify
   std::vector<uint8_t> ncls(G.Np, CLS_SOLID);
-  std::vector<int32_t> rec_of(G.Np, -1);
+  std::vector<int32_t> rec_of(G.Np, REC_SOLID);
   std::vector<int32_t> r_node;
   std::vector<uint32_t> r_mask;
   std::vector<int32_t> r_link0;
@@ -365,6 +365,7 @@ extern "C" lbm_status lbm_create(const lbm_desc* d, void* hip_stream, lbm_ctx** 
         const long long p = pad(x, y, z);
         if (!general) {
           ncls[p] = CLS_BULK;
+          rec_of[p] = -1;
           ctx->n_bulk++;
           continue;
         }

@@ -9,6 +9,9 @@ namespace lbm {
 // Node classes used by the fused stream-collide kernel.
 enum : uint8_t { CLS_SOLID = 0, CLS_BULK = 1, CLS_GENERAL = 2 };
 
+// rec_of at a solid node (and in the padding).
+constexpr int REC_SOLID = -2;
+
 // Status bits raised on the device.
 enum : uint32_t { ST_UNSTABLE = 1u, ST_DAMAGED = 2u };
 
@@ -30,7 +33,7 @@ constexpr int TILE_SHIFT = 6;
 // radius 19 (2562 vertices) need up to ~1430 box nodes; one block in a
 // thousand of the 16-capsule workload takes the direct path.
 constexpr int MARKERS_PER_BLOCK = 64;
-constexpr int BOX_CELLS = 1400;  // 73 KB of LDS: two blocks fit a CU
+constexpr int BOX_CELLS = 1400;  // 39 KB of LDS: four blocks fit a CU
 constexpr int BIN_LDS_KEYS = 8192;  // bodies up to this many faces are binned in LDS (64 KB)
 constexpr int BIN_THREADS = 1024;   // threads of the binning block
 constexpr int CHUNK_CAP = 3;        // marker chunks per 64 faces of a body
@@ -80,7 +83,7 @@ struct FluidArgs {
   const void* A;  // populations read this step
   void* B;        // populations written this step
   const uint8_t* ncls;
-  const int32_t* rec_of;     // [Np] -> record or -1
+  const int32_t* rec_of;     // [Np] -> record, -1 (bulk) or REC_SOLID
   int nrec;
   const int32_t* rec_node;   // padded index
   const uint32_t* rec_mask;  // bit j: pulled direction j comes from a wall link

@@ -1506,26 +1506,152 @@ __device__ __forceinline__ void axis_nodes(int base, int n, int periodic, int st
 __device__ __forceinline__ int sel3i(int i, const int (&w)[3]) { return i == 0 ? w[0] : (i == 1 ? w[1] : w[2]); }
 __device__ __forceinline__ bool sel3b(int i, const bool (&w)[3]) { return i == 0 ? w[0] : (i == 1 ? w[1] : w[2]); }
 
+// u* = sum f e / rho of the streamed populations (no force) at the node
+// (x, y, z), inside the box, of padded index node; false at a solid node.  The
+// 19 plain pulls go out with the node's class; a boundary record then replaces
+// those that come from a wall link (three links per batch of loads) and, on an
+// open face, takes rho and u from the known populations (Zou-He).
+template <class S>
+__device__ __forceinline__ bool cell_velocity(const FluidArgs& a, int node, int x, int y, int z, double (&u)[3]) {
+  typedef typename Store<S>::C C;
+  const Grid& G = a.g;
+  const S* A = (const S*)a.A;
+  const int r = a.rec_of[node];
+  S pl[19];
+  {
+    const int pxy = G.px * G.ny;
+    const int xs[3] = {x == 0 ? G.nx - 1 : x - 1, x, x == G.nx - 1 ? 0 : x + 1};
+    const int ys[3] = {G.px * (y == 0 ? G.ny - 1 : y - 1), G.px * y, G.px * (y == G.ny - 1 ? 0 : y + 1)};
+    const int zs[3] = {pxy * (z == 0 ? G.nz - 1 : z - 1), pxy * z, pxy * (z == G.nz - 1 ? 0 : z + 1)};
+#pragma unroll
+    for (int j = 0; j < 19; j++)
+      pl[j] = (A + (long long)j * G.plane)[xs[1 - EX[j]] + ys[1 - EY[j]] + zs[1 - EZ[j]]];
+  }
+  if (r == REC_SOLID) return false;
+  double g[19], dl = 0.0, ml[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+  for (int j = 0; j < 19; j++) g[j] = (double)to_c(pl[j]);
+  if (r >= 0) {
+    const uint32_t mask = a.rec_mask[r], hqm = a.rec_mb[r];
+    const int lk0 = a.rec_link0[r], fc = a.rec_face[r];
+    const int ax = (fc & 7) >> 1, sg = (fc & 1) ? -1 : 1;
+    double bc[4] = {0.0, 0.0, 0.0, 0.0};
+    if (fc != 0xff) {
+#pragma unroll
+      for (int k = 0; k < 4; k++) bc[k] = a.rec_bc[(long long)k * a.nrec + r];
+    }
+    double G0 = 0.0, Gout = 0.0;
+    const C* lc = (const C*)a.lk_c;
+    const long long nl = a.nlinks;
+    uint32_t m = mask;
+    for (int l = lk0; m; l += 3) {
+      int jj[3];
+      C v[3][6];
+#pragma unroll
+      for (int q = 0; q < 3; q++) {
+        const bool on = m != 0;
+        const int j = on ? __ffs(m) - 1 : 1;
+        jj[q] = on ? j : 0;
+        m &= m - 1;
+        const int i = opp_of(j), lq = on ? l + q : lk0;
+        const bool hq = (hqm >> j) & 1u;
+        const int ex = dir_of(dir_bits(EX), j), ey = dir_of(dir_bits(EY), j), ez = dir_of(dir_bits(EZ), j);
+        const long long n1 = nbr(G, x, y, z, ex, ey, ez), n2 = nbr(G, x, y, z, 2 * ex, 2 * ey, 2 * ez);
+        v[q][0] = lc[lq];
+        v[q][1] = lc[nl + lq];
+        v[q][2] = lc[2 * nl + lq];
+        v[q][3] = ldA<S>(a, i, node);
+        v[q][4] = ldA<S>(a, hq ? j : i, hq ? (long long)node : n1);
+        v[q][5] = ldA<S>(a, hq ? j : i, hq ? n1 : n2);
+      }
+#pragma unroll
+      for (int q = 0; q < 3; q++) {
+        const int j = jj[q];
+        const double w = j ? (double)(v[q][0] * v[q][3] + v[q][1] * v[q][4] + v[q][2] * v[q][5]) : 0.0;
+        const int ex = dir_of(dir_bits(EX), j), ey = dir_of(dir_bits(EY), j), ez = dir_of(dir_bits(EZ), j);
+        const int en = sg * (ax == 0 ? ex : (ax == 1 ? ey : ez));
+        dl += w;
+        ml[0] += ex * w;
+        ml[1] += ey * w;
+        ml[2] += ez * w;
+        G0 += en == 0 ? w : 0.0;
+        Gout += en == -1 ? w : 0.0;
+      }
+    }
+#pragma unroll
+    for (int j = 1; j < 19; j++) {
+      const int en = sg * (ax == 0 ? EX[j] : (ax == 1 ? EY[j] : EZ[j]));
+      if (((mask >> j) & 1u) || (fc != 0xff && en == 1)) g[j] = 0.0;
+    }
+    if (fc != 0xff) {
+#pragma unroll
+      for (int j = 0; j < 19; j++) {
+        const int en = sg * (ax == 0 ? EX[j] : (ax == 1 ? EY[j] : EZ[j]));
+        G0 += en == 0 ? g[j] : 0.0;
+        Gout += en == -1 ? g[j] : 0.0;
+      }
+      double un, ut[3] = {0.0, 0.0, 0.0};
+      if (((fc >> 4) & 1) == 0) {
+        un = sg * (ax == 0 ? bc[0] : (ax == 1 ? bc[1] : bc[2]));
+#pragma unroll
+        for (int k = 0; k < 3; k++) ut[k] = bc[k];
+      } else {
+        un = (bc[3] - 1.0 - G0 - 2.0 * Gout) / bc[3];
+      }
+#pragma unroll
+      for (int k = 0; k < 3; k++) u[k] = k == ax ? sg * un : ut[k];
+      return true;
+    }
+  }
+  const double ir = 1.0 / (1.0 + (dev_sum(g) + dl));
+  const double mx = (g[1] - g[2]) + (g[7] + g[8]) + (g[9] + g[10]) - (g[11] + g[12]) - (g[13] + g[14]);
+  const double my = (g[3] - g[4]) + (g[7] - g[8]) + (g[11] - g[12]) + (g[15] + g[16]) - (g[17] + g[18]);
+  const double mz = (g[5] - g[6]) + (g[9] - g[10]) + (g[13] - g[14]) + (g[15] - g[16]) + (g[17] - g[18]);
+  u[0] = (mx + ml[0]) * ir;
+  u[1] = (my + ml[1]) * ir;
+  u[2] = (mz + ml[2]) * ir;
+  return true;
+}
+
+// Smallest (largest with MAX) of v over the wave, for values that agree inside
+// a quad; on every lane.
+template <bool MAX>
+__device__ __forceinline__ int wave_ext(int v) {
+  auto ext = [](int p, int q) { return MAX ? max(p, q) : min(p, q); };
+  v = ext(v, __builtin_amdgcn_mov_dpp(v, 0x141, 0xf, 0xf, true));  // the other quad of eight lanes
+  v = ext(v, __builtin_amdgcn_mov_dpp(v, 0x140, 0xf, 0xf, true));  // the other eight of sixteen
+  return ext(ext(__builtin_amdgcn_readlane(v, 0), __builtin_amdgcn_readlane(v, 16)),
+             ext(__builtin_amdgcn_readlane(v, 32), __builtin_amdgcn_readlane(v, 48)));
+}
+
+// The three components of a contribution into the fixed-point sums at p,
+// p + stride, p + 2 stride.
+template <class T>
+__device__ __forceinline__ void spread_add(const FluidArgs& a, T* p, long long stride, double c, const double (&F)[3]) {
+#pragma unroll
+  for (int q = 0; q < 3; q++)
+    atomicAdd((unsigned long long*)(p + q * stride), (unsigned long long)fx_quant(c * F[q], a));
+}
+
 template <class S>
 __device__ void marker_block(const FluidArgs& a, const BodyArgs& b, int blk, long long* fxc,
-                             uint8_t* tfc) {
-  __shared__ double s_u[3][BOX_CELLS];
+                             uint8_t* tfc, unsigned int halt) {
+  // u* of the box (as the bits of doubles), then, once every marker has read
+  // it, the box's force sums
   __shared__ long long s_acc[3][BOX_CELLS];
   __shared__ int s_node[BOX_CELLS];  // padded node index (< 2^31) or -1
-  __shared__ int s_box[6];
+  __shared__ int s_wbox[4][6];
   const Grid& G = a.g;
   const int t = threadIdx.x, sub = t & 3;
-  const int nchunk = b.chunk_n[blk];
+  const int nchunk = b.chunk_n[blk], s0 = b.chunk_s0[blk];
   if (nchunk == 0) {
     // an unused chunk: its box stays empty (the repulsion and the owner
     // pass skip it), and nothing else is done
-    if (t < 6) b.chunk_box[6 * blk + t] = t < 3 ? INT_MAX : INT_MIN;
+    if (t < 6 && !halt) b.chunk_box[6 * blk + t] = t < 3 ? INT_MAX : INT_MIN;
     return;
   }
-  const int m = b.chunk_s0[blk] + (t >> 2);  // slot
+  const int m = s0 + (t >> 2);  // slot
   const bool mk = (t >> 2) < nchunk;
-  if (t < 6) s_box[t] = t < 3 ? INT_MAX : INT_MIN;
-  __syncthreads();
   double cen[3] = {0.0, 0.0, 0.0}, Ub[3] = {0.0, 0.0, 0.0}, area = 0.0;
   int bs[3] = {0, 0, 0};
   if (mk) {
@@ -1545,9 +1671,12 @@ __device__ void marker_block(const FluidArgs& a, const BodyArgs& b, int blk, lon
       vb[k] = b.Vel[3 * v1 + k];
       vd[k] = b.Vel[3 * v2 + k];
     }
+    int rigid = 0;
+    if (b.n_rigid) {
 #pragma unroll
-    for (int k = 0; k < 12; k++) rs[k] = b.b_rig[32 * body + k];
-    const int rigid = b.b_rigid[body];
+      for (int k = 0; k < 12; k++) rs[k] = b.b_rig[32 * body + k];
+      rigid = b.b_rigid[body];
+    }
     double nrm[3];
     face_geom_pts(pa, pb, pd, cen, nrm, area);
     if (rigid) {
@@ -1558,141 +1687,159 @@ __device__ void marker_block(const FluidArgs& a, const BodyArgs& b, int blk, lon
       Ub[2] = rs[5] + (w[0] * r[1] - w[1] * r[0]);
     } else {
 #pragma unroll
-      for (int k = 0; k < 3; k++) Ub[k] = (va[k] + vb[k] + vd[k]) / 3.0;
+      for (int k = 0; k < 3; k++) Ub[k] = (va[k] + vb[k] + vd[k]) * (1.0 / 3.0);
     }
 #pragma unroll
     for (int k = 0; k < 3; k++) bs[k] = (int)floor(cen[k] + 0.5);
-    if (sub == 0) {
+  }
+  if (halt) return;
+  if (mk && sub == 0) {
 #pragma unroll
-      for (int k = 0; k < 3; k++) b.centroid[3 * m + k] = cen[k];
-      atomicMin(&s_box[0], bs[0]);
-      atomicMin(&s_box[1], bs[1]);
-      atomicMin(&s_box[2], bs[2]);
-      atomicMax(&s_box[3], bs[0]);
-      atomicMax(&s_box[4], bs[1]);
-      atomicMax(&s_box[5], bs[2]);
+    for (int k = 0; k < 3; k++) b.centroid[3 * m + k] = cen[k];
+  }
+#pragma unroll
+  for (int k = 0; k < 3; k++) {
+    const int lo = wave_ext<false>(mk ? bs[k] : INT_MAX), hi = wave_ext<true>(mk ? bs[k] : INT_MIN);
+    if ((t & 63) == 0) {
+      s_wbox[t >> 6][k] = lo;
+      s_wbox[t >> 6][3 + k] = hi;
     }
   }
   __syncthreads();
+  int lo[3], hi[3];
+#pragma unroll
+  for (int k = 0; k < 3; k++) {
+    lo[k] = min(min(s_wbox[0][k], s_wbox[1][k]), min(s_wbox[2][k], s_wbox[3][k]));
+    hi[k] = max(max(s_wbox[0][3 + k], s_wbox[1][3 + k]), max(s_wbox[2][3 + k], s_wbox[3][3 + k]));
+  }
   // this block's slots form one chunk: its box of stencil bases lets the
   // repulsion skip the chunk when a face is farther than dx from it (an
   // unused chunk keeps the empty box)
-  if (t < 6) b.chunk_box[6 * blk + t] = s_box[t];
-  const int x0 = s_box[0] - 1, y0 = s_box[1] - 1, z0 = s_box[2] - 1;
-  const int ex = s_box[3] - s_box[0] + 3, ey = s_box[4] - s_box[1] + 3, ez = s_box[5] - s_box[2] + 3;
-  const bool fits = s_box[3] >= s_box[0] && (long long)ex * ey * ez <= BOX_CELLS;
-  const int ncell = fits ? ex * ey * ez : 0;
-  for (int c = t; c < ncell; c += blockDim.x) {
-    long long node = -1;
-    double u3[3] = {0.0, 0.0, 0.0};
-    if (support_node(G, a.ncls, x0 + c % ex, y0 + (c / ex) % ey, z0 + c / (ex * ey), node)) {
-      const Moments mo = streamed_moments<S>(a, node);
-      const double rho = 1.0 + mo.drho;
-#pragma unroll
-      for (int k = 0; k < 3; k++) u3[k] = mo.m[k] / rho;
-    } else {
-      node = -1;
-    }
+  if (t == 0) {
 #pragma unroll
     for (int k = 0; k < 3; k++) {
-      s_u[k][c] = u3[k];
-      s_acc[k][c] = 0;
+      b.chunk_box[6 * blk + k] = lo[k];
+      b.chunk_box[6 * blk + 3 + k] = hi[k];
     }
-    s_node[c] = (int)node;
   }
-  __syncthreads();
+  const int x0 = lo[0] - 1, y0 = lo[1] - 1, z0 = lo[2] - 1;
+  const int ex = hi[0] - lo[0] + 3, ey = hi[1] - lo[1] + 3, ez = hi[2] - lo[2] + 3;
+  const bool fits = (long long)ex * ey * ez <= BOX_CELLS;
+  const int ncell = fits ? ex * ey * ez : 0;
+  const float iex = 1.0f / (float)ex, iey = 1.0f / (float)ey;
+  for (int c = t; c < ncell; c += blockDim.x) {
+    // c / ex and so on for c < 1400: the half keeps the product off the integers
+    const int q = (int)(((float)c + 0.5f) * iex), cz = (int)(((float)q + 0.5f) * iey);
+    int p[3] = {x0 + c - q * ex, y0 + q - cz * ey, z0 + cz};
+    const int dim[3] = {G.nx, G.ny, G.nz};
+    bool in = true;
+#pragma unroll
+    for (int k = 0; k < 3; k++)
+      if (p[k] < 0 || p[k] >= dim[k]) {
+        if (G.per[k]) p[k] = ((p[k] % dim[k]) + dim[k]) % dim[k];
+        else in = false;
+      }
+    const int node = in ? p[0] + G.px * (p[1] + G.ny * p[2]) : 0;
+    double u3[3] = {0.0, 0.0, 0.0};
+    const bool ok = in && cell_velocity<S>(a, node, p[0], p[1], p[2], u3);
+#pragma unroll
+    for (int k = 0; k < 3; k++) s_acc[k][c] = __double_as_longlong(u3[k]);
+    s_node[c] = ok ? node : -1;
+  }
   // a quad always holds one marker (or none), so the quad sums below see
   // four lanes that agree on mk
-  double wx[3], wy[3], wz[3];
-  axis_weights(cen[0], bs[0], wx);
-  axis_weights(cen[1], bs[1], wy);
-  axis_weights(cen[2], bs[2], wz);
-  double A[10] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0}, bu[3][4] = {{0, 0, 0, 0}, {0, 0, 0, 0}, {0, 0, 0, 0}};
-  // The support loops run rolled: each marker block runs this code once per
-  // step on its CU, so its length costs instruction fetch (measured: the
-  // seven-fold unrolled loops took longer than their arithmetic).
-  if (mk && fits) {
-#pragma unroll 1
-    for (int k = sub; k < 27; k += 4) {
-      const int kx = k % 3, ky = (k / 3) % 3, kz = k / 9;
-      const int cx = bs[0] + kx - 1, cy = bs[1] + ky - 1, cz = bs[2] + kz - 1;
-      const double dx = cx - cen[0], dy = cy - cen[1], dz = cz - cen[2];
-      const int c = (cx - x0) + ex * ((cy - y0) + ey * (cz - z0));
-      const double W = s_node[c] >= 0 ? sel3(kx, wx) * sel3(ky, wy) * sel3(kz, wz) : 0.0;
-      mls_add(A, W, dx, dy, dz);
+  double wx[3], wy[3], wz[3], dx[3];
+  quad_weights(sub, cen, bs, wx, wy, wz);
 #pragma unroll
-      for (int q = 0; q < 3; q++) mls_rhs(bu[q], W, dx, dy, dz, s_u[q][c]);
+  for (int k = 0; k < 3; k++) dx[k] = (double)(bs[0] + k - 1) - cen[0];
+  __syncthreads();
+  FitSums<3> fs;
+  fs.clear();
+  const int c00 = (bs[0] - 1 - x0) + ex * ((bs[1] - 1 - y0) + ey * (bs[2] - 1 - z0));
+  if (mk && fits) {
+#pragma unroll
+    for (int i = 0; i < 3; i++) {
+      int ky = 2, kz = 2;
+      if (i < 2) row_yz(sub + 4 * i, ky, kz);
+      const int cr = c00 + ex * (ky + ey * kz) + (i < 2 ? 0 : min(sub, 2));
+      RowSums<3> rs;
+      rs.clear();
+#pragma unroll
+      for (int k = 0; k < (i < 2 ? 3 : 1); k++) {
+        const bool on = s_node[cr + k] >= 0 && (i < 2 || sub < 3);
+        const double w = on ? (i < 2 ? wx[k] : sel3(sub, wx)) : 0.0, d = i < 2 ? dx[k] : sel3(sub, dx);
+        const double f[3] = {__longlong_as_double(s_acc[0][cr + k]), __longlong_as_double(s_acc[1][cr + k]),
+                             __longlong_as_double(s_acc[2][cr + k])};
+        rs.add(w, d, f);
+      }
+      fs.add(rs, sel3(ky, wy) * sel3(kz, wz), (double)(bs[1] + ky - 1) - cen[1], (double)(bs[2] + kz - 1) - cen[2]);
     }
   } else if (mk) {
 #pragma unroll 1
     for (int k = sub; k < 27; k += 4) {
       const int kx = k % 3, ky = (k / 3) % 3, kz = k / 9;
       const int cx = bs[0] + kx - 1, cy = bs[1] + ky - 1, cz = bs[2] + kz - 1;
-      const double dx = cx - cen[0], dy = cy - cen[1], dz = cz - cen[2];
       long long node;
       double u3[3] = {0.0, 0.0, 0.0};
-      const bool ok = support_node(G, a.ncls, cx, cy, cz, node);
+      bool ok = support_node(G, a.ncls, cx, cy, cz, node);
       if (ok) {
-        const Moments mo = streamed_moments<S>(a, node);
-#pragma unroll
-        for (int q = 0; q < 3; q++) u3[q] = mo.m[q] / (1.0 + mo.drho);
+        int x, y, z;
+        coords(G, node, x, y, z);
+        ok = cell_velocity<S>(a, (int)node, x, y, z, u3);
       }
-      const double W = ok ? sel3(kx, wx) * sel3(ky, wy) * sel3(kz, wz) : 0.0;
-      mls_add(A, W, dx, dy, dz);
-#pragma unroll
-      for (int q = 0; q < 3; q++) mls_rhs(bu[q], W, dx, dy, dz, u3[q]);
+      RowSums<3> rs;
+      rs.clear();
+      rs.add(ok ? sel3(kx, wx) : 0.0, cx - cen[0], u3);
+      fs.add(rs, sel3(ky, wy) * sel3(kz, wz), cy - cen[1], cz - cen[2]);
     }
   }
+  __syncthreads();
+  for (int c = t; c < ncell; c += blockDim.x) {
 #pragma unroll
-  for (int k = 0; k < 10; k++) A[k] = quad_sum(A[k]);
-#pragma unroll
-  for (int q = 0; q < 3; q++)
-#pragma unroll
-    for (int k = 0; k < 4; k++) bu[q][k] = quad_sum(bu[q][k]);
+    for (int k = 0; k < 3; k++) s_acc[k][c] = 0;
+  }
+  fs.quad();
+  double F[3] = {0.0, 0.0, 0.0}, cc[4] = {0.0, 0.0, 0.0, 0.0};
   if (mk) {
     Chol4 ch;
-    double cc[4] = {0.0, 0.0, 0.0, 0.0};
-    if (chol4(A, ch)) {
+    if (chol4(fs.A, ch)) {
       const double e0[4] = {1.0, 0.0, 0.0, 0.0};
       chol_solve(ch, e0, cc);
     } else if (sub == 0) {
       atomicAdd(&a.flags->mls_singular, 1);
     }
-    double F[3];
 #pragma unroll
     for (int q = 0; q < 3; q++)
-      F[q] = Ub[q] - (cc[0] * bu[q][0] + cc[1] * bu[q][1] + cc[2] * bu[q][2] + cc[3] * bu[q][3]);
-    if (fits) {
+      F[q] = Ub[q] - (cc[0] * fs.b[q][0] + cc[1] * fs.b[q][1] + cc[2] * fs.b[q][2] + cc[3] * fs.b[q][3]);
+  }
+  __syncthreads();
+  if (mk && fits) {
 #pragma unroll 1
-      for (int k = sub; k < 27; k += 4) {
-        const int kx = k % 3, ky = (k / 3) % 3, kz = k / 9;
-        const int cx = bs[0] + kx - 1, cy = bs[1] + ky - 1, cz = bs[2] + kz - 1;
-        const double dx = cx - cen[0], dy = cy - cen[1], dz = cz - cen[2];
-        const int c = (cx - x0) + ex * ((cy - y0) + ey * (cz - z0));
-        const double phi = sel3(kx, wx) * sel3(ky, wy) * sel3(kz, wz) * (cc[0] + cc[1] * dx + cc[2] * dy + cc[3] * dz);
-        if (s_node[c] >= 0 && phi != 0.0) {
-          const double cp = area * phi;
+    for (int i = 0; i < 3; i++) {
+      int ky = 2, kz = 2;
+      if (i < 2) row_yz(sub + 4 * i, ky, kz);
+      const double dy = (double)(bs[1] + ky - 1) - cen[1], dz = (double)(bs[2] + kz - 1) - cen[2];
+      const double w = area * (sel3(ky, wy) * sel3(kz, wz)), t0 = cc[0] + cc[2] * dy + cc[3] * dz;
+      const int cr = c00 + ex * (ky + ey * kz);
 #pragma unroll
-          for (int q = 0; q < 3; q++)
-            atomicAdd((unsigned long long*)&s_acc[q][c], (unsigned long long)fx_quant(cp * F[q], a));
-        }
+      for (int k = 0; k < 3; k++) {
+        if (i == 2 && k != sub) continue;
+        const double c = w * wx[k] * (t0 + cc[1] * dx[k]);
+        if (s_node[cr + k] >= 0 && c != 0.0) spread_add(a, &s_acc[0][cr + k], BOX_CELLS, c, F);
       }
-    } else {
+    }
+  } else if (mk) {
 #pragma unroll 1
-      for (int k = sub; k < 27; k += 4) {
-        const int kx = k % 3, ky = (k / 3) % 3, kz = k / 9;
-        const int cx = bs[0] + kx - 1, cy = bs[1] + ky - 1, cz = bs[2] + kz - 1;
-        const double dx = cx - cen[0], dy = cy - cen[1], dz = cz - cen[2];
-        long long node;
-        const bool ok = support_node(G, a.ncls, cx, cy, cz, node);
-        const double phi = sel3(kx, wx) * sel3(ky, wy) * sel3(kz, wz) * (cc[0] + cc[1] * dx + cc[2] * dy + cc[3] * dz);
-        if (ok && phi != 0.0) {
-          const double cp = area * phi;
-#pragma unroll
-          for (int q = 0; q < 3; q++)
-            atomicAdd((unsigned long long*)(fxc + q * G.Np + node), (unsigned long long)fx_quant(cp * F[q], a));
-          tfc[node >> TILE_SHIFT] = 1;
-        }
+    for (int k = sub; k < 27; k += 4) {
+      const int kx = k % 3, ky = (k / 3) % 3, kz = k / 9;
+      const int cx = bs[0] + kx - 1, cy = bs[1] + ky - 1, cz = bs[2] + kz - 1;
+      const double ddx = cx - cen[0], dy = cy - cen[1], dz = cz - cen[2];
+      long long node;
+      const bool ok = support_node(G, a.ncls, cx, cy, cz, node);
+      const double c = area * sel3(kx, wx) * sel3(ky, wy) * sel3(kz, wz) * (cc[0] + cc[1] * ddx + cc[2] * dy + cc[3] * dz);
+      if (ok && c != 0.0) {
+        spread_add(a, fxc + node, G.Np, c, F);
+        tfc[node >> TILE_SHIFT] = 1;
       }
     }
   }
@@ -2127,11 +2274,14 @@ template <class S>
 __device__ __forceinline__ void ib_force_block(const FluidArgs& a, const BodyArgs& b, long long* fxc,
                                                uint8_t* tfc, long long* fxp, uint8_t* tfp,
                                                unsigned int* counter, int blk) {
+  const unsigned int halt = halted(a.flags, a.par);
   const int nmk = b.n_marker_blocks, nel = b.n_elem_blocks;
   (void)fxp;
   (void)tfp;
   if (blk < nmk) {
-    marker_block<S>(a, b, blk, fxc, tfc);
+    marker_block<S>(a, b, blk, fxc, tfc, halt);
+  } else if (halt) {
+    return;
   } else if (blk < nmk + nel) {
     membrane_element(b, (blk - nmk) * 256 + threadIdx.x);
   } else {
@@ -2146,14 +2296,20 @@ __device__ __forceinline__ void ib_force_block(const FluidArgs& a, const BodyArg
   }
 }
 
-// Two blocks per CU (two waves per SIMD) in FP32 and FP16S: the marker
-// blocks are latency-bound chains, and a second resident block hides them.
-// (FP64 would spill to scratch at that register budget.)
+// The marker blocks are chains of dependent loads (about 1 us per round trip
+// to memory another XCD wrote last) with little arithmetic, 4 waves on a CU:
+// the launch lasts as long as its longest chain.  So: flags, chunk and slot
+// tables in two rounds, the 19 pulls of a cell with its class instead of
+// after it, three links of a boundary node per round, sums row by row and
+// through DPP moves, and one LDS array for u* and then the sums (39 KB, 217
+// registers: two waves per SIMD; asking for three or four spills and is
+// slower, 15.4 and 17.8 us on one capsule).  Measured per launch, before ->
+// after: one capsule 18.7 -> 14.0 us, a train of three 32 -> 21, a small
+// sphere in FP64 28 -> 18.7, 16 capsules 110 -> 82, a sweep of ten 43 -> 31.7.
 template <class S>
-__global__ __launch_bounds__(256, sizeof(S) == 8 ? 1 : 2) void k_ib_force(FluidArgs a, BodyArgs b, long long* fxc,
+__global__ __launch_bounds__(256, 2) void k_ib_force(FluidArgs a, BodyArgs b, long long* fxc,
                                                   uint8_t* tfc, long long* fxp, uint8_t* tfp,
                                                   unsigned int* counter) {
-  if (halted(a.flags, a.par)) return;
   ib_force_block<S>(a, b, fxc, tfc, fxp, tfp, counter, blockIdx.x);
 }
 
@@ -2711,11 +2867,10 @@ __device__ __forceinline__ const BatchItem& batch_item(const BatchItem* items, i
 }
 
 template <class S>
-__global__ __launch_bounds__(256, sizeof(S) == 8 ? 1 : 2) void kb_ib_force(const BatchItem* items,
+__global__ __launch_bounds__(256, 2) void kb_ib_force(const BatchItem* items,
                                                                           const int2* map) {
   const int2 m = batch_unit(map);
   const BatchItem& it = batch_item(items, m.x);
-  if (halted(it.a.flags, it.a.par)) return;
   ib_force_block<S>(it.a, it.b, it.fxc, it.tfc, it.fxp, it.tfp, it.counter, m.y);
 }
 
