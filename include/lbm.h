@@ -244,8 +244,8 @@ lbm_status ib_spread_noalloc(lbm_ctx *ctx, int64_t n, const double *d_pts, const
  * Checkpoints: the state is kept every checkpoint_every steps and each
  * segment is recomputed once in the reverse sweep (device memory: 6 FP64
  * fields and ceil(n/K) + max(K, 2) states of 19 x plane values, plus K x 19
- * doubles per boundary record; with a body, eleven FP64 [Np] fields, a
- * state and 9 nv doubles per checkpoint and per step of a segment;
+ * doubles per boundary record; with a body, 16 FP64 [Np] fields
+ * and 9 nv doubles per checkpoint and per step of a segment;
  * allocated and freed by the call; LBM_E_NOMEM if it does not fit).  The
  * context's state and step count are not changed.  Contexts with rigid or
  * fixed bodies, or with more than one body (the repulsion), give

@@ -1901,12 +1901,12 @@ static lbm_status adjoint_sweep(lbm_ctx* ctx, int32_t n_steps, int32_t every, co
   const int npart = adj_part_blocks(ctx->nrec, ctx->n_bulk);
   const size_t pbytes = ADJ_PART * (size_t)npart * sizeof(double);
   // with bodies: two force fields and their tile flags, the node sources and
-  // flags, dJ/dF at nodes, a scratch state, body checkpoints and tape (P, Q,
-  // V per step), eight body adjoint arrays
+  // flags, dJ/dF at nodes, body checkpoints and tape (P, Q, V per step), eight
+  // body adjoint arrays
   const long long ntiles = (G.Np >> TILE_SHIFT) + 1;
   const size_t bstate = 9 * sizeof(double) * (size_t)ctx->nv;  // P, Q, V
   const size_t ib_bytes = ib ? 2 * up256(3 * (size_t)G.Np * 8) + 2 * up256(ntiles) + up256(7 * (size_t)G.Np * 8) +
-                                   up256(ntiles) + up256(3 * (size_t)G.Np * 8) + xbytes +
+                                   up256(ntiles) + up256(3 * (size_t)G.Np * 8) +
                                    (size_t)(nseg + tlen + 1) * up256(bstate) + 8 * up256(bstate / 3) +
                                    up256(sizeof(double) * (2 + nb)) + up256(sizeof(DevFlags) + 64)
                              : 0;
@@ -1959,7 +1959,6 @@ static lbm_status adjoint_sweep(lbm_ctx* ctx, int32_t n_steps, int32_t every, co
     uint8_t* tf[2];
     double *ext, *fbar, *gsum;
     uint8_t* etf;
-    void* gB;
     std::vector<double*> bck, bt;
     double *arr[8];
     DevFlags* flags;
@@ -1975,7 +1974,6 @@ static lbm_status adjoint_sweep(lbm_ctx* ctx, int32_t n_steps, int32_t every, co
     q.ext = (double*)carve(7 * (size_t)G.Np * 8);
     q.etf = (uint8_t*)carve(ntiles);
     q.fbar = (double*)carve(3 * (size_t)G.Np * 8);
-    q.gB = carve(xraw);
     for (int c = 0; c < nseg; c++) q.bck.push_back((double*)carve(bstate));
     for (int k = 0; k <= tlen; k++) q.bt.push_back((double*)carve(bstate));
     for (int k = 0; k < 8; k++) q.arr[k] = (double*)carve(bstate / 3);
@@ -2062,7 +2060,9 @@ static lbm_status adjoint_sweep(lbm_ctx* ctx, int32_t n_steps, int32_t every, co
     hipError_t e = hipSuccess;
     if (!h_J) return e;
     if (m.w && (e = launch_adj_wdot(ctx->prec, a, g, m.w, m.amask, 1, m.jpart, s)) != hipSuccess) return e;
-    if (ib && (e = launch_taylor(bb, P, std::max(tbody, 0), 0.0, nullptr, jsum, s)) != hipSuccess) return e;
+    // (with a Taylor term the step back adds its value along with its gradient)
+    if (ib && theta == 0.0 && (e = launch_taylor(bb, P, std::max(tbody, 0), 0.0, nullptr, jsum, s)) != hipSuccess)
+      return e;
     return e;
   };
   // reverse pass, segment by segment: recompute its states (and the records'
@@ -2112,10 +2112,10 @@ static lbm_status adjoint_sweep(lbm_ctx* ctx, int32_t n_steps, int32_t every, co
       st.part = m.part;
       if (ib) {
         double* Pk = q.bt[k];  // the state the step started from
-        if (theta != 0.0) CHK(launch_taylor(bb, q.bt[k + 1], tbody, theta, A3[0], nullptr, s));
-        // the step's force field and fields again (into scratch)
+        if (theta != 0.0) CHK(launch_taylor(bb, q.bt[k + 1], tbody, theta, A3[0], h_J ? jsum : nullptr, s));
+        // the step's force field and fields again
         FluidArgs fa = a;
-        fa.B = q.gB;
+        fa.B = nullptr;
         fa.fx = q.fx[0];
         fa.tflag = q.tf[0];
         fa.mac = ctx->mac;
@@ -2124,6 +2124,7 @@ static lbm_status adjoint_sweep(lbm_ctx* ctx, int32_t n_steps, int32_t every, co
         b2.Xcur = Pk;
         b2.Xnext = q.bt[k + 1];  // not written by the forcing launch
         b2.Vel = Pk + 2 * nv3;
+        b2.support_tf = q.etf;
         CHK(launch_ib_force(ctx->prec, fa, b2, q.fx[0], q.tf[0], q.fx[1], q.tf[1], q.cnt, s));
         CHK(launch_adjoint_forward(ctx->prec, fa, nullptr, merged, s));
         AdjIB ibp{};
@@ -2143,7 +2144,6 @@ static lbm_status adjoint_sweep(lbm_ctx* ctx, int32_t n_steps, int32_t every, co
         CHK(launch_adjb_vertex(b2, ibp, s));
         CHK(launch_adjb_body(ctx->prec, fa, b2, ibp, s));
         CHK(launch_adjb_volume(b2, ibp, s));
-        CHK(launch_adjb_support(G, ctx->ncls, b2, q.etf, s));
         st.fx = q.fx[0];
         st.ftf = q.tf[0];
         st.ext = q.ext;

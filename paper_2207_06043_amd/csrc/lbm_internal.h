@@ -175,6 +175,7 @@ struct BodyArgs {
   double* centroid;            // [nf][3] by slot
   double* fext;                // [nf][6] hydrodynamic + repulsion force and centroid (rigid bodies)
   int* chunk_box;              // [n_marker_blocks][6] box of stencil bases of each chunk
+  uint8_t* support_tf;         // adjoint: the forcing launch flags the tiles of every box cell here (else null)
   // Two-pass spread (null: one pass with atomics): each marker block's box
   // sums, [n_marker_blocks][BOX_CELLS][3] fixed point, and the node of each
   // box cell (-1: none), [n_marker_blocks][BOX_CELLS].
@@ -308,7 +309,6 @@ hipError_t launch_adjoint_grad(const double* part, int nblk, double omega, const
 hipError_t launch_adjb_vertex(const BodyArgs& b, const AdjIB& ib, hipStream_t s);
 hipError_t launch_adjb_body(int prec, const FluidArgs& a, const BodyArgs& b, const AdjIB& ib, hipStream_t s);
 hipError_t launch_adjb_volume(const BodyArgs& b, const AdjIB& ib, hipStream_t s);
-hipError_t launch_adjb_support(const Grid& g, const uint8_t* ncls, const BodyArgs& b, uint8_t* etf, hipStream_t s);
 hipError_t launch_adjb_markers(int prec, const FluidArgs& a, const BodyArgs& b, const AdjIB& ib, hipStream_t s);
 hipError_t launch_taylor(const BodyArgs& b, const double* X, int body, double theta, double* aP, double* jsum,
                          hipStream_t s);

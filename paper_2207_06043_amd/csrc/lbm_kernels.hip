@@ -286,41 +286,6 @@ __device__ void zouhe(C (&g)[19], int face, int kind, C bx, C by, C bz, C brho) 
 // link's branch, t1 = f*_i(x - e_i), t2 = f*_i(x - 2e_i) (q < 1/2) or
 // t1 = f*_j(x), t2 = f*_j(x - e_i) (q >= 1/2); k1, k2 are zero where the
 // fluid neighbours are missing.
-template <class S>
-struct Bfl {
-  typename Store<S>::C k0, k1, k2, s, t1, t2;
-};
-
-// The IB kernels' form, one node per thread.  The loads carry no branch (they
-// go out in one batch with the rest of the node's loads); for a direction
-// without a link they read the node's own values (no traffic) and the caller
-// drops the result.  Each neighbour index is formed on its own (few values
-// live at once: registers are scarce there).
-template <class S>
-__device__ __forceinline__ Bfl<S> bfl_load_nb(const FluidArgs& a, int j, bool linked, int lk, bool hq,
-                                              long long node, int x, int y, int z) {
-  typedef typename Store<S>::C C;
-  const Grid& G = a.g;
-  const C* lc = (const C*)a.lk_c;
-  const long long nl = a.nlinks;
-  const int i = OPP[j];
-  const int l = linked ? lk : 0;
-  const long long n1 = linked ? nbr(G, x, y, z, EX[j], EY[j], EZ[j]) : node;  // x - e_i
-  const long long n2 = linked ? nbr(G, x, y, z, 2 * EX[j], 2 * EY[j], 2 * EZ[j]) : node;
-  Bfl<S> r;
-  r.k0 = lc[l];
-  r.k1 = lc[nl + l];
-  r.k2 = lc[2 * nl + l];
-  r.s = ldA<S>(a, i, node);
-  r.t1 = ldA<S>(a, hq ? j : i, hq ? node : n1);
-  r.t2 = ldA<S>(a, hq ? j : i, hq ? n1 : n2);
-  return r;
-}
-
-template <class S>
-__device__ __forceinline__ typename Store<S>::C bfl_value(const Bfl<S>& b) {
-  return b.k0 * b.s + b.k1 * b.t1 + b.k2 * b.t2;
-}
 
 // Direction arithmetic for a direction known only at run time: the
 // components of e_j (two bits each, biased by one) and the opposite.
@@ -479,82 +444,6 @@ __device__ __forceinline__ void pull_records(const FluidArgs& a, int r0, typenam
     zouhe<C>(g, face, kind, (C)bc[0], (C)bc[1], (C)bc[2], (C)bc[3]);
   }
   flagged = tfl != 0;
-}
-
-struct Moments {
-  double drho, m[3];
-};
-
-template <class S>
-__device__ __forceinline__ Moments streamed_moments(const FluidArgs& a, long long node) {
-  Moments out;
-  double& drho = out.drho;
-  double (&m)[3] = out.m;
-  const Grid& G = a.g;
-  int x, y, z;
-  coords(G, node, x, y, z);
-  double g[19];
-  if (a.ncls[node] == CLS_BULK) {
-#pragma unroll
-    for (int j = 0; j < 19; j++) g[j] = (double)ldA<S>(a, j, nbr(G, x, y, z, -EX[j], -EY[j], -EZ[j]));
-  } else {
-    const int r = a.rec_of[node];
-    const uint32_t mask = a.rec_mask[r];
-    const uint32_t hqm = a.rec_mb[r];
-    const int lk0 = a.rec_link0[r];
-    const int fc = a.rec_face[r];
-    const int face = fc & 7, ax = face >> 1, sgn = (face & 1) ? -1 : 1;
-    typedef typename Store<S>::C C;
-    C pl[19];
-    Bfl<S> bb[19];
-    pl[0] = ldA<S>(a, 0, node);
-#pragma unroll
-    for (int j = 1; j < 19; j++) {
-      const int en = sgn * (ax == 0 ? EX[j] : (ax == 1 ? EY[j] : EZ[j]));
-      const bool linked = (mask >> j) & 1u;
-      const bool plain = !linked && !(fc != 0xff && en == 1);
-      pl[j] = ldA<S>(a, plain ? j : 0, plain ? nbr(G, x, y, z, -EX[j], -EY[j], -EZ[j]) : node);
-      bb[j] = bfl_load_nb<S>(a, j, linked, lk0 + __popc(mask & ((1u << j) - 1u)), (hqm >> j) & 1u, node, x, y, z);
-    }
-    g[0] = (double)pl[0];
-#pragma unroll
-    for (int j = 1; j < 19; j++) {
-      const int en = sgn * (ax == 0 ? EX[j] : (ax == 1 ? EY[j] : EZ[j]));
-      const bool linked = (mask >> j) & 1u;
-      const bool unknown = fc != 0xff && en == 1;  // the Zou-He rule fills it
-      g[j] = linked ? (double)bfl_value<S>(bb[j]) : (unknown ? 0.0 : (double)pl[j]);
-    }
-    if (fc != 0xff) {
-      double G0 = 0.0, Gout = 0.0;
-#pragma unroll
-      for (int j = 0; j < 19; j++) {
-        const int en = sgn * (ax == 0 ? EX[j] : (ax == 1 ? EY[j] : EZ[j]));
-        G0 += en == 0 ? g[j] : 0.0;
-        Gout += en == -1 ? g[j] : 0.0;
-      }
-      const int kind = (fc >> 4) & 1;
-      double rw, un, ut[3] = {0.0, 0.0, 0.0};
-      if (kind == 0) {
-        const double bu[3] = {a.rec_bc[r], a.rec_bc[a.nrec + r], a.rec_bc[2 * a.nrec + r]};
-        un = sgn * bu[ax];
-        rw = (1.0 + G0 + 2.0 * Gout) / (1.0 - un);
-#pragma unroll
-        for (int k = 0; k < 3; k++) ut[k] = k == ax ? 0.0 : bu[k];
-      } else {
-        rw = a.rec_bc[3 * a.nrec + r];
-        un = (rw - 1.0 - G0 - 2.0 * Gout) / rw;
-      }
-      drho = rw - 1.0;
-#pragma unroll
-      for (int k = 0; k < 3; k++) m[k] = rw * (k == ax ? sgn * un : ut[k]);
-      return out;
-    }
-  }
-  drho = dev_sum(g);
-  m[0] = (g[1] - g[2]) + (g[7] + g[8]) + (g[9] + g[10]) - (g[11] + g[12]) - (g[13] + g[14]);
-  m[1] = (g[3] - g[4]) + (g[7] - g[8]) + (g[11] - g[12]) + (g[15] + g[16]) - (g[17] + g[18]);
-  m[2] = (g[5] - g[6]) + (g[9] - g[10]) + (g[13] - g[14]) + (g[15] - g[16]) + (g[17] - g[18]);
-  return out;
 }
 
 template <class C>
@@ -1745,6 +1634,7 @@ __device__ void marker_block(const FluidArgs& a, const BodyArgs& b, int blk, lon
 #pragma unroll
     for (int k = 0; k < 3; k++) s_acc[k][c] = __double_as_longlong(u3[k]);
     s_node[c] = ok ? node : -1;
+    if (ok && b.support_tf) b.support_tf[node >> TILE_SHIFT] = 1;
   }
   // a quad always holds one marker (or none), so the quad sums below see
   // four lanes that agree on mk
@@ -1786,6 +1676,7 @@ __device__ void marker_block(const FluidArgs& a, const BodyArgs& b, int blk, lon
         int x, y, z;
         coords(G, node, x, y, z);
         ok = cell_velocity<S>(a, (int)node, x, y, z, u3);
+        if (b.support_tf) b.support_tf[node >> TILE_SHIFT] = 1;
       }
       RowSums<3> rs;
       rs.clear();
@@ -3348,7 +3239,8 @@ __device__ __forceinline__ bool zh_unknown(int fc, int j) {
 }
 
 // One forward step of the fluid in the context's precision (storage S, the
-// same pull and collision as the stream-collide kernels) from a.A into a.B:
+// same pull and collision as the stream-collide kernels) from a.A into a.B
+// (null: only rho and u, into a.mac):
 // bulk node t of a.bulk_list, or
 // boundary record r.  Solid nodes are not written (they hold zero in every
 // buffer of the sweep).  hrec (may be null): [19][nrec], the records'
@@ -3368,6 +3260,7 @@ __device__ __forceinline__ void adj_fwd_bulk_one(const FluidArgs& a, int t) {
   node_force<C>(a, n, a.tflag && a.tflag[n >> TILE_SHIFT], Fx, Fy, Fz);
   collide<C>(g, Fx, Fy, Fz, (C)a.omega, dr, ux, uy, uz);
   if (a.mac) store_mac<C>(a, n, dr, ux, uy, uz);
+  if (!B) return;  // the step back needs the fields alone
 #pragma unroll
   for (int j = 0; j < 19; j++) B[(long long)j * G.plane + n] = (S)g[j];
 }
@@ -3389,6 +3282,7 @@ __device__ __forceinline__ void adj_fwd_rec_block(const FluidArgs& a, double* hr
   collide<C>(g, Fx, Fy, Fz, (C)a.omega, dr, ux, uy, uz);
   if (a.mac) store_mac<C>(a, n, dr, ux, uy, uz);
   S* B = (S*)a.B;
+  if (!B) return;
 #pragma unroll
   for (int j = 0; j < 19; j++) B[(long long)j * a.g.plane + n] = (S)g[j];
 }
@@ -3433,7 +3327,9 @@ __global__ __launch_bounds__(256) void k_adj_fwd_all(FluidArgs a, double* hrec, 
 //   mu_j = (1 - omega) l_j + P + sum_a U_a (e_ja - u_a)/rho,
 //   dJ/dF_a += Q_a + U_a/(2 rho).
 // With the sums over i of w_i l_i times 1, (1 + 3 e.u + 9/2 (e.u)^2 - 3/2 u.u),
-// (3 + 9 e.u) e_a and (e.F) e_a (SL, P', V_a, Z_a):
+// (3 + 9 e.u) e_a and (e.F) e_a (SL, P', V_a, Z_a), all of them combinations
+// of the ten moments of w_i l_i up to second order (which costs a third of the
+// operations of summing each over the directions):
 //   P = omega P',  U_a = omega rho V_a + 9 kf Z_a - 3 (omega rho u_a + kf F_a) SL,
 //   Q_a = kf (V_a - 3 u_a SL),  kf = 1 - omega/2.
 // dF[3] += dJ/d(omega) at fixed h: sum_i l_i (g^eq_i - h_i - G_i / (2 kf)).
@@ -3442,34 +3338,74 @@ __global__ __launch_bounds__(256) void k_adj_fwd_all(FluidArgs a, double* hrec, 
 // velocities; u depends on F, so they enter dJ/dF too), x7[4..6] = dJ/du*
 // of the pre-force velocity u* = m / rho that the forcing markers read
 // (mu_j += dJ/du* . (e_j - u*) / rho).  dFn: this node's dJ/dF, dw: dJ/d(omega).
-__device__ __forceinline__ void collide_vjp(const double (&h)[19], const double (&l)[19], double Fx, double Fy,
-                                            double Fz, double omega, const double (&x7)[7], double (&mu)[19],
-                                            double (&dFn)[3], double& dw) {
-  const double drho = dev_sum(h);
-  const double mx = (h[1] - h[2]) + (h[7] + h[8]) + (h[9] + h[10]) - (h[11] + h[12]) - (h[13] + h[14]);
-  const double my = (h[3] - h[4]) + (h[7] - h[8]) + (h[11] - h[12]) + (h[15] + h[16]) - (h[17] + h[18]);
-  const double mz = (h[5] - h[6]) + (h[9] - h[10]) + (h[13] - h[14]) + (h[15] - h[16]) + (h[17] - h[18]);
+// The populations h enter through their moments and sum l h alone (AdjIn),
+// which are formed as soon as they are loaded: h need not be held.
+struct AdjIn {
+  double drho, mx, my, mz, lh;
+};
+template <class C>
+__device__ __forceinline__ AdjIn adj_in(const C (&hc)[19], const double (&l)[19]) {
+  double h[19];
+  AdjIn s;
+  s.lh = 0.0;
+#pragma unroll
+  for (int j = 0; j < 19; j++) {
+    h[j] = (double)hc[j];
+    s.lh += l[j] * h[j];
+  }
+  s.drho = dev_sum(h);
+  s.mx = (h[1] - h[2]) + (h[7] + h[8]) + (h[9] + h[10]) - (h[11] + h[12]) - (h[13] + h[14]);
+  s.my = (h[3] - h[4]) + (h[7] - h[8]) + (h[11] - h[12]) + (h[15] + h[16]) - (h[17] + h[18]);
+  s.mz = (h[5] - h[6]) + (h[9] - h[10]) + (h[13] - h[14]) + (h[15] - h[16]) + (h[17] - h[18]);
+  return s;
+}
+
+// Entry i (padded index) of plane j of an adjoint field, or of a state: a
+// uniform base and a 32-bit byte offset, so that a load takes one address
+// register instead of two (a sweep's six FP64 fields of 19 planes fit the
+// device only below 2^29 padded nodes).
+template <class T>
+__device__ __forceinline__ T& plane_at(T* f, const Grid& G, int j, unsigned int i) {
+  return *(T*)((char*)(f + (long long)j * G.plane) + (size_t)(i * (unsigned int)sizeof(T)));
+}
+
+// mu_j = (1 - omega) l_j + A0 + e_j.(a0, a1, a2)
+struct AdjOut {
+  double A0, a0, a1, a2;
+  __device__ __forceinline__ double mu(int j, double lj, double omega) const {
+    return (1.0 - omega) * lj + A0 + (eterm(EX[j], a0) + eterm(EY[j], a1) + eterm(EZ[j], a2));
+  }
+};
+
+__device__ __forceinline__ AdjOut collide_vjp(const AdjIn& in, const double (&l)[19], double Fx, double Fy, double Fz,
+                                              double omega, const double (&x7)[7], double (&dFn)[3], double& dw) {
+  const double drho = in.drho, mx = in.mx, my = in.my, mz = in.mz;
   const double rho = 1.0 + drho, ir = 1.0 / rho;
   const double ux = (mx + 0.5 * Fx) * ir, uy = (my + 0.5 * Fy) * ir, uz = (mz + 0.5 * Fz) * ir;
   const double usq = ux * ux + uy * uy + uz * uz;
   const double kf = 1.0 - 0.5 * omega;
   const double uF = ux * Fx + uy * Fy + uz * Fz;
-  double SL = 0.0, Pp = 0.0, V0 = 0.0, V1 = 0.0, V2 = 0.0, Z0 = 0.0, Z1 = 0.0, Z2 = 0.0, Dw = 0.0;
+  double SL = 0.0, M0 = 0.0, M1 = 0.0, M2 = 0.0, XX = 0.0, YY = 0.0, ZZ = 0.0, XY = 0.0, XZ = 0.0, YZ = 0.0;
 #pragma unroll
   for (int i = 0; i < 19; i++) {
-    const double eu = EX[i] * ux + EY[i] * uy + EZ[i] * uz;
-    const double eF = EX[i] * Fx + EY[i] * Fy + EZ[i] * Fz;
     const double wl = WD[i] * l[i];
     SL += wl;
-    Pp += wl * (1.0 + 3.0 * eu + 4.5 * eu * eu - 1.5 * usq);
-    // d(out_i)/d(omega) = -(h_i - g^eq_i) - 1/2 w_i (3 (e.F - u.F) + 9 (e.u)(e.F))
-    Dw += wl * (drho + rho * (3.0 * eu + 4.5 * eu * eu - 1.5 * usq) - 0.5 * (3.0 * (eF - uF) + 9.0 * eu * eF)) -
-          l[i] * h[i];
-    const double v = wl * (3.0 + 9.0 * eu), zz = wl * eF;
-    if (EX[i]) { V0 += EX[i] * v; Z0 += EX[i] * zz; }
-    if (EY[i]) { V1 += EY[i] * v; Z1 += EY[i] * zz; }
-    if (EZ[i]) { V2 += EZ[i] * v; Z2 += EZ[i] * zz; }
+    if (EX[i]) { M0 += EX[i] * wl; XX += wl; }
+    if (EY[i]) { M1 += EY[i] * wl; YY += wl; }
+    if (EZ[i]) { M2 += EZ[i] * wl; ZZ += wl; }
+    if (EX[i] * EY[i]) XY += EX[i] * EY[i] * wl;
+    if (EX[i] * EZ[i]) XZ += EX[i] * EZ[i] * wl;
+    if (EY[i] * EZ[i]) YZ += EY[i] * EZ[i] * wl;
   }
+  const double Mu0 = XX * ux + XY * uy + XZ * uz, Mu1 = XY * ux + YY * uy + YZ * uz, Mu2 = XZ * ux + YZ * uy + ZZ * uz;
+  const double Z0 = XX * Fx + XY * Fy + XZ * Fz, Z1 = XY * Fx + YY * Fy + YZ * Fz, Z2 = XZ * Fx + YZ * Fy + ZZ * Fz;
+  const double V0 = 3.0 * M0 + 9.0 * Mu0, V1 = 3.0 * M1 + 9.0 * Mu1, V2 = 3.0 * M2 + 9.0 * Mu2;
+  // sum w l (3 e.u + 9/2 (e.u)^2 - 3/2 u.u)
+  const double Pe = 3.0 * (M0 * ux + M1 * uy + M2 * uz) + 4.5 * (Mu0 * ux + Mu1 * uy + Mu2 * uz) - 1.5 * usq * SL;
+  const double Pp = SL + Pe;
+  // d(out_i)/d(omega) = -(h_i - g^eq_i) - 1/2 w_i (3 (e.F - u.F) + 9 (e.u)(e.F))
+  const double Dw = drho * SL + rho * Pe -
+                    0.5 * (3.0 * (M0 * Fx + M1 * Fy + M2 * Fz - uF * SL) + 9.0 * (Mu0 * Fx + Mu1 * Fy + Mu2 * Fz));
   const double orho = omega * rho;
   const double U0 = orho * V0 + 9.0 * kf * Z0 - 3.0 * (orho * ux + kf * Fx) * SL + x7[1];
   const double U1 = orho * V1 + 9.0 * kf * Z1 - 3.0 * (orho * uy + kf * Fy) * SL + x7[2];
@@ -3479,35 +3415,38 @@ __device__ __forceinline__ void collide_vjp(const double (&h)[19], const double 
   dFn[0] = kf * (V0 - 3.0 * ux * SL) + 0.5 * a0;
   dFn[1] = kf * (V1 - 3.0 * uy * SL) + 0.5 * a1;
   dFn[2] = kf * (V2 - 3.0 * uz * SL) + 0.5 * a2;
-  dw = Dw;
+  dw = Dw - in.lh;
   // u* = m / rho (no force): mu_j += x7[4..6] . (e_j - u*) / rho
   A0 -= (x7[4] * mx + x7[5] * my + x7[6] * mz) * ir * ir;
   a0 += x7[4] * ir;
   a1 += x7[5] * ir;
   a2 += x7[6] * ir;
-#pragma unroll
-  for (int j = 0; j < 19; j++) mu[j] = (1.0 - omega) * l[j] + A0 + (EX[j] * a0 + EY[j] * a1 + EZ[j] * a2);
+  return AdjOut{A0, a0, a1, a2};
 }
 
 // Zou-He's transpose (the rule of zouhe(), affine in the known populations
 // for a fixed wall velocity or density): m = dJ/d(populations after the
 // rule) -> dJ/d(populations before it), in place; gs += dJ/ds with s the
-// scale of the wall velocity of a velocity face.  hz: the populations after
-// the rule (its known entries are the ones before).  With c_i = 1, 2, 0 for
+// scale of the wall velocity of a velocity face.  G0, Gout: the sums of the
+// populations after the rule (its known entries are the ones before) with
+// e.n = 0 and -1.  With c_i = 1, 2, 0 for
 // e_i.n = 0, -1, +1, rho_w depends on g_i through c_i / (1 - u_n) (velocity
 // face) and u_n through -c_i / rho_w (density face); the tangential sums T
 // through e_i (e_i.n = 0); each unknown j adds m_j to its opposite input.
-__device__ __forceinline__ void zouhe_vjp(const double (&hz)[19], double (&m)[19], int face, int kind,
-                                          const double* bc, double& gs) {
-  const int ax = face >> 1;
-  const int sg = (face & 1) ? -1 : 1;
-  double G0 = 0.0, Gout = 0.0;
+__device__ __forceinline__ void zouhe_sums(const double (&hz)[19], int face, double& G0, double& Gout) {
+  const int ax = face >> 1, sg = (face & 1) ? -1 : 1;
+  G0 = Gout = 0.0;
 #pragma unroll
   for (int j = 0; j < 19; j++) {
     const int en = sg * (ax == 0 ? EX[j] : (ax == 1 ? EY[j] : EZ[j]));
     G0 += en == 0 ? hz[j] : 0.0;
     Gout += en == -1 ? hz[j] : 0.0;
   }
+}
+__device__ __forceinline__ void zouhe_vjp(double G0, double Gout, double (&m)[19], int face, int kind,
+                                          const double* bc, double& gs) {
+  const int ax = face >> 1;
+  const int sg = (face & 1) ? -1 : 1;
   double u[3] = {bc[0], bc[1], bc[2]};
   double rho, un;
   if (kind == 0) {
@@ -3555,34 +3494,72 @@ __device__ __forceinline__ void zouhe_vjp(const double (&hz)[19], double (&m)[19
 }
 
 
-// The bounce-back transpose of record r's links: the mu m of each linked
-// direction goes back, with the rule's coefficients, to the three
-// populations the rule read (FP64 atomics: several links may feed one).
-template <class S>
-__device__ __forceinline__ void adj_links_one(const FluidArgs& a, int r, long long node, const double (&m)[19],
+// The bounce-back transposes of a block's records (r0 + 0..255): the mu of
+// each linked direction, which the records left in s_dyn by link, goes back,
+// with the rule's coefficients, to the three populations the rule read (FP64
+// atomics: several links may feed one).  As in pull_records the links are
+// spread over the threads, and their words and coefficients are loaded in one
+// batch ahead of the barrier: one record after another took its links in turn,
+// three loads and a wait each (record launch of the bifurcation, 133052 links:
+// 52 -> 41 us).  Every thread of the block calls.
+template <class S, int NP>
+__device__ __forceinline__ void adj_link_adds(const FluidArgs& a, int l0, int l1, int first, const int (&nd)[NP],
+                                              const unsigned int (&w)[NP], const typename Store<S>::C (&k)[NP][3],
                                               double* acc) {
-  const uint32_t mask = a.rec_mask[r];
-  if (!mask) return;
   const Grid& G = a.g;
-  const uint32_t hqm = a.rec_mb[r];
-  const int lk0 = a.rec_link0[r];
+  const double* s_m = s_dyn;
+#pragma unroll
+  for (int p = 0; p < NP; p++) {
+    const int l = first + p * 256;
+    if (l >= l1) continue;
+    const double m = s_m[l - l0];
+    const int j = w[p] & 31u, i = opp_of(j);
+    const bool hq = (w[p] >> 5) & 1u;
+    const int ex = dir_of(dir_bits(EX), j), ey = dir_of(dir_bits(EY), j), ez = dir_of(dir_bits(EZ), j);
+    int x, y, z;
+    coords(G, nd[p], x, y, z);
+    const long long n0 = nd[p], n1 = nbr(G, x, y, z, ex, ey, ez), n2 = nbr(G, x, y, z, 2 * ex, 2 * ey, 2 * ez);
+    double *ai = acc + (long long)i * G.plane, *at = hq ? acc + (long long)j * G.plane : ai;
+    const double k0 = (double)k[p][0], k1 = (double)k[p][1], k2 = (double)k[p][2];
+    if (k0 != 0.0) atomicAdd(ai + n0, k0 * m);
+    if (k1 != 0.0) atomicAdd(at + (hq ? n0 : n1), k1 * m);
+    if (k2 != 0.0) atomicAdd(at + (hq ? n1 : n2), k2 * m);
+  }
+}
+
+template <class S, int NP>
+__device__ __forceinline__ void adj_link_words(const FluidArgs& a, int l1, int first, int (&nd)[NP],
+                                               unsigned int (&w)[NP], typename Store<S>::C (&k)[NP][3]) {
   const typename Store<S>::C* lc = (const typename Store<S>::C*)a.lk_c;
   const long long nl = a.nlinks;
-  int x, y, z;
-  coords(G, node, x, y, z);
-  const Hood hd = hood(G, x, y, z);
 #pragma unroll
-  for (int j = 1; j < 19; j++) {
-    if (!((mask >> j) & 1u)) continue;
-    const int l = lk0 + __popc(mask & ((1u << j) - 1u));
-    const int i = OPP[j];
-    const bool hq = (hqm >> j) & 1u;
-    const long long n1 = hd.at(EX[j], EY[j], EZ[j]);  // x - e_i
-    const long long n2 = hd.at(2 * EX[j], 2 * EY[j], 2 * EZ[j]);
-    const double k0 = (double)lc[l], k1 = (double)lc[nl + l], k2 = (double)lc[2 * nl + l];
-    if (k0 != 0.0) atomicAdd(acc + (long long)i * G.plane + node, k0 * m[j]);
-    if (k1 != 0.0) atomicAdd(acc + (long long)(hq ? j : i) * G.plane + (hq ? node : n1), k1 * m[j]);
-    if (k2 != 0.0) atomicAdd(acc + (long long)(hq ? j : i) * G.plane + (hq ? n1 : n2), k2 * m[j]);
+  for (int p = 0; p < NP; p++) {
+    const int l = max(min(first + p * 256, l1 - 1), 0);
+    nd[p] = a.lk_node[l];
+    w[p] = a.lk_w[l];
+#pragma unroll
+    for (int q = 0; q < 3; q++) k[p][q] = lc[q * nl + l];
+  }
+}
+
+template <class S>
+__device__ __forceinline__ void adj_links_block(const FluidArgs& a, int r0, double* acc) {
+  const int l0 = a.rec_link0[r0], l1 = a.rec_link0[min(r0 + 256, a.nrec)];
+  const int first = l0 + (int)threadIdx.x;
+  {
+    int nd[LINK_PASSES];
+    unsigned int w[LINK_PASSES];
+    typename Store<S>::C k[LINK_PASSES][3];
+    adj_link_words<S, LINK_PASSES>(a, l1, first, nd, w, k);
+    __syncthreads();
+    adj_link_adds<S, LINK_PASSES>(a, l0, l1, first, nd, w, k, acc);
+  }
+  for (int l = first + LINK_PASSES * 256; l < l1; l += 256) {  // a block with more links than the batch holds
+    int nd[1];
+    unsigned int w[1];
+    typename Store<S>::C k[1][3];
+    adj_link_words<S, 1>(a, l1, l, nd, w, k);
+    adj_link_adds<S, 1>(a, l0, l1, l, nd, w, k, acc);
   }
 }
 
@@ -3592,90 +3569,112 @@ __device__ __forceinline__ void adj_links_one(const FluidArgs& a, int r, long lo
 // (lam + w) for bulk node t of a.bulk_list (REC false) or boundary record t
 // (REC true; h: the populations that entered the collision, Zou-He applied,
 // as the recompute kept them in hrec; at open-face records mu is then taken
-// back through Zou-He and the links' transposes go to acc_out).  dF, gs += the node's derivatives of the body force and
-// of the inlet-velocity scale.
+// back through Zou-He, and that of the linked directions is left in s_dyn for
+// adj_links_block).  dF, gs += the node's derivatives of the body force and of
+// the inlet-velocity scale.
 template <bool REC, class S>
 __device__ __forceinline__ void adj_reverse_one(const FluidArgs& a, const AdjStep& st, int t, double (&dF)[4],
                                                 double& gs) {
+  typedef typename Store<S>::C C;
   const Grid& G = a.g;
-  double h[19], l[19], m[19];
-  long long n;
-  if (REC) {
-    n = a.rec_node[t];
-#pragma unroll
-    for (int j = 0; j < 19; j++) h[j] = st.hrec[(long long)j * a.nrec + t];
-  } else {
-    n = a.bulk_list[t];
-  }
+  const int n = REC ? a.rec_node[t] : a.bulk_list[t];
+  const int q = REC ? a.nbulk_nodes + t : t;
+  const uint32_t am = st.amask[q], pm = st.lam ? 0u : st.pmask[q];
+  const int fc = REC ? a.rec_face[t] : 0xff;
   // with bodies: the IB force at the node, and whether the force-adjoint
   // pass (mode 1) has anything to do here
   // (mode 1 also visits the tiles of every marker's supports, flagged in etf
   // beforehand: dJ/dF is needed there even where the step's force is zero)
-  const bool fflag = st.ftf && st.ftf[n >> TILE_SHIFT];
-  if (st.mode == 1 && !fflag && !(st.etf && st.etf[n >> TILE_SHIFT])) return;
+  const uint8_t fft = st.ftf ? st.ftf[n >> TILE_SHIFT] : 0, eft = st.etf ? st.etf[n >> TILE_SHIFT] : 0;
+  if (st.mode == 1 && !fft && !eft) return;
   int x, y, z;
   coords(G, n, x, y, z);
   const Hood hd = hood(G, x, y, z);
-  if (!REC) {
-#pragma unroll
-    for (int j = 0; j < 19; j++) h[j] = (double)ldA<S>(a, j, hd.at(-EX[j], -EY[j], -EZ[j]));
-  }
-  const int q = REC ? a.nbulk_nodes + t : t;
-  const uint32_t am = st.amask[q];
+  double l[19];
   if (st.lam) {
 #pragma unroll
-    for (int j = 0; j < 19; j++) l[j] = st.lam[(long long)j * G.plane + n];
+    for (int j = 0; j < 19; j++) l[j] = plane_at(st.lam, G, j, n);
   } else {
-    const uint32_t pm = st.pmask[q];
+    // (a pull that another rule replaces reads the node's own entry and drops it)
 #pragma unroll
     for (int j = 0; j < 19; j++) {
-      const long long src = j == 0 ? n : hd.at(EX[j], EY[j], EZ[j]);
-      double v = ((pm >> j) & 1u) ? st.mu_next[(long long)j * G.plane + src] : 0.0;
+      const bool on = (pm >> j) & 1u;
+      const double v = plane_at(st.mu_next, G, j, j == 0 || !on ? n : hd.at(EX[j], EY[j], EZ[j]));
+      l[j] = on ? v : 0.0;
+    }
+  }
+  AdjIn in;
+  double G0 = 0.0, Gout = 0.0;
+  double hr[REC ? 19 : 1];
+  C hb[REC ? 1 : 19];
+  if constexpr (REC) {
+#pragma unroll
+    for (int j = 0; j < 19; j++) hr[j] = st.hrec[(long long)j * a.nrec + t];
+  } else {
+#pragma unroll
+    for (int j = 0; j < 19; j++) hb[j] = to_c(plane_at((const S*)a.A, G, j, hd.at(-EX[j], -EY[j], -EZ[j])));
+  }
+  if (!st.lam && (am & 0x7ffffu)) {
+#pragma unroll
+    for (int j = 0; j < 19; j++) {
       if ((am >> j) & 1u) {
-        double* pa = st.acc_in + (long long)j * G.plane + n;
-        v += *pa;
-        if (st.mode == 0) *pa = 0.0;
+        double& pa = plane_at(st.acc_in, G, j, n);
+        l[j] += pa;
+        if (st.mode == 0) pa = 0.0;
       }
-      l[j] = v;
     }
   }
   if (st.w && (am >> 31)) {  // w is non-zero at this node
 #pragma unroll
-    for (int j = 0; j < 19; j++) l[j] += st.w[(long long)j * G.plane + n];
+    for (int j = 0; j < 19; j++) l[j] += plane_at(st.w, G, j, n);
   }
   double Fx = a.gx, Fy = a.gy, Fz = a.gz;
-  if (fflag) {
+  if (fft) {
     Fx += (double)st.fx[n] * FX_INV;
     Fy += (double)st.fx[G.Np + n] * FX_INV;
     Fz += (double)st.fx[2 * G.Np + n] * FX_INV;
   }
   double x7[7] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-  if (st.etf && st.etf[n >> TILE_SHIFT]) {
+  if (eft) {
 #pragma unroll
     for (int k = 0; k < 7; k++) x7[k] = st.ext[(long long)k * G.Np + n];
   }
+  if constexpr (REC) {
+    in = adj_in(hr, l);
+    if (fc != 0xff) zouhe_sums(hr, fc & 7, G0, Gout);
+  } else {
+    in = adj_in(hb, l);
+  }
   double dFn[3], dw;
-  collide_vjp(h, l, Fx, Fy, Fz, a.omega, x7, m, dFn, dw);
+  const AdjOut o = collide_vjp(in, l, Fx, Fy, Fz, a.omega, x7, dFn, dw);
   if (st.mode == 1) {
 #pragma unroll
-    for (int k = 0; k < 3; k++) st.fbar[(long long)k * G.Np + n] = dFn[k];
+    for (int k = 0; k < 3; k++) st.fbar[k * G.Np + n] = dFn[k];
     return;
   }
   dF[0] += dFn[0];
   dF[1] += dFn[1];
   dF[2] += dFn[2];
   dF[3] += dw;
-  if (REC) {
-    const int fc = a.rec_face[t];
+  if constexpr (REC) {
+#pragma unroll
+    for (int j = 0; j < 19; j++) l[j] = o.mu(j, l[j], a.omega);
     if (fc != 0xff) {
       double bc[4];
-      for (int q = 0; q < 4; q++) bc[q] = a.rec_bc[(long long)q * a.nrec + t];
-      zouhe_vjp(h, m, fc & 7, (fc >> 4) & 1, bc, gs);
+      for (int k = 0; k < 4; k++) bc[k] = a.rec_bc[(long long)k * a.nrec + t];
+      zouhe_vjp(G0, Gout, l, fc & 7, (fc >> 4) & 1, bc, gs);
     }
-  }
 #pragma unroll
-  for (int j = 0; j < 19; j++) st.mu[(long long)j * G.plane + n] = m[j];
-  if (REC) adj_links_one<S>(a, t, n, m, st.acc_out);
+    for (int j = 0; j < 19; j++) plane_at(st.mu, G, j, n) = l[j];
+    const uint32_t mask = a.rec_mask[t];
+    const int lk = a.rec_link0[t] - a.rec_link0[t & ~255];
+#pragma unroll
+    for (int j = 1; j < 19; j++)
+      if ((mask >> j) & 1u) s_dyn[lk + __popc(mask & ((1u << j) - 1u))] = l[j];
+  } else {
+#pragma unroll
+    for (int j = 0; j < 19; j++) plane_at(st.mu, G, j, n) = o.mu(j, l[j], a.omega);
+  }
 }
 
 // part[block][0..4] += the block's sums of dJ/ds, dJ/dF, dJ/d(omega)
@@ -3701,27 +3700,37 @@ __device__ __forceinline__ void adj_part_add(double* part, double gs, const doub
 // grid-stride over at most ADJ_BLOCKS blocks each (partials of the record
 // launch in the second half of part).
 template <bool REC, class S>
-__global__ __launch_bounds__(256, REC ? 1 : 2) void k_adj_reverse(FluidArgs a, AdjStep st) {
+__global__ __launch_bounds__(256, 2) void k_adj_reverse(FluidArgs a, AdjStep st) {
   double dF[4] = {0.0, 0.0, 0.0, 0.0}, gs = 0.0;
   const int count = REC ? a.nrec : a.nbulk_nodes;
-  for (int t = blockIdx.x * 256 + threadIdx.x; t < count; t += gridDim.x * 256)
-    adj_reverse_one<REC, S>(a, st, t, dF, gs);
-  adj_part_add(st.part + (REC ? ADJ_PART * ADJ_BLOCKS : 0), gs, dF);
+  for (int t0 = blockIdx.x * 256; t0 < count; t0 += gridDim.x * 256) {
+    const int t = t0 + (int)threadIdx.x;
+    if (t < count) adj_reverse_one<REC, S>(a, st, t, dF, gs);
+    if (REC && st.mode == 0) {
+      adj_links_block<S>(a, t0, st.acc_out);
+      __syncthreads();  // the next records reuse the links' LDS
+    }
+  }
+  if (st.mode == 0) adj_part_add(st.part + (REC ? ADJ_PART * ADJ_BLOCKS : 0), gs, dF);
 }
 
 // Merged form: blocks below rec_blocks take records, the rest bulk nodes.
+// Bound by the waits for its loads at two waves per SIMD (221 registers; at
+// the 168 of three it spills 96): bifurcation, 175612 nodes, FP32 states,
+// 64 -> 51 us a step, the force-adjoint pass (mode 1) 20 -> 7.4 us.
 template <class S>
-__global__ __launch_bounds__(256) void k_adj_reverse_all(FluidArgs a, AdjStep st, int rec_blocks) {
+__global__ __launch_bounds__(256, 2) void k_adj_reverse_all(FluidArgs a, AdjStep st, int rec_blocks) {
   double dF[4] = {0.0, 0.0, 0.0, 0.0}, gs = 0.0;
   const int u = adj_unit(blockIdx.x, rec_blocks, gridDim.x);
   if (u < rec_blocks) {
     const int t = u * 256 + threadIdx.x;
     if (t < a.nrec) adj_reverse_one<true, S>(a, st, t, dF, gs);
+    if (st.mode == 0) adj_links_block<S>(a, u * 256, st.acc_out);
   } else {
     const int t = (u - rec_blocks) * 256 + threadIdx.x;
     if (t < a.nbulk_nodes) adj_reverse_one<false, S>(a, st, t, dF, gs);
   }
-  adj_part_add(st.part, gs, dF);
+  if (st.mode == 0) adj_part_add(st.part, gs, dF);
 }
 
 // Per non-solid node y (bulk list, then the records), once per sweep:
@@ -3812,18 +3821,22 @@ __global__ void k_adj_layout(Grid G, const uint8_t* ncls, const double* in, doub
 }
 
 // grad[0..4] = dJ/ds, dJ/dF, dJ/dtau = -omega^2 dJ/d(omega), summed over the
-// blocks in a fixed order.
-__global__ void k_adj_grad_final(const double* part, int nblk, double omega, const double* ibsum, int nout,
-                                 double* grad) {
-  const int q = threadIdx.x;
-  if (q >= nout) return;
-  if (q == 5) {
-    grad[5] = ibsum ? ibsum[1] : 0.0;
-    return;
-  }
-  double t = 0.0;
-  for (int b = 0; b < nblk; b++) t += part[ADJ_PART * b + q];
-  grad[q] = q == 4 ? -omega * omega * t + (ibsum ? ibsum[0] : 0.0) : t;
+// blocks in a fixed order: one block, every thread its own blocks' partials,
+// then a fixed tree (one thread per component took 466 us for 2800 blocks).
+__global__ __launch_bounds__(256) void k_adj_grad_final(const double* part, int nblk, double omega, const double* ibsum,
+                                                        int nout, double* grad) {
+  __shared__ double sh[8];
+  double t[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+  for (int b = threadIdx.x; b < nblk; b += 256)
+#pragma unroll
+    for (int q = 0; q < 5; q++) t[q] += part[ADJ_PART * b + q];
+#pragma unroll
+  for (int q = 0; q < 5; q++) t[q] = block_sum(t[q], sh);
+  if (threadIdx.x != 0) return;
+#pragma unroll
+  for (int q = 0; q < 4; q++) grad[q] = t[q];
+  grad[4] = -omega * omega * t[4] + (ibsum ? ibsum[0] : 0.0);
+  if (nout > 5) grad[5] = ibsum ? ibsum[1] : 0.0;
 }
 
 template <class S>
@@ -3854,11 +3867,12 @@ hipError_t launch_adjoint_mask(const FluidArgs& a, const double* w, uint32_t* pm
 template <class S>
 static void adj_reverse(const FluidArgs& a, const AdjStep& st, int merged, hipStream_t s) {
   const int rb = (int)cdiv(a.nrec, 256), bb = (int)cdiv(a.nbulk_nodes, 256);
+  const unsigned lds = (unsigned)(a.lds_links[2] * sizeof(double));  // a block's links
   if (merged) {
-    if (rb + bb > 0) k_adj_reverse_all<S><<<rb + bb, 256, 0, s>>>(a, st, rb);
+    if (rb + bb > 0) k_adj_reverse_all<S><<<rb + bb, 256, rb > 0 ? lds : 0u, s>>>(a, st, rb);
   } else {
     if (bb > 0) k_adj_reverse<false, S><<<std::min(bb, ADJ_BLOCKS), 256, 0, s>>>(a, st);
-    if (rb > 0) k_adj_reverse<true, S><<<std::min(rb, ADJ_BLOCKS), 256, 0, s>>>(a, st);
+    if (rb > 0) k_adj_reverse<true, S><<<std::min(rb, ADJ_BLOCKS), 256, lds, s>>>(a, st);
   }
 }
 
@@ -3885,7 +3899,7 @@ hipError_t launch_adjoint_layout(const Grid& g, const uint8_t* ncls, const doubl
 
 hipError_t launch_adjoint_grad(const double* part, int nblk, double omega, const double* ibsum, int nout,
                                double* grad, hipStream_t s) {
-  k_adj_grad_final<<<1, 64, 0, s>>>(part, nblk, omega, ibsum, nout, grad);
+  k_adj_grad_final<<<1, 256, 0, s>>>(part, nblk, omega, ibsum, nout, grad);
   return hipGetLastError();
 }
 
@@ -4228,110 +4242,144 @@ __device__ __forceinline__ T dot_t(const T (&a)[3], const T (&b)[3]) {
   return a[0] * b[0] + a[1] * b[1] + a[2] * b[2];
 }
 
-__device__ __forceinline__ double shfl_xor_t(double a, int m) { return __shfl_xor(a, m, 64); }
-template <int N>
-__device__ __forceinline__ Dual<N> shfl_xor_t(const Dual<N>& a, int m) {
-  Dual<N> r;
-  r.v = __shfl_xor(a.v, m, 64);
+// The fits' derivatives with respect to their point p, in closed form.  With
+// d = x_k - p, P = (1, d), W = exp(-K |d|^2), A = sum W P P^T, b = sum W P f
+// and c = A^-1 b: dW/dp_m = 2 K d_m W and dP/dp_m = -(0, e_m) give
+//   dc/dp_m = c_m e_0 + 2 K A^-1 sum_k W d_m P (f_k - P.c)
+// (the terms in sum W P (f - P.c) vanish: the normal equations).  A functional
+// s.c of the coefficients, z = A^-1 s, has then the derivative
+//   c_m s_0 + 2 K sum_k W d_m (z.P) (f_k - P.c)
+// and depends on the node values through W (z.P): one more pass over the
+// supports with a few products each, where dual numbers carried three
+// derivatives through the moment matrix, its factor and 27 solves.
+//
+// A quad of lanes per point, its lane's seven supports as in the step's fits
+// (rows sub, sub + 4 and a third of row 8).
+struct QuadSupports {
+  int node[7];  // padded index, -1 where there is no usable support
+  int cell[7];  // x + 3 (y + 3 z) offsets as kx | ky << 2 | kz << 4
+  double W[7], dx[7], dy[3], dz[3];
+};
+__device__ __forceinline__ void quad_supports(const FluidArgs& a, int sub, const double (&p)[3], const int (&bs)[3],
+                                              QuadSupports& q) {
+  const Grid& G = a.g;
+  int ox[3], oy[3], oz[3];
+  bool ix[3], iy[3], iz[3];
+  axis_nodes(bs[0], G.nx, G.per[0], 1, ox, ix);
+  axis_nodes(bs[1], G.ny, G.per[1], G.px, oy, iy);
+  axis_nodes(bs[2], G.nz, G.per[2], G.px * G.ny, oz, iz);
+  uint8_t cls[7];
+  double wr[3];
+  double wx[3], wy[3], wz[3], dx[3];
+  quad_weights(sub, p, bs, wx, wy, wz);
 #pragma unroll
-  for (int i = 0; i < N; i++) r.d[i] = __shfl_xor(a.d[i], m, 64);
-  return r;
+  for (int k = 0; k < 3; k++) dx[k] = (double)(bs[0] + k - 1) - p[0];
+#pragma unroll
+  for (int i = 0; i < 3; i++) {
+    int ky = 2, kz = 2;
+    if (i < 2) row_yz(sub + 4 * i, ky, kz);
+    const int row = sel3i(ky, oy) + sel3i(kz, oz);
+    const bool rin = sel3b(ky, iy) && sel3b(kz, iz);
+    q.dy[i] = (double)(bs[1] + ky - 1) - p[1];
+    q.dz[i] = (double)(bs[2] + kz - 1) - p[2];
+    wr[i] = sel3(ky, wy) * sel3(kz, wz);
+#pragma unroll
+    for (int k = 0; k < (i < 2 ? 3 : 1); k++) {
+      const int n = (i < 2 ? ox[k] : sel3i(sub, ox)) + row;
+      const bool in = rin && (i < 2 ? ix[k] : sub < 3 && sel3b(sub, ix));
+      cls[3 * i + k] = a.ncls[n];
+      q.node[3 * i + k] = in ? n : -1;
+      q.cell[3 * i + k] = (i < 2 ? k : min(sub, 2)) | ky << 2 | kz << 4;
+      q.dx[3 * i + k] = i < 2 ? dx[k] : sel3(sub, dx);
+      q.W[3 * i + k] = (i < 2 ? wx[k] : sel3(sub, wx)) * wr[i];
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < 7; k++)
+    if (q.node[k] < 0 || cls[k] == CLS_SOLID) {
+      q.node[k] = -1;
+      q.W[k] = 0.0;
+    }
 }
 
-// Sum over the GS lanes of an aligned group inside one wave (xor tree:
-// every lane ends with the same value, bit for bit).
-template <int GS, class T>
-__device__ __forceinline__ T group_sum(T v) {
+// Moments of the supports with the fields f[7][NF].
+template <int NF>
+__device__ __forceinline__ void quad_moments(const QuadSupports& q, const double (&f)[7][NF], FitSums<NF>& fs) {
+  fs.clear();
 #pragma unroll
-  for (int m = GS / 2; m >= 1; m >>= 1) v = v + shfl_xor_t(v, m);
-  return v;
+  for (int i = 0; i < 3; i++) {
+    RowSums<NF> rs;
+    rs.clear();
+#pragma unroll
+    for (int k = 0; k < (i < 2 ? 3 : 1); k++) rs.add(q.W[3 * i + k], q.dx[3 * i + k], f[3 * i + k]);
+    fs.add(rs, 1.0, q.dy[i], q.dz[i]);
+  }
+  fs.quad();
 }
 
-// MLS at point p in any scalar type: the 27 supports of floor(p + 1/2)
-// (solid and out-of-box nodes left out, as in the step), A = sum W P P^T
-// with W = exp(-|d|^2 / (2.6^2 0.3^2)) and P = (1, d), d = x_k - p, then for
-// each usable support fn(k, node, psi), psi = W A^{-1} P (psi[0] the
-// interpolation weight phi_k, psi[1..3] the gradient weights of the linear
-// fit).  A singular moment matrix (the step's rule) calls nothing and
-// returns false.
-// The work is split over a group of GS lanes (all of them call it, with the
-// same p): lane l takes the supports l, l + GS, ...; the moment matrix is
-// summed over the group, and fn runs for the lane's own supports.
-template <int GS, class T, class Fn>
-__device__ bool mls_each_g(const Grid& G, const uint8_t* ncls, const T (&p)[3], int lane, Fn&& fn) {
-  const int bs[3] = {(int)floor(dval(p[0]) + 0.5), (int)floor(dval(p[1]) + 0.5), (int)floor(dval(p[2]) + 0.5)};
-  T A[10];
+__device__ __forceinline__ double lin4(const double (&c)[4], double dx, double dy, double dz) {
+  return c[0] + c[1] * dx + c[2] * dy + c[3] * dz;
+}
+
+// Box of stencil bases of a block's points (bs of the quads with on set), its
+// cells with the supports around them; false when they exceed BOX_CELLS or no
+// quad is on.  s_wbox: [4][6] ints.  Every thread calls (two barriers).
+struct Box {
+  int x0, y0, z0, ex, ey, ez;
+  __device__ __forceinline__ int cells() const { return ex * ey * ez; }
+  __device__ __forceinline__ int corner(const int (&bs)[3]) const {
+    return (bs[0] - 1 - x0) + ex * ((bs[1] - 1 - y0) + ey * (bs[2] - 1 - z0));
+  }
+  __device__ __forceinline__ int at(int c00, int cell) const {
+    return c00 + (cell & 3) + ex * (((cell >> 2) & 3) + ey * (cell >> 4));
+  }
+};
+__device__ __forceinline__ bool block_box(const int (&bs)[3], bool on, int (*s_wbox)[6], Box& bx) {
+  __syncthreads();
 #pragma unroll
-  for (int k = 0; k < 10; k++) A[k] = Scal<T>::c(0.0);
-  for (int k = lane; k < 27; k += GS) {
-    long long node;
-    const int c[3] = {bs[0] + k % 3 - 1, bs[1] + (k / 3) % 3 - 1, bs[2] + k / 9 - 1};
-    if (!support_node(G, ncls, c[0], c[1], c[2], node)) continue;
-    const T dx = (double)c[0] - p[0], dy = (double)c[1] - p[1], dz = (double)c[2] - p[2];
-    const T W = dexp((dx * dx + dy * dy + dz * dz) * (-MLS_K));
-    const T wx = W * dx, wy = W * dy, wz = W * dz;
-    A[0] += W;
-    A[1] += wx;
-    A[2] += wy;
-    A[3] += wz;
-    A[4] += wx * dx;
-    A[5] += wx * dy;
-    A[6] += wx * dz;
-    A[7] += wy * dy;
-    A[8] += wy * dz;
-    A[9] += wz * dz;
+  for (int k = 0; k < 3; k++) {
+    const int lo = wave_ext<false>(on ? bs[k] : INT_MAX), hi = wave_ext<true>(on ? bs[k] : INT_MIN);
+    if ((threadIdx.x & 63) == 0) {
+      s_wbox[threadIdx.x >> 6][k] = lo;
+      s_wbox[threadIdx.x >> 6][3 + k] = hi;
+    }
   }
-  if (GS > 1) {
+  __syncthreads();
+  int lo[3], hi[3];
 #pragma unroll
-    for (int k = 0; k < 10; k++) A[k] = group_sum<GS>(A[k]);
+  for (int k = 0; k < 3; k++) {
+    lo[k] = min(min(s_wbox[0][k], s_wbox[1][k]), min(s_wbox[2][k], s_wbox[3][k]));
+    hi[k] = max(max(s_wbox[0][3 + k], s_wbox[1][3 + k]), max(s_wbox[2][3 + k], s_wbox[3][3 + k]));
   }
-  const int ix[4][4] = {{0, 1, 2, 3}, {1, 4, 5, 6}, {2, 5, 7, 8}, {3, 6, 8, 9}};
-  const double dmax = fmax(fmax(dval(A[0]), dval(A[4])), fmax(dval(A[7]), dval(A[9])));
-  if (!(dmax > 0.0)) return false;
-  // Cholesky factor, lower triangle packed row by row: L(i, j) = Lp[i (i + 1) / 2 + j]
-  T Lp[10];
-  for (int j = 0; j < 4; j++) {
-    T d = A[ix[j][j]];
-    for (int k = 0; k < j; k++) d -= Lp[j * (j + 1) / 2 + k] * Lp[j * (j + 1) / 2 + k];
-    if (!(dval(d) > 1e-10 * dmax)) return false;
-    Lp[j * (j + 1) / 2 + j] = dsqrt(d);
-    for (int i = j + 1; i < 4; i++) {
-      T v = A[ix[i][j]];
-      for (int k = 0; k < j; k++) v -= Lp[i * (i + 1) / 2 + k] * Lp[j * (j + 1) / 2 + k];
-      Lp[i * (i + 1) / 2 + j] = v / Lp[j * (j + 1) / 2 + j];
-    }
+  if (hi[0] < lo[0]) {
+    bx = Box{0, 0, 0, 0, 0, 0};
+    return false;
   }
-  for (int k = lane; k < 27; k += GS) {
-    long long node;
-    const int c[3] = {bs[0] + k % 3 - 1, bs[1] + (k / 3) % 3 - 1, bs[2] + k / 9 - 1};
-    if (!support_node(G, ncls, c[0], c[1], c[2], node)) continue;
-    const T P[4] = {Scal<T>::c(1.0), (double)c[0] - p[0], (double)c[1] - p[1], (double)c[2] - p[2]};
-    const T W = dexp((P[1] * P[1] + P[2] * P[2] + P[3] * P[3]) * (-MLS_K));
-    // psi = W A^{-1} P by the two triangular solves
-    T y[4], psi[4];
-    for (int i = 0; i < 4; i++) {
-      T v = P[i];
-      for (int j = 0; j < i; j++) v -= Lp[i * (i + 1) / 2 + j] * y[j];
-      y[i] = v / Lp[i * (i + 1) / 2 + i];
+  bx.x0 = lo[0] - 1;
+  bx.y0 = lo[1] - 1;
+  bx.z0 = lo[2] - 1;
+  bx.ex = hi[0] - lo[0] + 3;
+  bx.ey = hi[1] - lo[1] + 3;
+  bx.ez = hi[2] - lo[2] + 3;
+  return (long long)bx.ex * bx.ey * bx.ez <= BOX_CELLS;
+}
+
+// The cell c of a box: node coordinates in the periodic box; false outside.
+__device__ __forceinline__ bool box_node(const Grid& G, const Box& bx, int c, int (&p)[3], int& node) {
+  const int q = (int)(((float)c + 0.5f) / (float)bx.ex), cz = (int)(((float)q + 0.5f) / (float)bx.ey);
+  p[0] = bx.x0 + c - q * bx.ex;
+  p[1] = bx.y0 + q - cz * bx.ey;
+  p[2] = bx.z0 + cz;
+  const int dim[3] = {G.nx, G.ny, G.nz};
+#pragma unroll
+  for (int k = 0; k < 3; k++)
+    if (p[k] < 0 || p[k] >= dim[k]) {
+      if (!G.per[k]) return false;
+      p[k] = ((p[k] % dim[k]) + dim[k]) % dim[k];
     }
-    for (int i = 3; i >= 0; i--) {
-      T v = y[i];
-      for (int j = i + 1; j < 4; j++) v -= Lp[j * (j + 1) / 2 + i] * psi[j];
-      psi[i] = v / Lp[i * (i + 1) / 2 + i];
-    }
-    for (int i = 0; i < 4; i++) psi[i] = W * psi[i];
-    fn(k, node, psi);
-  }
+  node = p[0] + G.px * (p[1] + G.ny * p[2]);
   return true;
 }
-
-template <class T, class Fn>
-__device__ bool mls_each(const Grid& G, const uint8_t* ncls, const T (&p)[3], Fn&& fn) {
-  return mls_each_g<1>(G, ncls, p, 0, fn);
-}
-
-// Lanes per point in the IB transposes' MLS fits.
-constexpr int ADJ_GS = 8;
 
 // The bending force of a hinge (a, b, c, d) in any scalar type: the signed
 // dihedral angle and F_r = -k_b sin(theta - theta0) dtheta/dx_r, with the
@@ -4395,245 +4443,282 @@ __global__ __launch_bounds__(256) void k_adjb_vertex(BodyArgs b, AdjIB ib) {
   }
 }
 
-// Lift a function of a probe point (derivatives along its three
-// coordinates) to the nine vertex coordinates the point depends on.
-__device__ __forceinline__ Dual<9> lift9(const Dual<3>& f, const Dual<9> (&p)[3]) {
-  Dual<9> r;
-  r.v = f.v;
-#pragma unroll
-  for (int i = 0; i < 9; i++) r.d[i] = f.d[0] * p[0].d[i] + f.d[1] * p[1].d[i] + f.d[2] * p[2].d[i];
-  return r;
-}
-
-// Elements, probes and vertex velocities transposed, one thread each:
-// items [0, ne) edges, [ne, ne + nh) hinges, then faces, then soft vertices.
-// Threads: one per edge and hinge, then (from the next multiple of 64) a
-// group of ADJ_GS lanes per face and probe side, then per soft vertex; a
-// group's MLS fits split the supports over its lanes.
-__host__ __device__ __forceinline__ long long adjb_body_face0(const BodyArgs& b) {
-  return ((long long)b.ne + b.nh + 63) / 64 * 64;
-}
-
-template <class S>
-__global__ __launch_bounds__(128) void k_adjb_body(FluidArgs a, BodyArgs b, AdjIB ib) {
-  const long long gt = blockIdx.x * 128LL + threadIdx.x;
-  const Grid& G = a.g;
+// Edges and hinges transposed, one thread each (whole waves of them): dJ/dkappa
+// is summed over the wave first, one atomic per wave.
+__device__ __forceinline__ void adjb_element(const BodyArgs& b, const AdjIB& ib, long long gt) {
   const double* X = b.Xcur;
-  const double ikap = 1.0 / ib.kappa;
-  const long long g0 = adjb_body_face0(b);
-  if (gt < g0) {
-    // whole waves of elements (and padding lanes): dJ/dkappa summed over
-    // the wave first, one atomic per wave
-    const int it = gt < b.ne + b.nh ? (int)gt : -1;
-    double fy = 0.0;
-    if (it >= 0 && it < b.ne) {
-      // stretching (Eq. strainFor): F_a = -k (l - l0) r / l, r = x_a - x_b; its
-      // Jacobian K = -k [(1 - l0/l) 1 + l0 r r^T / l^3] is symmetric, and
-      // dF_b = -dF_a
-      const int e = it, va = b.edges[2 * e], vb = b.edges[2 * e + 1];
-      double r[3], y[3];
-      for (int k = 0; k < 3; k++) {
-        r[k] = X[3 * va + k] - X[3 * vb + k];
-        y[k] = ib.Fb[3 * va + k] - ib.Fb[3 * vb + k];
-      }
-      const double l = sqrt(r[0] * r[0] + r[1] * r[1] + r[2] * r[2]);
-      const double kl = b.kl[e], l0 = b.l0[e];
-      const double ry = r[0] * y[0] + r[1] * y[1] + r[2] * y[2];
-      for (int k = 0; k < 3; k++) {
-        const double g = -kl * ((1.0 - l0 / l) * y[k] + l0 * ry * r[k] / (l * l * l));
-        atomicAdd(ib.LP + 3 * va + k, g);
-        atomicAdd(ib.LP + 3 * vb + k, -g);
-        fy += -kl * (l - l0) * r[k] / l * y[k];  // the force is linear in the modulus
-      }
-    } else if (it >= 0) {
-      // bending: the force is minus the gradient of the hinge energy, so its
-      // Jacobian is symmetric and the transposed product is the derivative
-      // along the adjoint itself (one dual direction)
-      const int h = it - b.ne;
-      const int32_t* H = b.hinges + 4 * h;
-      Dual<1> P[4][3], F[4][3];
-      for (int r = 0; r < 4; r++)
-        for (int k = 0; k < 3; k++) {
-          P[r][k].v = X[3 * H[r] + k];
-          P[r][k].d[0] = ib.Fb[3 * H[r] + k];
-        }
-      hinge_force_t(P, b.kb[h], b.theta0[h], F);
-      for (int r = 0; r < 4; r++)
-        for (int k = 0; k < 3; k++) {
-          atomicAdd(ib.LP + 3 * H[r] + k, F[r][k].d[0]);
-          fy += F[r][k].v * ib.Fb[3 * H[r] + k];
-        }
+  const int it = gt < b.ne + b.nh ? (int)gt : -1;
+  double fy = 0.0;
+  if (it >= 0 && it < b.ne) {
+    // stretching (Eq. strainFor): F_a = -k (l - l0) r / l, r = x_a - x_b; its
+    // Jacobian K = -k [(1 - l0/l) 1 + l0 r r^T / l^3] is symmetric, and
+    // dF_b = -dF_a
+    const int e = it, va = b.edges[2 * e], vb = b.edges[2 * e + 1];
+    double r[3], y[3];
+    for (int k = 0; k < 3; k++) {
+      r[k] = X[3 * va + k] - X[3 * vb + k];
+      y[k] = ib.Fb[3 * va + k] - ib.Fb[3 * vb + k];
     }
-    fy = group_sum<64>(fy);
-    if ((threadIdx.x & 63) == 0 && fy != 0.0) atomicAdd(ib.gsum + 1, fy * ikap);
-    return;
+    const double l = sqrt(r[0] * r[0] + r[1] * r[1] + r[2] * r[2]);
+    const double kl = b.kl[e], l0 = b.l0[e];
+    const double ry = r[0] * y[0] + r[1] * y[1] + r[2] * y[2];
+    for (int k = 0; k < 3; k++) {
+      const double g = -kl * ((1.0 - l0 / l) * y[k] + l0 * ry * r[k] / (l * l * l));
+      atomicAdd(ib.LP + 3 * va + k, g);
+      atomicAdd(ib.LP + 3 * vb + k, -g);
+      fy += -kl * (l - l0) * r[k] / l * y[k];  // the force is linear in the modulus
+    }
+  } else if (it >= 0) {
+    // bending: the force is minus the gradient of the hinge energy, so its
+    // Jacobian is symmetric and the transposed product is the derivative
+    // along the adjoint itself (one dual direction)
+    const int h = it - b.ne;
+    const int32_t* H = b.hinges + 4 * h;
+    Dual<1> P[4][3], F[4][3];
+    for (int r = 0; r < 4; r++)
+      for (int k = 0; k < 3; k++) {
+        P[r][k].v = X[3 * H[r] + k];
+        P[r][k].d[0] = ib.Fb[3 * H[r] + k];
+      }
+    hinge_force_t(P, b.kb[h], b.theta0[h], F);
+    for (int r = 0; r < 4; r++)
+      for (int k = 0; k < 3; k++) {
+        atomicAdd(ib.LP + 3 * H[r] + k, F[r][k].d[0]);
+        fy += F[r][k].v * ib.Fb[3 * H[r] + k];
+      }
   }
-  const int lane = (int)((gt - g0) % ADJ_GS);
-  const long long grp = (gt - g0) / ADJ_GS;
-  const long long nfg = (2LL * b.nf * ADJ_GS + 63) / 64 * 64 / ADJ_GS;  // face groups, whole waves
-  if (grp < nfg) {
-    // face force Ft = A [-(r+ - r-)/3 n + nu (r+ (G+ + G+^T) - r- (G- + G-^T)) n]
-    // + k_v (1 - V/V0) A n (probes at c +- 1.2 n: fitted density r and
-    // velocity gradient G), a third at each vertex: dJ/dFt = the mean of
-    // the vertices' dJ/dF.  Two groups per face: the outer probe's terms
-    // with the volume term, and the inner probe's.
-    const bool real = grp < 2LL * b.nf;  // groups past the faces pad the last wave
-    const int f = real ? (int)(grp >> 1) : 0, side = (int)(grp & 1);
-    const int body = b.face_body[f];
-    const int vv[3] = {b.faces[3 * f], b.faces[3 * f + 1], b.faces[3 * f + 2]};
-    double ab[3];
-    for (int k = 0; k < 3; k++) ab[k] = (ib.Fb[3 * vv[0] + k] + ib.Fb[3 * vv[1] + k] + ib.Fb[3 * vv[2] + k]) / 3.0;
-    // unit normal n and area A with their derivatives in the nine vertex
-    // coordinates (j = 3 r + k), by dual numbers in this scope only
-    double nv[3], Av, dn[3][9], dA[9], cen[3];
-    {
-      Dual<9> P[3][3];
-      for (int r = 0; r < 3; r++)
-        for (int k = 0; k < 3; k++) P[r][k] = dseed<9>(X[3 * vv[r] + k], 3 * r + k);
-      Dual<9> u[3], w[3], N[3];
-      for (int k = 0; k < 3; k++) {
-        u[k] = P[1][k] - P[0][k];
-        w[k] = P[2][k] - P[0][k];
-      }
-      cross_t(u, w, N);
-      const Dual<9> ln = dsqrt(dot_t(N, N));
-      for (int k = 0; k < 3; k++) {
-        const Dual<9> nk = N[k] / ln;
-        nv[k] = nk.v;
-        for (int j = 0; j < 9; j++) dn[k][j] = nk.d[j];
-        cen[k] = (P[0][k].v + P[1][k].v + P[2][k].v) / 3.0;
-      }
-      Av = 0.5 * ln.v;
-      for (int j = 0; j < 9; j++) dA[j] = 0.5 * ln.d[j];
-    }
-    const double nu = b.nu;
-    const double V0 = b.b_param[8 * body], kv = b.b_param[8 * body + 2];
-    const double cv = kv * (1.0 - b.b_diag[16 * body] / V0);
-    const double an = ab[0] * nv[0] + ab[1] * nv[1] + ab[2] * nv[2];
-    double dan[9];
-    for (int j = 0; j < 9; j++) dan[j] = ab[0] * dn[0][j] + ab[1] * dn[1][j] + ab[2] * dn[2][j];
-    // ds[j]: derivative of this group's part of ab . Ft in vertex coordinate j
-    double ds[9];
-    for (int j = 0; j < 9; j++) ds[j] = side == 0 ? cv * (dA[j] * an + Av * dan[j]) : 0.0;  // the volume force
-    double visc = 0.0;  // d s / d nu
-    {
-      const double sg = side == 0 ? 1.2 : -1.2, sgn = side == 0 ? 1.0 : -1.0;
-      double pp[3];
-      for (int k = 0; k < 3; k++) pp[k] = cen[k] + nv[k] * sg;
-      // the fits at the probe, with their derivatives in its coordinates
-      const Dual<3> q[3] = {dseed<3>(pp[0], 0), dseed<3>(pp[1], 1), dseed<3>(pp[2], 2)};
-      Dual<3> r3 = Scal<Dual<3>>::c(0.0), G3[3][3];
-      for (int i = 0; i < 3; i++)
-        for (int c = 0; c < 3; c++) G3[i][c] = Scal<Dual<3>>::c(0.0);
-      mls_each_g<ADJ_GS>(G, a.ncls, q, lane, [&](int, long long node, const Dual<3>(&psi)[4]) {
-        double dr, uu[3];
-        load_mac<S>(a, node, dr, uu[0], uu[1], uu[2]);
-        r3 += psi[0] * dr;
-        for (int i = 0; i < 3; i++)
-          for (int c = 0; c < 3; c++) G3[i][c] += psi[1 + c] * uu[i];
-      });
-      r3 = group_sum<ADJ_GS>(r3) + 1.0;  // the weights add up to 1: rho = 1 + the fit of rho - 1
-      for (int i = 0; i < 3; i++)
-        for (int c = 0; c < 3; c++) G3[i][c] = group_sum<ADJ_GS>(G3[i][c]);
-      // s = A sgn r Q with Q = -an/3 + nu sv, sv = sum_ic ab_i (G_ic + G_ci) n_c;
-      // the probe moves with the face: dp_m/dx_j = [m == j % 3]/3 + sg dn_m/dx_j
-      double sv = 0.0, h[3] = {0.0, 0.0, 0.0}, qc[3] = {0.0, 0.0, 0.0};
-      for (int i = 0; i < 3; i++)
-        for (int c = 0; c < 3; c++) {
-          const double gs = G3[i][c].v + G3[c][i].v;
-          sv += ab[i] * gs * nv[c];
-          qc[c] += ab[i] * gs;
-          for (int m = 0; m < 3; m++) h[m] += ab[i] * (G3[i][c].d[m] + G3[c][i].d[m]) * nv[c];
-        }
-      const double rv = r3.v, Q = -an / 3.0 + nu * sv;
-      for (int j = 0; j < 9; j++) {
-        double drj = 0.0, dsvj = 0.0;
-        for (int m = 0; m < 3; m++) {
-          const double dp = (m == j % 3 ? 1.0 / 3.0 : 0.0) + sg * dn[m][j];
-          drj += r3.d[m] * dp;
-          dsvj += h[m] * dp + qc[m] * dn[m][j];
-        }
-        const double dQ = -dan[j] / 3.0 + nu * dsvj;
-        ds[j] += sgn * (dA[j] * rv * Q + Av * (drj * Q + rv * dQ));
-      }
-      visc += Av * sgn * rv * sv;
-      // field adjoints at this probe's supports
-      const double rbar = Av * sgn * Q;
-      double Gbar[3][3];
-      for (int i = 0; i < 3; i++)
-        for (int c = 0; c < 3; c++) Gbar[i][c] = Av * sgn * nu * rv * (ab[i] * nv[c] + ab[c] * nv[i]);
-      if (real)  // (uniform over the group)
-        mls_each_g<ADJ_GS>(G, a.ncls, pp, lane, [&](int, long long node, const double(&psi)[4]) {
-          atomicAdd(ib.ext + node, rbar * psi[0]);
-          for (int i = 0; i < 3; i++)
-            atomicAdd(ib.ext + (long long)(1 + i) * G.Np + node,
-                      Gbar[i][0] * psi[1] + Gbar[i][1] * psi[2] + Gbar[i][2] * psi[3]);
-          set_tile(ib.etf, node);
-        });
-    }
-    const double A_v = Av;
-    // the scalar gradients summed over the wave first (one group's lane 0
-    // per face side contributes), then one atomic per wave
-    const bool lead = real && lane == 0;
-    const double gv = group_sum<64>(lead ? visc / 3.0 : 0.0);  // nu = (tau - 1/2) / 3
-    const double gk = group_sum<64>(lead && side == 0 && b.b_param[8 * body + 6] != 0.0 ? cv * A_v * an * ikap : 0.0);
-    if ((threadIdx.x & 63) == 0) {
-      if (gv != 0.0) atomicAdd(ib.gsum, gv);
-      if (gk != 0.0) atomicAdd(ib.gsum + 1, gk);
-    }
-    // sum of A n . dJ/dFt per body: one atomic per wave when its faces
-    // belong to one body
-    {
-      const int bsel = lead && side == 0 ? body : -1;
-      const double gb = bsel >= 0 ? A_v * an : 0.0;
-      const unsigned long long bm = __ballot(bsel >= 0);
-      if (bm) {
-        const int first = __shfl(bsel, __ffsll((unsigned long long)bm) - 1, 64);
-        if (__ballot(bsel >= 0 && bsel != first) == 0ull) {
-          const double t = group_sum<64>(gb);
-          if ((threadIdx.x & 63) == 0) atomicAdd(ib.gsum + 2 + first, t);
-        } else if (bsel >= 0) {
-          atomicAdd(ib.gsum + 2 + bsel, gb);
-        }
-      }
-    }
-    if (!lead) return;
-    for (int r = 0; r < 3; r++)
-      for (int k = 0; k < 3; k++) atomicAdd(ib.LP + 3 * vv[r] + k, ds[3 * r + k]);
-    return;
-  }
-  const long long idx = grp - nfg;
-  if (idx >= b.nsoft_v) return;
-  // MLS velocity at the vertex: u0 = sum phi_k u_k
-  const int v = b.soft_vlist[idx];
-  const double ub[3] = {ib.ub0[3 * v], ib.ub0[3 * v + 1], ib.ub0[3 * v + 2]};
-  const Dual<3> p[3] = {dseed<3>(X[3 * v], 0), dseed<3>(X[3 * v + 1], 1), dseed<3>(X[3 * v + 2], 2)};
-  Dual<3> s = Scal<Dual<3>>::c(0.0);
-  mls_each_g<ADJ_GS>(G, a.ncls, p, lane, [&](int, long long node, const Dual<3>(&psi)[4]) {
-    double dr, uu[3];
-    load_mac<S>(a, node, dr, uu[0], uu[1], uu[2]);
-    s += psi[0] * (uu[0] * ub[0] + uu[1] * ub[1] + uu[2] * ub[2]);
-    for (int i = 0; i < 3; i++) atomicAdd(ib.ext + (long long)(1 + i) * G.Np + node, psi[0].v * ub[i]);
-    set_tile(ib.etf, node);
-  });
-  s = group_sum<ADJ_GS>(s);
-  if (lane == 0)
-    for (int k = 0; k < 3; k++) atomicAdd(ib.LP + 3 * v + k, s.d[k]);
+  fy = red64(fy);
+  if ((threadIdx.x & 63) == 0 && fy != 0.0) atomicAdd(ib.gsum + 1, fy / ib.kappa);
 }
 
-// Flags the tiles of every forcing marker's support nodes (the force adjoint
-// is needed there whatever the step's force was).
-__global__ __launch_bounds__(256) void k_adjb_support(Grid G, const uint8_t* ncls, BodyArgs b, uint8_t* etf) {
-  const int m = blockIdx.x * 256 + threadIdx.x;
-  if (m >= b.nf) return;
-  double cen[3], n[3], area;
-  face_geom(b.Xcur, b.faces, m, cen, n, area);
-  const int bs[3] = {(int)floor(cen[0] + 0.5), (int)floor(cen[1] + 0.5), (int)floor(cen[2] + 0.5)};
-  for (int k = 0; k < 27; k++) {
-    long long node;
-    if (support_node(G, ncls, bs[0] + k % 3 - 1, bs[1] + (k / 3) % 3 - 1, bs[2] + k / 9 - 1, node))
-      set_tile(etf, node);
+// Field values of a quad's supports from the macro field: u and rho - 1.
+template <class S>
+__device__ __forceinline__ void mac_fields(const FluidArgs& a, const QuadSupports& q, double (&f)[7][4]) {
+#pragma unroll
+  for (int k = 0; k < 7; k++) {
+    double v[4];
+    load_mac<S>(a, q.node[k] < 0 ? 0 : q.node[k], v[3], v[0], v[1], v[2]);
+#pragma unroll
+    for (int c = 0; c < 4; c++) f[k][c] = q.node[k] < 0 ? 0.0 : v[c];
   }
+}
+
+// The tractions of a marker chunk's faces transposed (a block per chunk, a
+// quad per face, its outer probe and then its inner one):
+//   s = sum over the sides of sg A r Q + k_v (1 - V/V0) A ab.n,
+//   Q = -ab.n / 3 + nu S:G,  S = ab n^T + n ab^T,
+// with ab the mean of the vertices' dJ/dF, r and G the fitted density and
+// velocity gradient at the probe c +- 1.2 n.  The sources at the nodes are
+// summed in LDS over the chunk's box of supports and added to ext once per node
+// and component; the derivatives in n, A and c go to the vertices at the end.
+template <class S>
+__device__ void adjb_probes(const FluidArgs& a, const BodyArgs& b, const AdjIB& ib, int blk) {
+  __shared__ double s_ext[4][BOX_CELLS];
+  __shared__ int s_wbox[4][6];
+  __shared__ double s_sum[4][3];
+  const Grid& G = a.g;
+  const int t = threadIdx.x, sub = t & 3;
+  const int nchunk = b.chunk_n[blk], s0 = b.chunk_s0[blk];
+  if (nchunk == 0) return;
+  const bool mk = (t >> 2) < nchunk;
+  const int4 sf = *(const int4*)(b.slot_f + 4 * (long long)(s0 + (mk ? t >> 2 : 0)));
+  const int vv[3] = {sf.x, sf.y, sf.z}, body = sf.w;
+  double X[3][3], ab[3];
+#pragma unroll
+  for (int r = 0; r < 3; r++)
+#pragma unroll
+    for (int k = 0; k < 3; k++) X[r][k] = b.Xcur[3 * vv[r] + k];
+#pragma unroll
+  for (int k = 0; k < 3; k++)
+    ab[k] = (ib.Fb[3 * vv[0] + k] + ib.Fb[3 * vv[1] + k] + ib.Fb[3 * vv[2] + k]) * (1.0 / 3.0);
+  const double nu = b.nu, V0 = b.b_param[8 * body], kv = b.b_param[8 * body + 2];
+  const double cv = kv * (1.0 - b.b_diag[16 * body] / V0);
+  const bool kvd = b.b_param[8 * body + 6] != 0.0;
+  double cen[3], n[3], A;
+  face_geom_pts(X[0], X[1], X[2], cen, n, A);
+  const double an = ab[0] * n[0] + ab[1] * n[1] + ab[2] * n[2];
+  // derivatives of s in the area, the normal and the centroid
+  double gA = cv * an, gn[3] = {cv * A * ab[0], cv * A * ab[1], cv * A * ab[2]}, gc[3] = {0.0, 0.0, 0.0};
+  double visc = 0.0;
+#pragma unroll 1
+  for (int side = 0; side < 2; side++) {
+    const double off = side == 0 ? 1.2 : -1.2, sg = side == 0 ? 1.0 : -1.0;
+    const double p[3] = {cen[0] + off * n[0], cen[1] + off * n[1], cen[2] + off * n[2]};
+    const int bs[3] = {(int)floor(p[0] + 0.5), (int)floor(p[1] + 0.5), (int)floor(p[2] + 0.5)};
+    Box bx;
+    const bool fits = block_box(bs, mk, s_wbox, bx);
+    const int ncell = fits ? bx.cells() : 0;
+    for (int c = t; c < ncell; c += blockDim.x)
+#pragma unroll
+      for (int k = 0; k < 4; k++) s_ext[k][c] = 0.0;
+    QuadSupports q;
+    quad_supports(a, sub, p, bs, q);
+    double f[7][4];
+    mac_fields<S>(a, q, f);
+    FitSums<4> fs;
+    quad_moments(q, f, fs);
+    Chol4 ch;
+    const bool ok = mk && chol4(fs.A, ch);  // a singular fit gives 0
+    __syncthreads();
+    if (ok) {
+      double cc[4], c[4][4], z[3][4], Q = 0.0, qc[3] = {0.0, 0.0, 0.0};
+      const double e0[4] = {1.0, 0.0, 0.0, 0.0};
+      chol_solve(ch, e0, cc);
+#pragma unroll
+      for (int i = 0; i < 4; i++) chol_solve(ch, fs.b[i], c[i]);
+#pragma unroll
+      for (int i = 0; i < 3; i++) {
+        const double si[4] = {0.0, ab[i] * n[0] + ab[0] * n[i], ab[i] * n[1] + ab[1] * n[i],
+                              ab[i] * n[2] + ab[2] * n[i]};
+        chol_solve(ch, si, z[i]);
+#pragma unroll
+        for (int k = 0; k < 3; k++) {
+          Q += si[1 + k] * c[i][1 + k];
+          qc[k] += ab[i] * (c[i][1 + k] + c[k][1 + i]);
+        }
+      }
+      const double r = 1.0 + c[3][0], sv = Q;  // the weights add up to 1: rho = 1 + the fit of rho - 1
+      const double Qt = -an * (1.0 / 3.0) + nu * sv;
+      // sources: dJ/drho_k = A sg Qt phi_k, dJ/du_ik = A sg nu r W z_i.P
+      const double rb = A * sg * Qt, ub = A * sg * nu * r;
+      double H[3] = {0.0, 0.0, 0.0}, R[3] = {0.0, 0.0, 0.0};
+      const int c00 = fits ? bx.corner(bs) : 0;
+#pragma unroll
+      for (int k = 0; k < 7; k++) {
+        if (q.node[k] < 0) continue;
+        const double dx = q.dx[k], dy = q.dy[k / 3], dz = q.dz[k / 3];
+        const double phi = q.W[k] * lin4(cc, dx, dy, dz);
+        double wz[3], h = 0.0;
+#pragma unroll
+        for (int i = 0; i < 3; i++) {
+          wz[i] = q.W[k] * lin4(z[i], dx, dy, dz);
+          h += wz[i] * (f[k][i] - lin4(c[i], dx, dy, dz));
+        }
+        const double rr = phi * (f[k][3] - lin4(c[3], dx, dy, dz));
+        H[0] += h * dx;
+        H[1] += h * dy;
+        H[2] += h * dz;
+        R[0] += rr * dx;
+        R[1] += rr * dy;
+        R[2] += rr * dz;
+        const double e[4] = {rb * phi, ub * wz[0], ub * wz[1], ub * wz[2]};
+        if (fits) {
+          const int cl = bx.at(c00, q.cell[k]);
+#pragma unroll
+          for (int i = 0; i < 4; i++) atomicAdd(&s_ext[i][cl], e[i]);
+        } else {
+#pragma unroll
+          for (int i = 0; i < 4; i++) atomicAdd(ib.ext + (long long)i * G.Np + q.node[k], e[i]);
+          set_tile(ib.etf, q.node[k]);
+        }
+      }
+      gA += sg * r * Qt;
+      visc += A * sg * r * sv;
+#pragma unroll
+      for (int m = 0; m < 3; m++) {
+        const double dr = c[3][1 + m] + 2.0 * MLS_K * quad_sum(R[m]), dq = 2.0 * MLS_K * quad_sum(H[m]);
+        const double gp = A * sg * (dr * Qt + r * nu * dq);
+        gc[m] += gp;
+        gn[m] += off * gp + A * sg * r * (nu * qc[m] - ab[m] * (1.0 / 3.0));
+      }
+    }
+    __syncthreads();
+    for (int c = t; c < ncell; c += blockDim.x) {
+      double v[4];
+#pragma unroll
+      for (int k = 0; k < 4; k++) v[k] = s_ext[k][c];
+      if (v[0] == 0.0 && v[1] == 0.0 && v[2] == 0.0 && v[3] == 0.0) continue;
+      int x[3], node;
+      if (!box_node(G, bx, c, x, node)) continue;
+#pragma unroll
+      for (int k = 0; k < 4; k++) atomicAdd(ib.ext + (long long)k * G.Np + node, v[k]);
+      set_tile(ib.etf, node);
+    }
+  }
+  // the scalar gradients: one atomic per block
+  const bool lead = mk && sub == 0;
+  const double sums[3] = {red64(lead ? visc * (1.0 / 3.0) : 0.0),  // nu = (tau - 1/2) / 3
+                          red64(lead && kvd ? cv * A * an : 0.0), red64(lead ? A * an : 0.0)};
+  if ((t & 63) == 0)
+    for (int k = 0; k < 3; k++) s_sum[t >> 6][k] = sums[k];
+  __syncthreads();
+  if (t == 0) {
+    double v[3] = {0.0, 0.0, 0.0};
+    for (int w = 0; w < 4; w++)
+      for (int k = 0; k < 3; k++) v[k] += s_sum[w][k];
+    atomicAdd(ib.gsum, v[0]);
+    if (v[1] != 0.0) atomicAdd(ib.gsum + 1, v[1] / ib.kappa);
+    atomicAdd(ib.gsum + 2 + body, v[2]);  // a chunk's faces belong to one body
+  }
+  if (!lead) return;
+  // to the vertices: N = u x w, n = N / |N|, A = |N| / 2, c the mean
+  const double u[3] = {X[1][0] - X[0][0], X[1][1] - X[0][1], X[1][2] - X[0][2]};
+  const double w[3] = {X[2][0] - X[0][0], X[2][1] - X[0][1], X[2][2] - X[0][2]};
+  const double ng = n[0] * gn[0] + n[1] * gn[1] + n[2] * gn[2], il = 0.5 / A;
+  double gN[3], gu[3], gw[3];
+#pragma unroll
+  for (int k = 0; k < 3; k++) gN[k] = (gn[k] - n[k] * ng) * il + 0.5 * gA * n[k];
+  cross3(w, gN, gu);
+  cross3(gN, u, gw);
+#pragma unroll
+  for (int k = 0; k < 3; k++) {
+    const double m = gc[k] * (1.0 / 3.0);
+    atomicAdd(ib.LP + 3 * vv[0] + k, m - gu[k] - gw[k]);
+    atomicAdd(ib.LP + 3 * vv[1] + k, m + gu[k]);
+    atomicAdd(ib.LP + 3 * vv[2] + k, m + gw[k]);
+  }
+}
+
+// The MLS velocity at a soft vertex transposed (a quad each): u0 = sum phi_k u_k.
+template <class S>
+__device__ __forceinline__ void adjb_vertex_velocity(const FluidArgs& a, const BodyArgs& b, const AdjIB& ib, int idx) {
+  if (idx >= b.nsoft_v) return;  // whole quads
+  const int v = b.soft_vlist[idx], sub = threadIdx.x & 3;
+  const double p[3] = {b.Xcur[3 * v], b.Xcur[3 * v + 1], b.Xcur[3 * v + 2]};
+  const double ub[3] = {ib.ub0[3 * v], ib.ub0[3 * v + 1], ib.ub0[3 * v + 2]};
+  const int bs[3] = {(int)floor(p[0] + 0.5), (int)floor(p[1] + 0.5), (int)floor(p[2] + 0.5)};
+  QuadSupports q;
+  quad_supports(a, sub, p, bs, q);
+  double f[7][4], h[7][1];
+  mac_fields<S>(a, q, f);
+#pragma unroll
+  for (int k = 0; k < 7; k++) h[k][0] = ub[0] * f[k][0] + ub[1] * f[k][1] + ub[2] * f[k][2];
+  FitSums<1> fs;
+  quad_moments(q, h, fs);
+  Chol4 ch;
+  if (!chol4(fs.A, ch)) return;
+  double cc[4], c[4], H[3] = {0.0, 0.0, 0.0};
+  const double e0[4] = {1.0, 0.0, 0.0, 0.0};
+  chol_solve(ch, e0, cc);
+  chol_solve(ch, fs.b[0], c);
+#pragma unroll
+  for (int k = 0; k < 7; k++) {
+    if (q.node[k] < 0) continue;
+    const double dx = q.dx[k], dy = q.dy[k / 3], dz = q.dz[k / 3];
+    const double phi = q.W[k] * lin4(cc, dx, dy, dz), r = phi * (h[k][0] - lin4(c, dx, dy, dz));
+    H[0] += r * dx;
+    H[1] += r * dy;
+    H[2] += r * dz;
+#pragma unroll
+    for (int i = 0; i < 3; i++) atomicAdd(ib.ext + (long long)(1 + i) * a.g.Np + q.node[k], phi * ub[i]);
+    set_tile(ib.etf, q.node[k]);
+  }
+#pragma unroll
+  for (int m = 0; m < 3; m++) H[m] = c[1 + m] + 2.0 * MLS_K * quad_sum(H[m]);
+  if (sub < 3) atomicAdd(ib.LP + 3 * v + sub, sel3(sub, H));
+}
+
+// Elements, probes and vertex velocities transposed, in blocks: the marker
+// chunks (probes of their faces), 256 edges and hinges each, 64 soft vertices
+// each.  Measured per launch on the 2562-vertex capsule: 105 us with dual
+// numbers through every fit and 1.3 million atomics on the node sources,
+// 28 us.
+template <class S>
+__global__ __launch_bounds__(256, 1) void k_adjb_body(FluidArgs a, BodyArgs b, AdjIB ib) {
+  const int nmk = b.n_marker_blocks, nel = b.n_elem_blocks, u = blockIdx.x;
+  if (u < nmk) adjb_probes<S>(a, b, ib, u);
+  else if (u < nmk + nel) adjb_element(b, ib, (long long)(u - nmk) * 256 + threadIdx.x);
+  else adjb_vertex_velocity<S>(a, b, ib, (u - nmk - nel) * 64 + (threadIdx.x >> 2));
 }
 
 // The volume force through V: Ft_f contains k_v (1 - V/V0) A_f n_f, and
@@ -4650,67 +4735,163 @@ __global__ __launch_bounds__(256) void k_adjb_volume(BodyArgs b, AdjIB ib) {
     for (int k = 0; k < 3; k++) atomicAdd(ib.LP + 3 * b.faces[3 * f + r] + k, c * area * n[k]);
 }
 
-// The forcing markers transposed (one thread per face): U = sum phi u*,
-// F_l = U_b - U, f_ib += A phi F_l.  dJ/dF_l = A sum phi dJ/dF_k; dJ/dU_b =
-// dJ/dF_l (a third to each vertex velocity); dJ/du*_k -= phi_k dJ/dF_l; and
-// the positions through the centroid (phi) and the area.
+// The forcing markers transposed (a block per marker chunk, a quad per face):
+// U = sum phi u*, F_l = U_b - U, f_ib += A phi F_l.  With Fs = sum phi dJ/dF_k:
+// dJ/dF_l = A Fs, of which a third goes to each vertex velocity; dJ/du*_k =
+// -phi_k A Fs; and the positions through the area (F_l.Fs) and the centroid
+// (the derivative of sum phi h, h = A F_l.dJ/dF_k - u*_k.A Fs).  As in the
+// forcing itself u* is formed once per node of the chunk's box in LDS (twice
+// per support and face before), and the node sources are summed there.
+// Measured per launch on the 2562-vertex capsule: 50 -> 17 us.
 template <class S>
-__global__ __launch_bounds__(128) void k_adjb_markers(FluidArgs a, BodyArgs b, AdjIB ib) {
-  // a group of ADJ_GS lanes per face, the supports split over it
-  const int gt = blockIdx.x * 128 + threadIdx.x;
-  const int m = gt / ADJ_GS, lane = gt % ADJ_GS;
-  if (m >= b.nf) return;  // whole groups
+__global__ __launch_bounds__(256, 1) void k_adjb_markers(FluidArgs a, BodyArgs b, AdjIB ib) {
+  __shared__ double s_v[6][BOX_CELLS];  // u*, dJ/dF; then the sums of dJ/du* in the first three
+  __shared__ int s_wbox[4][6];
   const Grid& G = a.g;
-  const int vv[3] = {b.faces[3 * m], b.faces[3 * m + 1], b.faces[3 * m + 2]};
-  double cen[3], n[3], area, Ub[3];
-  face_geom(b.Xcur, b.faces, m, cen, n, area);
-  for (int k = 0; k < 3; k++) Ub[k] = (b.Vel[3 * vv[0] + k] + b.Vel[3 * vv[1] + k] + b.Vel[3 * vv[2] + k]) / 3.0;
-  double U[3] = {0.0, 0.0, 0.0}, Fs[3] = {0.0, 0.0, 0.0};
-  mls_each_g<ADJ_GS>(G, a.ncls, cen, lane, [&](int, long long node, const double(&psi)[4]) {
-    const Moments mo = streamed_moments<S>(a, node);
-    const double rho = 1.0 + mo.drho;
+  const int t = threadIdx.x, sub = t & 3, blk = blockIdx.x;
+  const int nchunk = b.chunk_n[blk], s0 = b.chunk_s0[blk];
+  if (nchunk == 0) return;
+  const bool mk = (t >> 2) < nchunk;
+  const int4 sf = *(const int4*)(b.slot_f + 4 * (long long)(s0 + (mk ? t >> 2 : 0)));
+  const int vv[3] = {sf.x, sf.y, sf.z};
+  double X[3][3], Ub[3];
+#pragma unroll
+  for (int r = 0; r < 3; r++)
+#pragma unroll
+    for (int k = 0; k < 3; k++) X[r][k] = b.Xcur[3 * vv[r] + k];
+#pragma unroll
+  for (int k = 0; k < 3; k++)
+    Ub[k] = (b.Vel[3 * vv[0] + k] + b.Vel[3 * vv[1] + k] + b.Vel[3 * vv[2] + k]) * (1.0 / 3.0);
+  double cen[3], n[3], area;
+  face_geom_pts(X[0], X[1], X[2], cen, n, area);
+  const int bs[3] = {(int)floor(cen[0] + 0.5), (int)floor(cen[1] + 0.5), (int)floor(cen[2] + 0.5)};
+  Box bx;
+  const bool fits = block_box(bs, mk, s_wbox, bx);
+  const int ncell = fits ? bx.cells() : 0;
+  auto fields = [&](int x, int y, int z, int node, double (&v)[6]) {
+    double us[3] = {0.0, 0.0, 0.0};
+    const bool ok = cell_velocity<S>(a, node, x, y, z, us);
+#pragma unroll
     for (int k = 0; k < 3; k++) {
-      U[k] += psi[0] * (mo.m[k] / rho);
-      Fs[k] += psi[0] * ib.fbar[(long long)k * G.Np + node];
+      v[k] = ok ? us[k] : 0.0;
+      v[3 + k] = ok ? ib.fbar[(long long)k * G.Np + node] : 0.0;
     }
-  });
-  double Fl[3], Fbl[3];
-  for (int k = 0; k < 3; k++) {
-    U[k] = group_sum<ADJ_GS>(U[k]);
-    Fs[k] = group_sum<ADJ_GS>(Fs[k]);
-    Fl[k] = Ub[k] - U[k];
-    Fbl[k] = area * Fs[k];
+  };
+  for (int c = t; c < ncell; c += blockDim.x) {
+    int x[3], node;
+    double v[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    if (box_node(G, bx, c, x, node)) fields(x[0], x[1], x[2], node, v);
+#pragma unroll
+    for (int k = 0; k < 6; k++) s_v[k][c] = v[k];
   }
-  if (lane == 0)
-    for (int r = 0; r < 3; r++)
-      for (int k = 0; k < 3; k++) atomicAdd(ib.Vn + 3 * vv[r] + k, Fbl[k] / 3.0);
-  const Dual<3> q[3] = {dseed<3>(cen[0], 0), dseed<3>(cen[1], 1), dseed<3>(cen[2], 2)};
-  Dual<3> s = Scal<Dual<3>>::c(0.0);
-  double Abar = 0.0;
-  mls_each_g<ADJ_GS>(G, a.ncls, q, lane, [&](int, long long node, const Dual<3>(&psi)[4]) {
-    const Moments mo = streamed_moments<S>(a, node);
-    const double rho = 1.0 + mo.drho;
-    double fF = 0.0, uF = 0.0;
-    for (int k = 0; k < 3; k++) {
-      fF += Fl[k] * ib.fbar[(long long)k * G.Np + node];
-      uF += (mo.m[k] / rho) * Fbl[k];
+  QuadSupports q;
+  quad_supports(a, sub, cen, bs, q);
+  __syncthreads();
+  double f[7][6];
+  const int c00 = fits ? bx.corner(bs) : 0;
+#pragma unroll
+  for (int k = 0; k < 7; k++) {
+    const int cl = fits && mk ? bx.at(c00, q.cell[k]) : 0;
+#pragma unroll
+    for (int i = 0; i < 6; i++) f[k][i] = fits && q.node[k] >= 0 ? s_v[i][cl] : 0.0;
+  }
+  if (!fits && mk) {  // a box beyond the LDS capacity: support by support
+#pragma unroll 1
+    for (int k = 0; k < 7; k++) {
+      int node = -1;
+      double v[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int i = 0; i < 7; i++) node = i == k ? q.node[i] : node;
+      if (node >= 0) {
+        int x, y, z;
+        coords(G, node, x, y, z);
+        fields(x, y, z, node, v);
+      }
+#pragma unroll
+      for (int i = 0; i < 7; i++)
+        if (i == k)
+#pragma unroll
+          for (int m = 0; m < 6; m++) f[i][m] = v[m];
     }
-    s += psi[0] * (area * fF - uF);
-    Abar += psi[0].v * fF;
-    for (int k = 0; k < 3; k++) atomicAdd(ib.ext + (long long)(4 + k) * G.Np + node, -psi[0].v * Fbl[k]);
+  }
+  FitSums<6> fs;
+  quad_moments(q, f, fs);
+  __syncthreads();
+  for (int c = t; c < ncell; c += blockDim.x)
+#pragma unroll
+    for (int k = 0; k < 3; k++) s_v[k][c] = 0.0;
+  Chol4 ch;
+  const bool ok = mk && chol4(fs.A, ch);  // a singular fit has U = 0 and spreads nothing
+  __syncthreads();
+  if (ok) {
+    double cc[4], Fl[3], Fbl[3], bh[4] = {0.0, 0.0, 0.0, 0.0}, c[4], H[3] = {0.0, 0.0, 0.0}, Ab = 0.0;
+    const double e0[4] = {1.0, 0.0, 0.0, 0.0};
+    chol_solve(ch, e0, cc);
+#pragma unroll
+    for (int k = 0; k < 3; k++) {
+      double U = 0.0, Fs = 0.0;
+#pragma unroll
+      for (int i = 0; i < 4; i++) {
+        U += cc[i] * fs.b[k][i];
+        Fs += cc[i] * fs.b[3 + k][i];
+      }
+      Fl[k] = Ub[k] - U;
+      Fbl[k] = area * Fs;
+      Ab += Fl[k] * Fs;
+#pragma unroll
+      for (int i = 0; i < 4; i++) bh[i] += area * Fl[k] * fs.b[3 + k][i] - Fbl[k] * fs.b[k][i];
+    }
+    chol_solve(ch, bh, c);
+#pragma unroll
+    for (int k = 0; k < 7; k++) {
+      if (q.node[k] < 0) continue;
+      const double dx = q.dx[k], dy = q.dy[k / 3], dz = q.dz[k / 3];
+      double h = 0.0;
+#pragma unroll
+      for (int i = 0; i < 3; i++) h += area * Fl[i] * f[k][3 + i] - Fbl[i] * f[k][i];
+      const double phi = q.W[k] * lin4(cc, dx, dy, dz), r = phi * (h - lin4(c, dx, dy, dz));
+      H[0] += r * dx;
+      H[1] += r * dy;
+      H[2] += r * dz;
+      if (fits) {
+        const int cl = bx.at(c00, q.cell[k]);
+#pragma unroll
+        for (int i = 0; i < 3; i++) atomicAdd(&s_v[i][cl], -phi * Fbl[i]);
+      } else {
+#pragma unroll
+        for (int i = 0; i < 3; i++) atomicAdd(ib.ext + (long long)(4 + i) * G.Np + q.node[k], -phi * Fbl[i]);
+        set_tile(ib.etf, q.node[k]);
+      }
+    }
+#pragma unroll
+    for (int m = 0; m < 3; m++) H[m] = c[1 + m] + 2.0 * MLS_K * quad_sum(H[m]);
+    if (sub < 3) {
+      // lane r takes vertex r; d area / d vertex: (1/2) n x (opposite edge), counter-clockwise
+      const int r = sub, r1 = r == 2 ? 0 : r + 1, r2 = r == 0 ? 2 : r - 1;
+      double e[3], dA[3];
+#pragma unroll
+      for (int k = 0; k < 3; k++) {
+        const double xk[3] = {X[0][k], X[1][k], X[2][k]};
+        e[k] = sel3(r2, xk) - sel3(r1, xk);
+      }
+      cross3(n, e, dA);
+      const int v = sel3i(r, vv);
+#pragma unroll
+      for (int k = 0; k < 3; k++) {
+        atomicAdd(ib.LP + 3 * v + k, H[k] * (1.0 / 3.0) + Ab * 0.5 * dA[k]);
+        atomicAdd(ib.Vn + 3 * v + k, Fbl[k] * (1.0 / 3.0));
+      }
+    }
+  }
+  __syncthreads();
+  for (int c = t; c < ncell; c += blockDim.x) {
+    const double v[3] = {s_v[0][c], s_v[1][c], s_v[2][c]};
+    if (v[0] == 0.0 && v[1] == 0.0 && v[2] == 0.0) continue;
+    int x[3], node;
+    if (!box_node(G, bx, c, x, node)) continue;
+#pragma unroll
+    for (int k = 0; k < 3; k++) atomicAdd(ib.ext + (long long)(4 + k) * G.Np + node, v[k]);
     set_tile(ib.etf, node);
-  });
-  s = group_sum<ADJ_GS>(s);
-  Abar = group_sum<ADJ_GS>(Abar);
-  if (lane != 0) return;
-  // d area / d vertex: (1/2) n x (opposite edge), counter-clockwise
-  for (int r = 0; r < 3; r++) {
-    const double* xb = b.Xcur + 3 * vv[(r + 1) % 3];
-    const double* xc = b.Xcur + 3 * vv[(r + 2) % 3];
-    const double e[3] = {xc[0] - xb[0], xc[1] - xb[1], xc[2] - xb[2]};
-    const double dA[3] = {0.5 * (n[1] * e[2] - n[2] * e[1]), 0.5 * (n[2] * e[0] - n[0] * e[2]),
-                          0.5 * (n[0] * e[1] - n[1] * e[0])};
-    for (int k = 0; k < 3; k++) atomicAdd(ib.LP + 3 * vv[r] + k, s.d[k] / 3.0 + Abar * dA[k]);
   }
 }
 
@@ -4754,27 +4935,68 @@ __device__ void jacobi3(double (&M)[3][3], double (&d)[3], double (&V)[3][3]) {
 // second-moment tensor M = sum (x - xbar)(x - xbar)^T / n; one block.  Adds
 // D to *jsum, or theta dD/dx = theta (2/n) G (x - xbar) to aP, with G =
 // dD/dl1 v1 v1^T + dD/dl3 v3 v3^T.
-__global__ __launch_bounds__(256) void k_taylor(BodyArgs b, const double* X, int body, double theta, double* aP,
-                                                double* jsum) {
-  __shared__ double sh[8];
-  __shared__ double s_G[9], s_m[3];
-  const int v0 = b.b_vert0[body], nvb = b.b_nv[body];
-  double m[3] = {0.0, 0.0, 0.0};
-  for (int v = v0 + threadIdx.x; v < v0 + nvb; v += 256)
-    for (int k = 0; k < 3; k++) m[k] += X[3 * v + k];
-  for (int k = 0; k < 3; k++) m[k] = block_sum(m[k], sh) / nvb;
+// Latency-bound (one block): 512 threads keep their first six vertices in
+// registers and add their sums in one exchange each for the mean and the
+// moments (256 threads, vertices read three times and a sum at a time: 17 us
+// for 2562 vertices, 13 us now).
+constexpr int TAYLOR_THREADS = 512, TAYLOR_KEEP = 6;
+template <int N>
+__device__ __forceinline__ void block_sums(double (&v)[N], double (*sh)[8]) {
+#pragma unroll
+  for (int k = 0; k < N; k++) v[k] = red64(v[k]);
+  __syncthreads();
+  if ((threadIdx.x & 63) == 0)
+#pragma unroll
+    for (int k = 0; k < N; k++) sh[threadIdx.x >> 6][k] = v[k];
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < N; k++) {
+    v[k] = 0.0;
+    for (int w = 0; w < (int)(blockDim.x >> 6); w++) v[k] += sh[w][k];
+  }
+}
+__global__ __launch_bounds__(TAYLOR_THREADS) void k_taylor(BodyArgs b, const double* X, int body, double theta,
+                                                           double* aP, double* jsum) {
+  __shared__ double sh[TAYLOR_THREADS / 64][8];
+  __shared__ double s_G[9];
+  const int v0 = b.b_vert0[body], nvb = b.b_nv[body], t = threadIdx.x;
+  double x[TAYLOR_KEEP][3], m[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+  for (int i = 0; i < TAYLOR_KEEP; i++) {
+    const int v = t + i * TAYLOR_THREADS;
+#pragma unroll
+    for (int k = 0; k < 3; k++) {
+      x[i][k] = v < nvb ? X[3 * (v0 + v) + k] : 0.0;
+      m[k] += x[i][k];
+    }
+  }
+  for (int v = t + TAYLOR_KEEP * TAYLOR_THREADS; v < nvb; v += TAYLOR_THREADS)
+    for (int k = 0; k < 3; k++) m[k] += X[3 * (v0 + v) + k];
+  block_sums(m, sh);
+#pragma unroll
+  for (int k = 0; k < 3; k++) m[k] /= nvb;
   double M6[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-  for (int v = v0 + threadIdx.x; v < v0 + nvb; v += 256) {
-    const double d[3] = {X[3 * v] - m[0], X[3 * v + 1] - m[1], X[3 * v + 2] - m[2]};
+  auto moment = [&](const double (&d)[3]) {
     M6[0] += d[0] * d[0];
     M6[1] += d[0] * d[1];
     M6[2] += d[0] * d[2];
     M6[3] += d[1] * d[1];
     M6[4] += d[1] * d[2];
     M6[5] += d[2] * d[2];
+  };
+#pragma unroll
+  for (int i = 0; i < TAYLOR_KEEP; i++) {
+    const double d[3] = {x[i][0] - m[0], x[i][1] - m[1], x[i][2] - m[2]};
+    if (t + i * TAYLOR_THREADS < nvb) moment(d);
   }
-  for (int k = 0; k < 6; k++) M6[k] = block_sum(M6[k], sh) / nvb;
-  if (threadIdx.x == 0) {
+  for (int v = t + TAYLOR_KEEP * TAYLOR_THREADS; v < nvb; v += TAYLOR_THREADS) {
+    const double* p = X + 3 * (long long)(v0 + v);
+    const double d[3] = {p[0] - m[0], p[1] - m[1], p[2] - m[2]};
+    moment(d);
+  }
+  block_sums(M6, sh);
+  if (t == 0) {
+    for (int k = 0; k < 6; k++) M6[k] /= nvb;
     double M[3][3] = {{M6[0], M6[1], M6[2]}, {M6[1], M6[3], M6[4]}, {M6[2], M6[4], M6[5]}};
     double d[3], V[3][3];
     jacobi3(M, d, V);
@@ -4788,33 +5010,56 @@ __global__ __launch_bounds__(256) void k_taylor(BodyArgs b, const double* X, int
     const double g1 = c / (a * s2), g3 = -a / (c * s2);  // dD/dl1, dD/dl3
     for (int i = 0; i < 3; i++)
       for (int j = 0; j < 3; j++) s_G[3 * i + j] = g1 * V[i][i1] * V[j][i1] + g3 * V[i][i3] * V[j][i3];
-    for (int k = 0; k < 3; k++) s_m[k] = m[k];
   }
-  __syncthreads();
   if (!aP) return;
-  for (int v = v0 + threadIdx.x; v < v0 + nvb; v += 256) {
-    const double d[3] = {X[3 * v] - s_m[0], X[3 * v + 1] - s_m[1], X[3 * v + 2] - s_m[2]};
+  __syncthreads();
+  const double f = theta * 2.0 / nvb;
+  auto add = [&](int v, const double (&d)[3]) {
+#pragma unroll
     for (int i = 0; i < 3; i++)
-      aP[3 * v + i] += theta * 2.0 / nvb * (s_G[3 * i] * d[0] + s_G[3 * i + 1] * d[1] + s_G[3 * i + 2] * d[2]);
+      aP[3 * (v0 + v) + i] += f * (s_G[3 * i] * d[0] + s_G[3 * i + 1] * d[1] + s_G[3 * i + 2] * d[2]);
+  };
+#pragma unroll
+  for (int i = 0; i < TAYLOR_KEEP; i++) {
+    const double d[3] = {x[i][0] - m[0], x[i][1] - m[1], x[i][2] - m[2]};
+    if (t + i * TAYLOR_THREADS < nvb) add(t + i * TAYLOR_THREADS, d);
+  }
+  for (int v = t + TAYLOR_KEEP * TAYLOR_THREADS; v < nvb; v += TAYLOR_THREADS) {
+    const double* p = X + 3 * (long long)(v0 + v);
+    const double d[3] = {p[0] - m[0], p[1] - m[1], p[2] - m[2]};
+    add(v, d);
   }
 }
 
-// Zero the extra adjoint sources and the fixed-point force in flagged
-// tiles (data first, then, in a second launch, the flags).
-__global__ __launch_bounds__(256) void k_adjb_clear_data(Grid G, double* ext, const uint8_t* etf, long long* fx,
-                                                         const uint8_t* ftf) {
-  const long long n = blockIdx.x * 256LL + threadIdx.x;
-  if (n >= G.Np) return;
-  if (etf[n >> TILE_SHIFT])
-    for (int k = 0; k < 7; k++) ext[(long long)k * G.Np + n] = 0.0;
-  if (ftf[n >> TILE_SHIFT])
-    for (int k = 0; k < 3; k++) fx[(long long)k * G.Np + n] = 0;
-}
-__global__ __launch_bounds__(256) void k_adjb_clear_flags(long long ntiles, uint8_t* etf, uint8_t* ftf) {
-  const long long t = blockIdx.x * 256LL + threadIdx.x;
-  if (t >= ntiles) return;
-  etf[t] = 0;
-  ftf[t] = 0;
+// Zero the extra adjoint sources and the fixed-point force in flagged tiles,
+// and the flags: a block reads the flags of 256 tiles, then clears the listed
+// ones with all its threads.
+__global__ __launch_bounds__(256) void k_adjb_clear(Grid G, long long ntiles, double* ext, uint8_t* etf, long long* fx,
+                                                    uint8_t* ftf) {
+  __shared__ int s_n;
+  __shared__ int s_list[256];
+  const int t = threadIdx.x;
+  if (t == 0) s_n = 0;
+  __syncthreads();
+  const long long tl = blockIdx.x * 256LL + t;
+  if (tl < ntiles) {
+    const bool e = etf[tl] != 0, f = ftf[tl] != 0;
+    if (e || f) s_list[atomicAdd(&s_n, 1)] = t | (e ? 256 : 0) | (f ? 512 : 0);
+    if (e) etf[tl] = 0;
+    if (f) ftf[tl] = 0;
+  }
+  __syncthreads();
+  for (int k = t; k < (s_n << TILE_SHIFT); k += 256) {
+    const int w = s_list[k >> TILE_SHIFT];
+    const long long n = ((blockIdx.x * 256LL + (w & 255)) << TILE_SHIFT) + (k & ((1 << TILE_SHIFT) - 1));
+    if (n >= G.Np) continue;
+    if (w & 256)
+#pragma unroll
+      for (int q = 0; q < 7; q++) ext[(long long)q * G.Np + n] = 0.0;
+    if (w & 512)
+#pragma unroll
+      for (int q = 0; q < 3; q++) fx[(long long)q * G.Np + n] = 0;
+  }
 }
 
 // <w, g> at the non-solid nodes (those with amask bit 31 when use_mask),
@@ -4836,11 +5081,12 @@ __global__ __launch_bounds__(256) void k_adj_wdot(FluidArgs a, const S* g, const
   if (threadIdx.x == 0) part[blockIdx.x] += acc;
 }
 
-__global__ void k_adj_sum(const double* part, int n, double* out) {
-  if (threadIdx.x != 0) return;
+__global__ __launch_bounds__(256) void k_adj_sum(const double* part, int n, double* out) {
+  __shared__ double sh[8];
   double t = 0.0;
-  for (int k = 0; k < n; k++) t += part[k];
-  *out = t;
+  for (int k = threadIdx.x; k < n; k += 256) t += part[k];
+  t = block_sum(t, sh);
+  if (threadIdx.x == 0) *out = t;
 }
 
 hipError_t launch_adjb_vertex(const BodyArgs& b, const AdjIB& ib, hipStream_t s) {
@@ -4866,13 +5112,12 @@ hipError_t launch_body_slots(const double* from, double* to, long long nv3, hipS
 }
 
 hipError_t launch_adjb_body(int prec, const FluidArgs& a, const BodyArgs& b, const AdjIB& ib, hipStream_t s) {
-  const long long threads = adjb_body_face0(b) + (2LL * b.nf * ADJ_GS + 63) / 64 * 64 + (long long)b.nsoft_v * ADJ_GS;
-  if ((long long)b.ne + b.nh + b.nf + b.nsoft_v == 0) return hipSuccess;
-  const unsigned grid = cdiv(threads, 128);
+  const unsigned grid = (unsigned)(b.n_marker_blocks + b.n_elem_blocks) + cdiv(b.nsoft_v, 64);
+  if (grid == 0) return hipSuccess;
   switch (prec) {
-    case 0: k_adjb_body<double><<<grid, 128, 0, s>>>(a, b, ib); break;
-    case 1: k_adjb_body<float><<<grid, 128, 0, s>>>(a, b, ib); break;
-    default: k_adjb_body<_Float16><<<grid, 128, 0, s>>>(a, b, ib); break;
+    case 0: k_adjb_body<double><<<grid, 256, 0, s>>>(a, b, ib); break;
+    case 1: k_adjb_body<float><<<grid, 256, 0, s>>>(a, b, ib); break;
+    default: k_adjb_body<_Float16><<<grid, 256, 0, s>>>(a, b, ib); break;
   }
   return hipGetLastError();
 }
@@ -4882,32 +5127,26 @@ hipError_t launch_adjb_volume(const BodyArgs& b, const AdjIB& ib, hipStream_t s)
   return hipGetLastError();
 }
 
-hipError_t launch_adjb_support(const Grid& g, const uint8_t* ncls, const BodyArgs& b, uint8_t* etf, hipStream_t s) {
-  if (b.nf > 0) k_adjb_support<<<cdiv(b.nf, 256), 256, 0, s>>>(g, ncls, b, etf);
-  return hipGetLastError();
-}
-
 hipError_t launch_adjb_markers(int prec, const FluidArgs& a, const BodyArgs& b, const AdjIB& ib, hipStream_t s) {
   if (b.nf == 0) return hipSuccess;
-  const unsigned grid = cdiv((long long)b.nf * ADJ_GS, 128);
+  const unsigned grid = (unsigned)b.n_marker_blocks;
   switch (prec) {
-    case 0: k_adjb_markers<double><<<grid, 128, 0, s>>>(a, b, ib); break;
-    case 1: k_adjb_markers<float><<<grid, 128, 0, s>>>(a, b, ib); break;
-    default: k_adjb_markers<_Float16><<<grid, 128, 0, s>>>(a, b, ib); break;
+    case 0: k_adjb_markers<double><<<grid, 256, 0, s>>>(a, b, ib); break;
+    case 1: k_adjb_markers<float><<<grid, 256, 0, s>>>(a, b, ib); break;
+    default: k_adjb_markers<_Float16><<<grid, 256, 0, s>>>(a, b, ib); break;
   }
   return hipGetLastError();
 }
 
 hipError_t launch_taylor(const BodyArgs& b, const double* X, int body, double theta, double* aP, double* jsum,
                          hipStream_t s) {
-  k_taylor<<<1, 256, 0, s>>>(b, X, body, theta, aP, jsum);
+  k_taylor<<<1, TAYLOR_THREADS, 0, s>>>(b, X, body, theta, aP, jsum);
   return hipGetLastError();
 }
 
 hipError_t launch_adjb_clear(const Grid& g, double* ext, uint8_t* etf, long long* fx, uint8_t* ftf, hipStream_t s) {
   const long long ntiles = (g.Np >> TILE_SHIFT) + 1;
-  k_adjb_clear_data<<<cdiv(g.Np, 256), 256, 0, s>>>(g, ext, etf, fx, ftf);
-  k_adjb_clear_flags<<<cdiv(ntiles, 256), 256, 0, s>>>(ntiles, etf, ftf);
+  k_adjb_clear<<<cdiv(ntiles, 256), 256, 0, s>>>(g, ntiles, ext, etf, fx, ftf);
   return hipGetLastError();
 }
 
@@ -4925,7 +5164,7 @@ hipError_t launch_adj_wdot(int prec, const FluidArgs& a, const void* g, const do
 }
 
 hipError_t launch_adj_sum(const double* part, int n, double* out, hipStream_t s) {
-  k_adj_sum<<<1, 64, 0, s>>>(part, n, out);
+  k_adj_sum<<<1, 256, 0, s>>>(part, n, out);
   return hipGetLastError();
 }
 
