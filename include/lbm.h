@@ -246,7 +246,9 @@ lbm_status ib_spread_noalloc(lbm_ctx *ctx, int64_t n, const double *d_pts, const
  * fields and ceil(n/K) + max(K, 2) states of 19 x plane values, plus K x 19
  * doubles per boundary record; with a body, 16 FP64 [Np] fields
  * and 9 nv doubles per checkpoint and per step of a segment;
- * allocated and freed by the call; LBM_E_NOMEM if it does not fit).  The
+ * LBM_E_NOMEM if it does not fit; up to 4 GiB of it are kept, once per
+ * device, for the next call on any context there, and freed with the device's
+ * last context or when an allocation of this library needs the room).  The
  * context's state and step count are not changed.  Contexts with rigid or
  * fixed bodies, or with more than one body (the repulsion), give
  * LBM_E_UNSUPPORTED; a trajectory on which a capsule is damaged or the flow

@@ -11,6 +11,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <map>
+#include <mutex>
 #include <string>
 #include <utility>
 #include <vector>
@@ -44,6 +45,88 @@ struct HostBody {
 
 }  // namespace
 
+namespace {
+// The sweep's device memory: one allocation, carved in 256-byte aligned pieces.
+// Mapping gigabytes costs more than a short sweep (about 55 ms for 2.5 GB
+// against 9 ms for 20 steps with a capsule), so the last arena of up to
+// ARENA_KEEP bytes is kept, one per device, for the next sweep of any context
+// there: a sweep takes it out of its slot and nobody else sees it until the
+// sweep, its stream waited for, puts it back.  It is freed with the device's
+// last context, for a larger one, and whenever an allocation of this library
+// fails.
+constexpr size_t ARENA_KEEP = (size_t)4 << 30;
+struct ArenaSlot {
+  char* base = nullptr;
+  size_t bytes = 0;
+  int contexts = 0;
+};
+std::mutex arena_mu;
+std::map<int, ArenaSlot> arena_slots;
+
+void arena_drop(int device) {  // (hipFree waits for the device)
+  char* p = nullptr;
+  {
+    std::lock_guard<std::mutex> lock(arena_mu);
+    ArenaSlot& sl = arena_slots[device];
+    std::swap(p, sl.base);
+    sl.bytes = 0;
+  }
+  if (p) (void)hipFree(p);
+}
+void arena_contexts(int device, int d) {
+  bool last = false;
+  {
+    std::lock_guard<std::mutex> lock(arena_mu);
+    last = (arena_slots[device].contexts += d) == 0;
+  }
+  if (last) arena_drop(device);
+}
+
+struct DevArena {
+  char* base = nullptr;
+  size_t bytes = 0;
+  int device = 0;
+  bool idle = false;  // the work that used it has completed
+  bool take(int dev, size_t n) {
+    device = dev;
+    char* small = nullptr;
+    {
+      std::lock_guard<std::mutex> lock(arena_mu);
+      ArenaSlot& sl = arena_slots[dev];
+      if (sl.bytes >= n) {
+        base = sl.base;
+        bytes = sl.bytes;
+      } else {
+        small = sl.base;
+      }
+      sl.base = nullptr;
+      sl.bytes = 0;
+    }
+    if (small) (void)hipFree(small);
+    if (base) return true;
+    if (hipMalloc(&base, n) != hipSuccess) {
+      (void)hipGetLastError();
+      base = nullptr;
+      return false;
+    }
+    bytes = n;
+    return true;
+  }
+  ~DevArena() {
+    if (!base) return;
+    if (idle && bytes <= ARENA_KEEP) {
+      std::lock_guard<std::mutex> lock(arena_mu);
+      ArenaSlot& sl = arena_slots[device];
+      if (sl.bytes < bytes) {
+        std::swap(sl.base, base);
+        std::swap(sl.bytes, bytes);
+      }
+    }
+    if (base) (void)hipFree(base);
+  }
+};
+}  // namespace
+
 struct lbm_ctx {
   int device = 0;                  // HIP device the context was created on
   hipStream_t stream = nullptr;
@@ -52,6 +135,7 @@ struct lbm_ctx {
   hipEvent_t ev_fork = nullptr, ev_join = nullptr;
   std::string err;
   bool broken = false;
+  bool counted = false;            // among its device's contexts (the adjoint's kept arena)
   Grid g{};
   int prec = 0;
   size_t ssize = 8;
@@ -132,10 +216,20 @@ static lbm_status fail(lbm_ctx* ctx, lbm_status st, const std::string& msg) {
   return st;
 }
 
+// Device memory; if there is none, the adjoint's kept arena goes first.
+static hipError_t dev_malloc(void** p, size_t bytes) {
+  hipError_t e = hipMalloc(p, bytes);
+  if (e != hipErrorOutOfMemory) return e;
+  (void)hipGetLastError();
+  int device = 0;
+  if (hipGetDevice(&device) == hipSuccess) arena_drop(device);
+  return hipMalloc(p, bytes);
+}
+
 template <class T>
 static hipError_t dalloc(T** p, size_t n) {
   if (n == 0) n = 1;
-  return hipMalloc((void**)p, n * sizeof(T));
+  return dev_malloc((void**)p, n * sizeof(T));
 }
 
 template <class T>
@@ -440,7 +534,7 @@ extern "C" lbm_status lbm_create(const lbm_desc* d, void* hip_stream, lbm_ctx** 
   CHK(hipEventCreateWithFlags(&ctx->ev_join, hipEventDisableTiming));
   const size_t fbytes = ((size_t)19 * G.plane + 2 * (size_t)G.guard) * ctx->ssize;
   for (int p = 0; p < 2; p++) {
-    CHK(hipMalloc(&ctx->f_alloc[p], fbytes));
+    CHK(dev_malloc((void**)&ctx->f_alloc[p], fbytes));
     CHK(hipMemset(ctx->f_alloc[p], 0, fbytes));
     ctx->f[p] = (char*)ctx->f_alloc[p] + (size_t)G.guard * ctx->ssize;
   }
@@ -496,22 +590,24 @@ extern "C" lbm_status lbm_create(const lbm_desc* d, void* hip_stream, lbm_ctx** 
   CHK(upload(&ctx->lk_node, ln));
   CHK(upload(&ctx->lk_w, lw));
   CHK(upload(&ctx->tile_list, tiles));
-  CHK(hipMalloc(&ctx->flags, sizeof(DevFlags) + 64));
+  CHK(dev_malloc((void**)&ctx->flags, sizeof(DevFlags) + 64));
   CHK(hipMemset(ctx->flags, 0, sizeof(DevFlags) + 64));
   // initial populations: equilibrium of the given fields
   double *drho = nullptr, *du = nullptr;
   if (d->init_rho) {
-    CHK(hipMalloc(&drho, N * sizeof(double)));
+    CHK(dev_malloc((void**)&drho, N * sizeof(double)));
     CHK(hipMemcpy(drho, d->init_rho, N * sizeof(double), hipMemcpyHostToDevice));
   }
   if (d->init_u) {
-    CHK(hipMalloc(&du, 3 * N * sizeof(double)));
+    CHK(dev_malloc((void**)&du, 3 * N * sizeof(double)));
     CHK(hipMemcpy(du, d->init_u, 3 * N * sizeof(double), hipMemcpyHostToDevice));
   }
   CHK(launch_init(ctx->prec, G, ctx->f[0], ctx->ncls, drho, du, ctx->cap));
   CHK(hipStreamSynchronize(ctx->cap));
   if (drho) CHK(hipFree(drho));
   if (du) CHK(hipFree(du));
+  arena_contexts(ctx->device, 1);
+  ctx->counted = true;
   *out = ctx;
   return LBM_OK;
 }
@@ -531,6 +627,7 @@ extern "C" lbm_status lbm_destroy(lbm_ctx* ctx) {
   if (ctx->side) (void)hipStreamDestroy(ctx->side);
   if (ctx->ev_fork) (void)hipEventDestroy(ctx->ev_fork);
   if (ctx->ev_join) (void)hipEventDestroy(ctx->ev_join);
+  if (ctx->counted) arena_contexts(ctx->device, -1);
   delete ctx;
   return LBM_OK;
 }
@@ -875,13 +972,13 @@ static lbm_status build_body_arrays(lbm_ctx* ctx, int cur, const std::vector<dou
   if (!ctx->fx[0]) {
     const size_t fxb = 3 * (size_t)ctx->g.Np * sizeof(long long);
     for (int p = 0; p < 2; p++) {
-      CHK(hipMalloc(&ctx->fx[p], fxb));
+      CHK(dev_malloc((void**)&ctx->fx[p], fxb));
       CHK(hipMemset(ctx->fx[p], 0, fxb));
-      CHK(hipMalloc(&ctx->tf[p], ctx->ntiles));
+      CHK(dev_malloc((void**)&ctx->tf[p], ctx->ntiles));
       CHK(hipMemset(ctx->tf[p], 0, ctx->ntiles));
     }
     const size_t macb = 4 * (size_t)ctx->g.Np * (ctx->prec == 0 ? sizeof(double) : sizeof(float));
-    CHK(hipMalloc(&ctx->mac, macb));
+    CHK(dev_malloc((void**)&ctx->mac, macb));
     CHK(hipMemset(ctx->mac, 0, macb));
     CHK(launch_mac_solid(ctx->prec, ctx->g, ctx->mac, ctx->ncls, ctx->stream));
   }
@@ -1407,12 +1504,12 @@ static lbm_status batch_build_tables(lbm_batch* b) {
   if (b->maps) CHKB(hipFree(b->maps));
   b->items = nullptr;
   b->maps = nullptr;
-  CHKB(hipMalloc(&b->items, sizeof(BatchItem) * items.size()));
+  CHKB(dev_malloc((void**)&b->items, sizeof(BatchItem) * items.size()));
   CHKB(hipMemcpy(b->items, items.data(), sizeof(BatchItem) * items.size(), hipMemcpyHostToDevice));
   std::vector<int2> m;
   const std::vector<int2>* parts[6] = {&ib, &all, &rec, &bulk, &mls, &body};
   for (auto* v : parts) m.insert(m.end(), v->begin(), v->end());
-  CHKB(hipMalloc(&b->maps, sizeof(int2) * std::max<size_t>(m.size(), 1)));
+  CHKB(dev_malloc((void**)&b->maps, sizeof(int2) * std::max<size_t>(m.size(), 1)));
   if (!m.empty()) CHKB(hipMemcpy(b->maps, m.data(), sizeof(int2) * m.size(), hipMemcpyHostToDevice));
   int2* base = b->maps;
   b->m_ib = base;   base += ib.size();
@@ -1686,7 +1783,7 @@ extern "C" lbm_status lbm_batch_time_fluid(lbm_batch* b, int32_t reps, double* a
 extern "C" lbm_status lbm_diagnostics(lbm_ctx* ctx, double* out) {
   if (!ctx || !out) return LBM_E_INVAL;
   if (ctx->broken) return LBM_E_STATE;
-  if (!ctx->gdiag) CHK(hipMalloc(&ctx->gdiag, sizeof(double) * (5 * 1024 + 8)));
+  if (!ctx->gdiag) CHK(dev_malloc((void**)&ctx->gdiag, sizeof(double) * (5 * 1024 + 8)));
   // the bodies' volume, area and stretch of the current positions
   if (ctx->nf > 0)
     CHK(launch_check(ctx->bargs[0], ctx->X[0], ctx->X[1], ctx->flags, counter(ctx, 3), ctx->stream));
@@ -1771,9 +1868,9 @@ extern "C" lbm_status ib_spread(lbm_ctx* ctx, int64_t n, const double* d_pts, co
   if (ctx->broken) return LBM_E_STATE;
   if (!ctx->fx_api) {
     const size_t b = 3 * (size_t)ctx->g.Np * sizeof(long long);
-    CHK(hipMalloc(&ctx->fx_api, b));
+    CHK(dev_malloc((void**)&ctx->fx_api, b));
     CHK(hipMemset(ctx->fx_api, 0, b));
-    CHK(hipMalloc(&ctx->api_flags, sizeof(DevFlags)));
+    CHK(dev_malloc((void**)&ctx->api_flags, sizeof(DevFlags)));
     CHK(hipMemset(ctx->api_flags, 0, sizeof(DevFlags)));
   }
   CHK(launch_spread_api(ctx->g, ctx->ncls, n, d_pts, d_F, d_c, ctx->fx_api, ctx->api_flags, ctx->stream));
@@ -1813,15 +1910,6 @@ extern "C" lbm_status ib_spread_noalloc(lbm_ctx* ctx, int64_t n, const double* d
 // the last segment back, the segment's states are recomputed into a tape
 // and the adjoint steps run over them in reverse.  The context's own state
 // and counters are left as they are.
-namespace {
-struct DevArena {  // one allocation, carved in 256-byte aligned pieces
-  char* base = nullptr;
-  ~DevArena() {
-    if (base) hipFree(base);
-  }
-};
-}  // namespace
-
 extern "C" lbm_status lbm_set_scales(lbm_ctx* ctx, double inlet_scale, double stiffness_scale) {
   if (!ctx) return LBM_E_INVAL;
   if (ctx->broken) return LBM_E_STATE;
@@ -1918,9 +2006,7 @@ static lbm_status adjoint_sweep(lbm_ctx* ctx, int32_t n_steps, int32_t every, co
   const char* sp_env = getenv("LBM_ADJ_SPLIT");
   const int merged = (ctx->n_bulk + ctx->nrec < (4LL << 20)) && !(sp_env && atoi(sp_env) != 0);
   DevArena ar;
-  if (hipMalloc(&ar.base, big_bytes + small + ib_bytes + 16 * 256) != hipSuccess) {
-    (void)hipGetLastError();
-    ar.base = nullptr;
+  if (!ar.take(ctx->device, big_bytes + small + ib_bytes + 16 * 256)) {
     return fail(ctx, LBM_E_NOMEM, "adjoint: not enough device memory for the checkpoints and the tape");
   }
   auto big = [&](size_t i) { return (double*)(ar.base + i * dbytes); };
@@ -1951,8 +2037,12 @@ static lbm_status adjoint_sweep(lbm_ctx* ctx, int32_t n_steps, int32_t every, co
   m.amask = (uint32_t*)carve(((size_t)ctx->n_bulk + ctx->nrec) * sizeof(uint32_t));
   for (int k = 0; k < tlen; k++) m.hrec.push_back((double*)carve(hbytes));
   hipStream_t s = ctx->stream;
-  // solid entries stay zero in every buffer (never written by the sweep)
-  CHK(hipMemsetAsync(ar.base, 0, big_bytes + pbytes + sizeof(double) * (ADJ_BLOCKS + 8) + 512, s));
+  // What is added to starts from zero: the two accumulators and the partial
+  // sums.  Solid entries of the other fields are never read (a pull from one is
+  // replaced by the rule of its link, and lambda comes out zero there).
+  CHK(hipMemsetAsync(m.acc[0], 0, 2 * dbytes, s));
+  CHK(hipMemsetAsync(m.part, 0, pbytes, s));
+  CHK(hipMemsetAsync(m.jpart, 0, sizeof(double) * (ADJ_BLOCKS + 8), s));
   // the body part of the arena
   struct {
     long long* fx[2];
@@ -2186,6 +2276,7 @@ static lbm_status adjoint_sweep(lbm_ctx* ctx, int32_t n_steps, int32_t every, co
     CHK(hipMemcpyAsync(bdiag_save, bdiag_h.data(), sizeof(double) * bdiag_h.size(), hipMemcpyHostToDevice, s));
   }
   CHK(hipStreamSynchronize(s));
+  ar.idle = true;
   if (h_J) {
     h_J[0] = jv[0];
     h_J[1] = jv[1];

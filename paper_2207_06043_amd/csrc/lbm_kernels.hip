@@ -3242,8 +3242,7 @@ __device__ __forceinline__ bool zh_unknown(int fc, int j) {
 // same pull and collision as the stream-collide kernels) from a.A into a.B
 // (null: only rho and u, into a.mac):
 // bulk node t of a.bulk_list, or
-// boundary record r.  Solid nodes are not written (they hold zero in every
-// buffer of the sweep).  hrec (may be null): [19][nrec], the records'
+// boundary record r.  Solid nodes are neither written nor read.  hrec (may be null): [19][nrec], the records'
 // populations entering the collision (after Zou-He), kept for the step back.
 template <class S>
 __device__ __forceinline__ void adj_fwd_bulk_one(const FluidArgs& a, int t) {
@@ -3802,7 +3801,8 @@ __global__ __launch_bounds__(256) void k_adj_gather(FluidArgs a, const uint32_t*
 }
 
 // [19][N] with x fastest (N = nx ny nz) <-> the padded [19][plane] layout;
-// towards the padded side only the non-solid nodes are written.
+// towards the padded side only the non-solid nodes are written, and solid
+// ones come out zero.
 __global__ void k_adj_layout(Grid G, const uint8_t* ncls, const double* in, double* out, int to_padded) {
   const long long p = blockIdx.x * 256LL + threadIdx.x;
   if (p >= G.Np) return;
@@ -3815,7 +3815,7 @@ __global__ void k_adj_layout(Grid G, const uint8_t* ncls, const double* in, doub
     if (to_padded) {
       if (!solid) out[(long long)j * G.plane + p] = in[(long long)j * N + n];
     } else if (x < G.nx) {
-      out[(long long)j * N + n] = in[(long long)j * G.plane + p];
+      out[(long long)j * N + n] = solid ? 0.0 : in[(long long)j * G.plane + p];
     }
   }
 }
