@@ -33,7 +33,7 @@ constexpr int TILE_SHIFT = 6;
 // radius 19 (2562 vertices) need up to ~1430 box nodes; one block in a
 // thousand of the 16-capsule workload takes the direct path.
 constexpr int MARKERS_PER_BLOCK = 64;
-constexpr int BOX_CELLS = 1400;  // 39 KB of LDS: four blocks fit a CU
+constexpr int BOX_CELLS = 1400;  // 42 KB of LDS in the forcing: three blocks fit a CU
 constexpr int BIN_LDS_KEYS = 8192;  // bodies up to this many faces are binned in LDS (64 KB)
 constexpr int BIN_THREADS = 1024;   // threads of the binning block
 constexpr int CHUNK_CAP = 3;        // marker chunks per 64 faces of a body

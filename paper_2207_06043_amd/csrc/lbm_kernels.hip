@@ -1112,7 +1112,8 @@ __device__ unsigned int diag_finalize(const BodyArgs& b) {
 }
 
 // ---------------------------------------------------------- k_ib_force
-// First launch of a coupled step, three kinds of blocks:
+// First launch of a coupled step, three kinds of blocks (the diagnostics first
+// in the grid, the elements last):
 //  markers   direct forcing at the face centroids (Eqs. uLag, the direct
 //            forcing equation, bodyforce): U = sum phi u* with u* = sum f e
 //            / rho of the streamed populations (no force), F_l = U_b - U,
@@ -1122,11 +1123,15 @@ __device__ unsigned int diag_finalize(const BodyArgs& b) {
 //  diag      volume, area, bounding box and stretch of x^n; the last block
 //            combines them and stops the computation before anything of
 //            this step is written when x^n is damaged or not finite.
+// Out of the fixed-point range: the step ends as unstable.
+__device__ __forceinline__ void fx_over(const FluidArgs& a) {
+  atomicOr(&a.flags->overflow, 1u);
+  raise_pending(a.flags, a.par, ST_UNSTABLE);
+}
+
 __device__ __forceinline__ long long fx_quant(double v, const FluidArgs& a) {
   if (!(fabs(v) <= 1.0)) {
-    // out of the fixed-point range: the step ends as unstable
-    atomicOr(&a.flags->overflow, 1u);
-    raise_pending(a.flags, a.par, ST_UNSTABLE);
+    fx_over(a);
     v = 0.0;
   }
   return __double2ll_rn(v * FX_SCALE);
@@ -1530,6 +1535,8 @@ __device__ void marker_block(const FluidArgs& a, const BodyArgs& b, int blk, lon
   __shared__ long long s_acc[3][BOX_CELLS];
   __shared__ int s_node[BOX_CELLS];  // padded node index (< 2^31) or -1
   __shared__ int s_wbox[4][6];
+  __shared__ unsigned short s_list[BOX_CELLS];
+  __shared__ int s_used;
   const Grid& G = a.g;
   const int t = threadIdx.x, sub = t & 3;
   const int nchunk = b.chunk_n[blk], s0 = b.chunk_s0[blk];
@@ -1616,7 +1623,30 @@ __device__ void marker_block(const FluidArgs& a, const BodyArgs& b, int blk, lon
   const bool fits = (long long)ex * ey * ez <= BOX_CELLS;
   const int ncell = fits ? ex * ey * ez : 0;
   const float iex = 1.0f / (float)ex, iey = 1.0f / (float)ey;
-  for (int c = t; c < ncell; c += blockDim.x) {
+  // Boxes of more cells than threads: only the cells that some marker uses are
+  // computed (the box of a curved patch is about half empty), from a list of
+  // them in any order.
+  const bool list = ncell > 256;
+  if (list) {
+    for (int c = t; c < ncell; c += 256) s_node[c] = -1;
+    if (t == 0) s_used = 0;
+    __syncthreads();
+    if (mk) {
+      const int c0 = (bs[0] - 1 - x0) + ex * ((bs[1] - 1 - y0) + ey * (bs[2] - 1 - z0));
+#pragma unroll
+      for (int i = 0; i < 7; i++) {
+        const int k = 4 * i + sub;
+        if (k < 27) s_node[c0 + k % 3 + ex * ((k / 3) % 3 + ey * (k / 9))] = 0;
+      }
+    }
+    __syncthreads();
+    for (int c = t; c < ncell; c += 256)
+      if (s_node[c] == 0) s_list[atomicAdd(&s_used, 1)] = (unsigned short)c;
+    __syncthreads();
+  }
+  const int nuse = list ? s_used : ncell;
+  for (int i = t; i < nuse; i += 256) {
+    const int c = list ? (int)s_list[i] : i;
     // c / ex and so on for c < 1400: the half keeps the product off the integers
     const int q = (int)(((float)c + 0.5f) * iex), cz = (int)(((float)q + 0.5f) * iey);
     int p[3] = {x0 + c - q * ex, y0 + q - cz * ey, z0 + cz};
@@ -1705,20 +1735,29 @@ __device__ void marker_block(const FluidArgs& a, const BodyArgs& b, int blk, lon
   }
   __syncthreads();
   if (mk && fits) {
-#pragma unroll 1
+    // straight-line, no branch per cell: a cell without a node gets zeros
+    bool over = false;
+#pragma unroll
     for (int i = 0; i < 3; i++) {
       int ky = 2, kz = 2;
       if (i < 2) row_yz(sub + 4 * i, ky, kz);
       const double dy = (double)(bs[1] + ky - 1) - cen[1], dz = (double)(bs[2] + kz - 1) - cen[2];
       const double w = area * (sel3(ky, wy) * sel3(kz, wz)), t0 = cc[0] + cc[2] * dy + cc[3] * dz;
-      const int cr = c00 + ex * (ky + ey * kz);
+      const int cr = c00 + ex * (ky + ey * kz) + (i < 2 ? 0 : min(sub, 2));
 #pragma unroll
-      for (int k = 0; k < 3; k++) {
-        if (i == 2 && k != sub) continue;
-        const double c = w * wx[k] * (t0 + cc[1] * dx[k]);
-        if (s_node[cr + k] >= 0 && c != 0.0) spread_add(a, &s_acc[0][cr + k], BOX_CELLS, c, F);
+      for (int k = 0; k < (i < 2 ? 3 : 1); k++) {
+        const double c = i < 2 ? w * wx[k] * (t0 + cc[1] * dx[k]) : w * sel3(sub, wx) * (t0 + cc[1] * sel3(sub, dx));
+        const bool on = s_node[cr + k] >= 0 && (i < 2 || sub < 3) && c != 0.0;
+#pragma unroll
+        for (int q = 0; q < 3; q++) {
+          const double v = c * F[q];
+          const bool in = fabs(v) <= 1.0;
+          over = over || (on && !in);
+          atomicAdd((unsigned long long*)&s_acc[q][cr + k], (unsigned long long)__double2ll_rn(on && in ? v * FX_SCALE : 0.0));
+        }
       }
     }
+    if (over) fx_over(a);
   } else if (mk) {
 #pragma unroll 1
     for (int k = sub; k < 27; k += 4) {
@@ -2166,17 +2205,14 @@ __device__ __forceinline__ void ib_force_block(const FluidArgs& a, const BodyArg
                                                uint8_t* tfc, long long* fxp, uint8_t* tfp,
                                                unsigned int* counter, int blk) {
   const unsigned int halt = halted(a.flags, a.par);
-  const int nmk = b.n_marker_blocks, nel = b.n_elem_blocks;
+  const int nmk = b.n_marker_blocks, ndg = b.n_diag_blocks;
   (void)fxp;
   (void)tfp;
-  if (blk < nmk) {
-    marker_block<S>(a, b, blk, fxc, tfc, halt);
-  } else if (halt) {
-    return;
-  } else if (blk < nmk + nel) {
-    membrane_element(b, (blk - nmk) * 256 + threadIdx.x);
-  } else {
-    diag_block(b, b.Xcur, blk - nmk - nel);
+  // The diagnostics first: their last block waits for all of them.  The short
+  // element blocks last, where they fill the places that the markers leave.
+  if (blk < ndg) {
+    if (halt) return;
+    diag_block(b, b.Xcur, blk);
     // the diagnostics blocks count themselves; the last one combines them
     if (last_block(counter, b.n_diag_blocks)) {
       const unsigned int raised = diag_finalize(b);
@@ -2184,6 +2220,10 @@ __device__ __forceinline__ void ib_force_block(const FluidArgs& a, const BodyArg
       __syncthreads();
       if (threadIdx.x == 0) *counter = 0u;
     }
+  } else if (blk < ndg + nmk) {
+    marker_block<S>(a, b, blk - ndg, fxc, tfc, halt);
+  } else if (!halt) {
+    membrane_element(b, (blk - ndg - nmk) * 256 + threadIdx.x);
   }
 }
 
@@ -2192,11 +2232,17 @@ __device__ __forceinline__ void ib_force_block(const FluidArgs& a, const BodyArg
 // the launch lasts as long as its longest chain.  So: flags, chunk and slot
 // tables in two rounds, the 19 pulls of a cell with its class instead of
 // after it, three links of a boundary node per round, sums row by row and
-// through DPP moves, and one LDS array for u* and then the sums (39 KB, 217
+// through DPP moves, and one LDS array for u* and then the sums (42 KB, 218
 // registers: two waves per SIMD; asking for three or four spills and is
-// slower, 15.4 and 17.8 us on one capsule).  Measured per launch, before ->
-// after: one capsule 18.7 -> 14.0 us, a train of three 32 -> 21, a small
-// sphere in FP64 28 -> 18.7, 16 capsules 110 -> 82, a sweep of ten 43 -> 31.7.
+// slower, 15.4 and 17.8 us on one capsule; 17.1 with the spread below).  Of a
+// block's 10 us the pulls take 2.5 (7 where links are near), the tables 2.3,
+// the spread into LDS 1.6 (2.7 with a branch per cell), the sums 1.1.  A box of
+// more than 256 cells computes the used ones only (a coarse sphere of 320 faces
+// at r = 4: 3 passes of the pulls become 2, a train of three 3 become 1), and
+// the diagnostics, whose last block waits for the others, come first in the
+// grid (16 capsules 79 -> 71 us, one 13.7 -> 12.0).  Measured per launch, at
+// first -> now: one capsule 18.7 -> 12.0 us, a train of three 32 -> 17, a small
+// sphere in FP64 28 -> 18, 16 capsules 110 -> 71, a sweep of ten 43 -> 30.
 template <class S>
 __global__ __launch_bounds__(256, 2) void k_ib_force(FluidArgs a, BodyArgs b, long long* fxc,
                                                   uint8_t* tfc, long long* fxp, uint8_t* tfp,
