@@ -3,7 +3,7 @@
 // "Numerical method and computational procedure").
 //
 // One coupled step is four launches on one stream (a step without bodies:
-// the fluid launch and k_close):
+// the fluid launch alone):
 //   k_ib_force   marker blocks: MLS interpolation of the streamed (pre-force)
 //                velocity at the face centroids, direct forcing and spreading
 //                (fixed-point atomics, deterministic); element blocks:
@@ -17,9 +17,8 @@
 //   k_mls_post   hydrodynamic probes (pressure and viscous stress from MLS
 //                fits at +-1.2 dx), repulsion, MLS velocity at the vertices,
 //                clearing of the previous step's spread buffer;
-//   k_body_post  vertex forces and Verlet (soft) / Newton-Euler (rigid); its
-//                last block closes the step (with many bodies a k_close
-//                launch follows instead).
+//   k_body_post  vertex forces and Verlet (soft) / Newton-Euler (rigid).
+// One thread of a step's last launch counts the step.
 // Populations are stored as deviations g_i = f_i - w_i from the rest
 // equilibrium; the collision is written for g (algebraically identical to the
 // BGK rule on f, with smaller rounding).
