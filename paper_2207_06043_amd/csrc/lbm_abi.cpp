@@ -60,8 +60,9 @@ struct ArenaSlot {
   size_t bytes = 0;
   int contexts = 0;
 };
-std::mutex arena_mu;
-std::map<int, ArenaSlot> arena_slots;
+// (never destroyed: a context may be destroyed as late as at exit)
+std::mutex& arena_mu = *new std::mutex;
+std::map<int, ArenaSlot>& arena_slots = *new std::map<int, ArenaSlot>;
 
 void arena_drop(int device) {  // (hipFree waits for the device)
   char* p = nullptr;
