@@ -2039,8 +2039,10 @@ static lbm_status adjoint_sweep(lbm_ctx* ctx, int32_t n_steps, int32_t every, co
   for (int k = 0; k < tlen; k++) m.hrec.push_back((double*)carve(hbytes));
   hipStream_t s = ctx->stream;
   // What is added to starts from zero: the two accumulators and the partial
-  // sums.  Solid entries of the other fields are never read (a pull from one is
-  // replaced by the rule of its link, and lambda comes out zero there).
+  // sums.  Solid entries of the other fields and states are left as the memory
+  // was: no value is formed from them (a pull from one is replaced by the rule
+  // of its link, which drops a neighbour behind that is not fluid, and lambda
+  // comes out zero there).
   CHK(hipMemsetAsync(m.acc[0], 0, 2 * dbytes, s));
   CHK(hipMemsetAsync(m.part, 0, pbytes, s));
   CHK(hipMemsetAsync(m.jpart, 0, sizeof(double) * (ADJ_BLOCKS + 8), s));

@@ -228,7 +228,8 @@ hipError_t launch_diag_sums(int prec, const Grid& g, const void* f0, const void*
 // Adjoint of the fluid step (no bodies; FluidArgs with A = the state g^k in
 // [19][plane] in the context's storage, prec 0 FP64, 1 FP32 or 2 FP16S,
 // bulk_list / nbulk_nodes set); the adjoint quantities are FP64 in all.  Solid entries
-// of the sweep's buffers are neither written nor read.  merged:
+// of the sweep's buffers are not written; they may be loaded (the forcing's
+// pulls and links) but no value depends on them.  merged:
 // records and bulk nodes in one launch (small grids), else two.
 // Buffers of one reverse step (from state k+1 back to state k).
 struct AdjStep {

@@ -1403,7 +1403,10 @@ __device__ __forceinline__ bool sel3b(int i, const bool (&w)[3]) { return i == 0
 // (x, y, z), inside the box, of padded index node; false at a solid node.  The
 // 19 plain pulls go out with the node's class; a boundary record then replaces
 // those that come from a wall link (three links per batch of loads) and, on an
-// open face, takes rho and u from the known populations (Zou-He).
+// open face, takes rho and u from the known populations (Zou-He).  Entries of
+// solid nodes are loaded (the class and the links' words would come a round
+// earlier than the loads otherwise) but enter no value: in a state of the
+// adjoint's sweep they hold whatever the memory held before, NaN included.
 template <class S>
 __device__ __forceinline__ bool cell_velocity(const FluidArgs& a, int node, int x, int y, int z, double (&u)[3]) {
   typedef typename Store<S>::C C;
@@ -1460,7 +1463,10 @@ __device__ __forceinline__ bool cell_velocity(const FluidArgs& a, int node, int 
 #pragma unroll
       for (int q = 0; q < 3; q++) {
         const int j = jj[q];
-        const double w = j ? (double)(v[q][0] * v[q][3] + v[q][1] * v[q][4] + v[q][2] * v[q][5]) : 0.0;
+        // (a zero coefficient drops what it stands at: a node behind that is
+        // not fluid, whose entry may hold anything)
+        const C t1 = v[q][1] != C(0) ? v[q][4] : C(0), t2 = v[q][2] != C(0) ? v[q][5] : C(0);
+        const double w = j ? (double)(v[q][0] * v[q][3] + v[q][1] * t1 + v[q][2] * t2) : 0.0;
         const int ex = dir_of(dir_bits(EX), j), ey = dir_of(dir_bits(EY), j), ez = dir_of(dir_bits(EZ), j);
         const int en = sg * (ax == 0 ? ex : (ax == 1 ? ey : ez));
         dl += w;
@@ -3287,7 +3293,8 @@ __device__ __forceinline__ bool zh_unknown(int fc, int j) {
 // same pull and collision as the stream-collide kernels) from a.A into a.B
 // (null: only rho and u, into a.mac):
 // bulk node t of a.bulk_list, or
-// boundary record r.  Solid nodes are neither written nor read.  hrec (may be null): [19][nrec], the records'
+// boundary record r.  Solid nodes are not written and no value is formed
+// from their entries.  hrec (may be null): [19][nrec], the records'
 // populations entering the collision (after Zou-He), kept for the step back.
 template <class S>
 __device__ __forceinline__ void adj_fwd_bulk_one(const FluidArgs& a, int t) {
