@@ -2256,10 +2256,12 @@ __global__ __launch_bounds__(256, 2) void k_ib_force(FluidArgs a, BodyArgs b, lo
 }
 
 // Diagnostics of the current positions only (set-up and synchronisation
-// points): fills the body table and stops on damage or non-finite values.
+// points): fills the body table and stops on damage or non-finite values.  Not
+// after a stop, one that the last step raised and the next would latch
+// included: the run's status is what stopped it.
 __global__ __launch_bounds__(256) void k_check(BodyArgs b, const double* X0, const double* X1,
                                                DevFlags* flags, unsigned int* counter) {
-  if (flags->stop) return;
+  if (flags->stop | flags->pend0 | flags->pend1) return;
   const double* X = (flags->steps_done & 1) ? X1 : X0;
   if ((int)blockIdx.x < b.n_diag_blocks) diag_block(b, X, blockIdx.x);
   if (last_block(counter, gridDim.x)) {
