@@ -639,8 +639,8 @@ static lbm_status read_flags(lbm_ctx* ctx, DevFlags* h) {
   CHK(hipStreamSynchronize(ctx->stream));
   CHK(hipMemcpy(h, ctx->flags, sizeof(DevFlags), hipMemcpyDeviceToHost));
   // bits of the last step, which the next one would have moved
-  h->stop |= h->pend0 | h->pend1;
-  h->pend0 = h->pend1 = 0u;
+  h->stop |= h->pend0 | h->pend1 | h->check;
+  h->pend0 = h->pend1 = h->check = 0u;
   return LBM_OK;
 }
 

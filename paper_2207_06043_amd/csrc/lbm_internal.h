@@ -52,7 +52,10 @@ constexpr int VT_SLOTS = 4 * VT_MAX, VT_SLOTS_LOW = 4 * VT_LOW;  // edges, hinge
 // A step of parity p raises bits in pend0 (p = 0) or pend1: they do not stop
 // its own launches, and stop every launch of the next step, whose closing
 // launch moves them to stop.  Closing a step is then one thread of its last
-// launch counting it, with nothing to wait for.
+// launch counting it, with nothing to wait for.  The forcing launch's check of
+// the positions raises its bits in check, which stop every later launch of the
+// same step (the closing one moves them to stop): no launch reads a word that
+// it may change, so that all waves of a block, and all blocks, decide alike.
 struct DevFlags {
   uint32_t stop;      // sticky stop bits
   uint32_t pend0;     // bits raised during a step of parity 0
@@ -60,7 +63,7 @@ struct DevFlags {
   uint32_t pend1;     // bits raised during a step of parity 1
   long long steps_done;
   int mls_singular;
-  int pad2;
+  uint32_t check;     // bits raised by the position check of the current step
 };
 
 struct Grid {

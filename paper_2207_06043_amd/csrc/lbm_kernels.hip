@@ -483,8 +483,13 @@ __device__ __forceinline__ void raise_pending(DevFlags* flags, int par, unsigned
 
 // Non-zero when the run stopped before this step: a sticky bit, or one that
 // the previous step raised.
-__device__ __forceinline__ unsigned int halted(const DevFlags* flags, int par) {
+__device__ __forceinline__ unsigned int halted_before(const DevFlags* flags, int par) {
   return flags->stop | (par ? flags->pend0 : flags->pend1);
+}
+// The same for the launches after the step's forcing, whose position check may
+// have stopped it as well.
+__device__ __forceinline__ unsigned int halted(const DevFlags* flags, int par) {
+  return halted_before(flags, par) | flags->check;
 }
 
 // Closes a step, by one thread of its last launch (halt: halted() as that
@@ -713,6 +718,10 @@ __global__ __launch_bounds__(256) void k_fluid_all(FluidArgs a, int nrb) {
 // parity 0.
 __global__ void k_close(DevFlags* flags) {
   if (flags->stop) return;
+  if (flags->check) {
+    flags->stop = flags->check;
+    return;
+  }
   flags->steps_done += 1;
   flags->stop = flags->pend0 | flags->pend1;
   flags->pend0 = flags->pend1 = 0u;
@@ -2209,7 +2218,9 @@ template <class S>
 __device__ __forceinline__ void ib_force_block(const FluidArgs& a, const BodyArgs& b, long long* fxc,
                                                uint8_t* tfc, long long* fxp, uint8_t* tfp,
                                                unsigned int* counter, int blk) {
-  const unsigned int halt = halted(a.flags, a.par);
+  // (not halted(): the check below is of this launch, and a block whose waves
+  // saw it at different times would lose some of them before its barriers)
+  const unsigned int halt = halted_before(a.flags, a.par);
   const int nmk = b.n_marker_blocks, ndg = b.n_diag_blocks;
   (void)fxp;
   (void)tfp;
@@ -2221,7 +2232,7 @@ __device__ __forceinline__ void ib_force_block(const FluidArgs& a, const BodyArg
     // the diagnostics blocks count themselves; the last one combines them
     if (last_block(counter, b.n_diag_blocks)) {
       const unsigned int raised = diag_finalize(b);
-      if (raised) atomicOr(&a.flags->stop, raised);
+      if (raised) atomicOr(&a.flags->check, raised);
       __syncthreads();
       if (threadIdx.x == 0) *counter = 0u;
     }
