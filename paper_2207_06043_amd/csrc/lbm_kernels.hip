@@ -1521,6 +1521,22 @@ __device__ __forceinline__ bool cell_velocity(const FluidArgs& a, int node, int 
   return true;
 }
 
+// Extents e of the box of stencil bases lo..hi (lo <= hi) with the supports
+// around them; false when its cells exceed BOX_CELLS.  The differences are
+// taken unsigned: points that have left the box may lie 2^31 or more apart,
+// where a signed extent turns negative and its product looks small.
+__device__ __forceinline__ bool box_fits(const int (&lo)[3], const int (&hi)[3], int (&e)[3]) {
+  bool ok = true;
+#pragma unroll
+  for (int k = 0; k < 3; k++) {
+    const unsigned int d = (unsigned int)hi[k] - (unsigned int)lo[k];
+    ok = ok && d < (unsigned int)BOX_CELLS;
+    e[k] = (int)(d + 3u);
+  }
+  return ok && (unsigned int)e[0] * (unsigned int)e[1] * (unsigned int)e[2] <= (unsigned int)BOX_CELLS;
+}
+static_assert((BOX_CELLS + 2LL) * (BOX_CELLS + 2LL) * (BOX_CELLS + 2LL) <= 0xffffffffLL, "the product is formed in 32 bits");
+
 // Smallest (largest with MAX) of v over the wave, for values that agree inside
 // a quad; on every lane.
 template <bool MAX>
@@ -1633,8 +1649,9 @@ __device__ void marker_block(const FluidArgs& a, const BodyArgs& b, int blk, lon
     }
   }
   const int x0 = lo[0] - 1, y0 = lo[1] - 1, z0 = lo[2] - 1;
-  const int ex = hi[0] - lo[0] + 3, ey = hi[1] - lo[1] + 3, ez = hi[2] - lo[2] + 3;
-  const bool fits = (long long)ex * ey * ez <= BOX_CELLS;
+  int be[3];
+  const bool fits = box_fits(lo, hi, be);
+  const int ex = be[0], ey = be[1], ez = be[2];
   const int ncell = fits ? ex * ey * ez : 0;
   const float iex = 1.0f / (float)ex, iey = 1.0f / (float)ey;
   // Boxes of more cells than threads: only the cells that some marker uses are
@@ -1835,12 +1852,10 @@ __device__ __forceinline__ int box_cell(const Grid& G, const int (&o)[3], const 
 // did not fit LDS (its block added its sums with atomics) or is empty.
 __device__ __forceinline__ bool chunk_geom(const int* cb, int (&o)[3], int (&e)[3]) {
   if (cb[3] < cb[0]) return false;
+  const int lo[3] = {cb[0], cb[1], cb[2]}, hi[3] = {cb[3], cb[4], cb[5]};
 #pragma unroll
-  for (int a = 0; a < 3; a++) {
-    o[a] = cb[a] - 1;
-    e[a] = cb[3 + a] - cb[a] + 3;
-  }
-  return (long long)e[0] * e[1] * e[2] <= BOX_CELLS;
+  for (int a = 0; a < 3; a++) o[a] = lo[a] - 1;
+  return box_fits(lo, hi, e);
 }
 
 // Owner pass of the two-pass spread: thread (chunk c, cell i) holds node n;
@@ -4420,13 +4435,10 @@ __device__ __forceinline__ bool block_box(const int (&bs)[3], bool on, int (*s_w
     bx = Box{0, 0, 0, 0, 0, 0};
     return false;
   }
-  bx.x0 = lo[0] - 1;
-  bx.y0 = lo[1] - 1;
-  bx.z0 = lo[2] - 1;
-  bx.ex = hi[0] - lo[0] + 3;
-  bx.ey = hi[1] - lo[1] + 3;
-  bx.ez = hi[2] - lo[2] + 3;
-  return (long long)bx.ex * bx.ey * bx.ez <= BOX_CELLS;
+  int e[3];
+  const bool fits = box_fits(lo, hi, e);
+  bx = Box{lo[0] - 1, lo[1] - 1, lo[2] - 1, e[0], e[1], e[2]};
+  return fits;
 }
 
 // The cell c of a box: node coordinates in the periodic box; false outside.
