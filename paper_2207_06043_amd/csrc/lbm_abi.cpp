@@ -536,7 +536,7 @@ extern "C" lbm_status lbm_create(const lbm_desc* d, void* hip_stream, lbm_ctx** 
   const size_t fbytes = ((size_t)19 * G.plane + 2 * (size_t)G.guard) * ctx->ssize;
   for (int p = 0; p < 2; p++) {
     CHK(dev_malloc((void**)&ctx->f_alloc[p], fbytes));
-    CHK(hipMemset(ctx->f_alloc[p], 0, fbytes));
+    CHK(hipMemsetAsync(ctx->f_alloc[p], 0, fbytes, ctx->cap));
     ctx->f[p] = (char*)ctx->f_alloc[p] + (size_t)G.guard * ctx->ssize;
   }
   CHK(upload(&ctx->ncls, ncls));
@@ -592,7 +592,7 @@ extern "C" lbm_status lbm_create(const lbm_desc* d, void* hip_stream, lbm_ctx** 
   CHK(upload(&ctx->lk_w, lw));
   CHK(upload(&ctx->tile_list, tiles));
   CHK(dev_malloc((void**)&ctx->flags, sizeof(DevFlags) + 64));
-  CHK(hipMemset(ctx->flags, 0, sizeof(DevFlags) + 64));
+  CHK(hipMemsetAsync(ctx->flags, 0, sizeof(DevFlags) + 64, ctx->cap));
   // initial populations: equilibrium of the given fields
   double *drho = nullptr, *du = nullptr;
   if (d->init_rho) {
@@ -969,18 +969,19 @@ static lbm_status build_body_arrays(lbm_ctx* ctx, int cur, const std::vector<dou
     ctx->bargs[p].Xnext = ctx->X[p ^ 1];
     ctx->bargs[p].par = p;
   }
-  // force buffers (once)
+  // force buffers (once), cleared on the stream that uses them (hipMemset works
+  // on the default stream, which a non-blocking one does not wait for)
   if (!ctx->fx[0]) {
     const size_t fxb = 3 * (size_t)ctx->g.Np * sizeof(long long);
     for (int p = 0; p < 2; p++) {
       CHK(dev_malloc((void**)&ctx->fx[p], fxb));
-      CHK(hipMemset(ctx->fx[p], 0, fxb));
+      CHK(hipMemsetAsync(ctx->fx[p], 0, fxb, ctx->stream));
       CHK(dev_malloc((void**)&ctx->tf[p], ctx->ntiles));
-      CHK(hipMemset(ctx->tf[p], 0, ctx->ntiles));
+      CHK(hipMemsetAsync(ctx->tf[p], 0, ctx->ntiles, ctx->stream));
     }
     const size_t macb = 4 * (size_t)ctx->g.Np * (ctx->prec == 0 ? sizeof(double) : sizeof(float));
     CHK(dev_malloc((void**)&ctx->mac, macb));
-    CHK(hipMemset(ctx->mac, 0, macb));
+    CHK(hipMemsetAsync(ctx->mac, 0, macb, ctx->stream));
     CHK(launch_mac_solid(ctx->prec, ctx->g, ctx->mac, ctx->ncls, ctx->stream));
   }
   // marker order of the current positions, and their diagnostics
@@ -1870,9 +1871,9 @@ extern "C" lbm_status ib_spread(lbm_ctx* ctx, int64_t n, const double* d_pts, co
   if (!ctx->fx_api) {
     const size_t b = 3 * (size_t)ctx->g.Np * sizeof(long long);
     CHK(dev_malloc((void**)&ctx->fx_api, b));
-    CHK(hipMemset(ctx->fx_api, 0, b));
+    CHK(hipMemsetAsync(ctx->fx_api, 0, b, ctx->stream));
     CHK(dev_malloc((void**)&ctx->api_flags, sizeof(DevFlags)));
-    CHK(hipMemset(ctx->api_flags, 0, sizeof(DevFlags)));
+    CHK(hipMemsetAsync(ctx->api_flags, 0, sizeof(DevFlags), ctx->stream));
   }
   CHK(launch_spread_api(ctx->g, ctx->ncls, n, d_pts, d_F, d_c, ctx->fx_api, ctx->api_flags, ctx->stream));
   CHK(launch_flush_fx(ctx->g, ctx->fx_api, d_fib, ctx->stream));
@@ -1881,7 +1882,7 @@ extern "C" lbm_status ib_spread(lbm_ctx* ctx, int64_t n, const double* d_pts, co
   CHK(hipStreamSynchronize(ctx->stream));
   CHK(hipMemcpy(&h, ctx->api_flags, sizeof(DevFlags), hipMemcpyDeviceToHost));
   if (h.overflow) {
-    CHK(hipMemset(ctx->api_flags, 0, sizeof(DevFlags)));
+    CHK(hipMemsetAsync(ctx->api_flags, 0, sizeof(DevFlags), ctx->stream));
     return fail(ctx, LBM_E_INVAL, "ib_spread: a contribution c*phi*F exceeded +-1 (dropped)");
   }
   return LBM_OK;
