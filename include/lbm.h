@@ -246,9 +246,10 @@ lbm_status ib_spread_noalloc(lbm_ctx *ctx, int64_t n, const double *d_pts, const
  * fields and ceil(n/K) + max(K, 2) states of 19 x plane values, plus K x 19
  * doubles per boundary record; with a body, 16 FP64 [Np] fields
  * and 9 nv doubles per checkpoint and per step of a segment;
- * LBM_E_NOMEM if it does not fit; up to 4 GiB of it are kept, once per
- * device, for the next call on any context there, and freed with the device's
- * last context or when an allocation of this library needs the room).  The
+ * LBM_E_NOMEM if it does not fit; it is kept, once per device, for the next
+ * call on any context there, if it is at most 4 GiB and 16 times as much is
+ * still free, and given back by lbm_trim, with the device's last context, or
+ * when an allocation of this library needs the room).  The
  * context's state and step count are not changed.  Contexts with rigid or
  * fixed bodies, or with more than one body (the repulsion), give
  * LBM_E_UNSUPPORTED; a trajectory on which a capsule is damaged or the flow
@@ -256,6 +257,11 @@ lbm_status ib_spread_noalloc(lbm_ctx *ctx, int64_t n, const double *d_pts, const
  * context's stream. */
 lbm_status lbm_adjoint_step(lbm_ctx *ctx, int32_t n_steps, int32_t checkpoint_every,
                             const double *d_w, double *d_lambda, double *d_grad);
+
+/* Gives back the device memory that the library keeps on the context's device
+ * from one gradient to the next (see lbm_adjoint_step).  Results do not depend
+ * on it: the next gradient allocates again.  It may wait for the device. */
+lbm_status lbm_trim(lbm_ctx *ctx);
 
 /* The same sweep with the capsule objective of the differentiation form and
  * the membrane-stiffness gradient: J adds taylor_weight times the sum over

@@ -24,7 +24,7 @@ PRECISIONS = {"f64": 0, "f32": 1, "f16s": 2}
 EXPORTS = ["lbm_create", "lbm_destroy", "lbm_last_error", "lbm_info", "lbm_add_body", "lbm_step",
            "lbm_sync", "lbm_get_fields", "lbm_get_populations", "lbm_set_populations", "lbm_get_force",
            "lbm_get_body",
-           "ib_interpolate", "ib_spread", "ib_spread_noalloc", "lbm_adjoint_step", "lbm_adjoint_run",
+           "ib_interpolate", "ib_spread", "ib_spread_noalloc", "lbm_adjoint_step", "lbm_adjoint_run", "lbm_trim",
            "lbm_set_scales", "lbm_save", "lbm_load",
            "lbm_time_fluid_kernel", "lbm_set_graph", "lbm_set_launch_shape", "lbm_diagnostics",
            "lbm_batch_create",
@@ -123,6 +123,8 @@ def load_library():
     L.lbm_adjoint_step.argtypes = [vp, i32, i32, vp, vp, vp]
     L.lbm_adjoint_run.restype = st
     L.lbm_adjoint_run.argtypes = [vp, i32, i32, vp, C.c_double, i32, vp, vp, vp, dp]
+    L.lbm_trim.restype = st
+    L.lbm_trim.argtypes = [vp]
     L.lbm_set_scales.restype = st
     L.lbm_set_scales.argtypes = [vp, C.c_double, C.c_double]
     L.lbm_save.restype = st
@@ -388,6 +390,11 @@ class Lattice:
                                                    _ptr(grad), _ptr(bg), J))
         self.stream.synchronize()
         return lam, grad, bg, (J[0], J[1])
+
+    def trim(self):
+        """lbm_trim: gives back the device memory kept from one gradient to
+        the next."""
+        self._check(load_library().lbm_trim(self._h))
 
     def set_scales(self, inlet=1.0, stiffness=1.0):
         """lbm_set_scales: inlet wall velocities times `inlet`, membrane

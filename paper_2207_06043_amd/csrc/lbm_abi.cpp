@@ -51,10 +51,12 @@ namespace {
 // against 9 ms for 20 steps with a capsule), so the last arena of up to
 // ARENA_KEEP bytes is kept, one per device, for the next sweep of any context
 // there: a sweep takes it out of its slot and nobody else sees it until the
-// sweep, its stream waited for, puts it back.  It is freed with the device's
-// last context, for a larger one, and whenever an allocation of this library
-// fails.
+// sweep, its stream waited for, puts it back.  It is kept only while at least
+// ARENA_FREE times its size is free besides, so that it takes no room on a card
+// that others fill, and freed by lbm_trim, with the device's last context, for a
+// larger one, and whenever an allocation of this library fails.
 constexpr size_t ARENA_KEEP = (size_t)4 << 30;
+constexpr size_t ARENA_FREE = 16;
 struct ArenaSlot {
   char* base = nullptr;
   size_t bytes = 0;
@@ -64,7 +66,7 @@ struct ArenaSlot {
 std::mutex& arena_mu = *new std::mutex;
 std::map<int, ArenaSlot>& arena_slots = *new std::map<int, ArenaSlot>;
 
-void arena_drop(int device) {  // (hipFree waits for the device)
+hipError_t arena_drop(int device) {  // (hipFree waits for the device)
   char* p = nullptr;
   {
     std::lock_guard<std::mutex> lock(arena_mu);
@@ -72,7 +74,7 @@ void arena_drop(int device) {  // (hipFree waits for the device)
     std::swap(p, sl.base);
     sl.bytes = 0;
   }
-  if (p) (void)hipFree(p);
+  return p ? hipFree(p) : hipSuccess;
 }
 void arena_contexts(int device, int d) {
   bool last = false;
@@ -80,18 +82,21 @@ void arena_contexts(int device, int d) {
     std::lock_guard<std::mutex> lock(arena_mu);
     last = (arena_slots[device].contexts += d) == 0;
   }
-  if (last) arena_drop(device);
+  if (last) (void)arena_drop(device);
 }
 
 struct DevArena {
   char* base = nullptr;
   size_t bytes = 0;
   int device = 0;
-  bool idle = false;  // the work that used it has completed
+  bool pooled = false;  // on the current device: from its slot, and back to it
+  bool idle = false;    // the work that used it has completed
   bool take(int dev, size_t n) {
     device = dev;
+    int cur = -1;
+    pooled = hipGetDevice(&cur) == hipSuccess && cur == dev;
     char* small = nullptr;
-    {
+    if (pooled) {
       std::lock_guard<std::mutex> lock(arena_mu);
       ArenaSlot& sl = arena_slots[dev];
       if (sl.bytes >= n) {
@@ -115,7 +120,9 @@ struct DevArena {
   }
   ~DevArena() {
     if (!base) return;
-    if (idle && bytes <= ARENA_KEEP) {
+    size_t room = 0, total = 0;
+    if (idle && pooled && bytes <= ARENA_KEEP && hipMemGetInfo(&room, &total) == hipSuccess &&
+        room / ARENA_FREE >= bytes) {
       std::lock_guard<std::mutex> lock(arena_mu);
       ArenaSlot& sl = arena_slots[device];
       if (sl.bytes < bytes) {
@@ -223,7 +230,7 @@ static hipError_t dev_malloc(void** p, size_t bytes) {
   if (e != hipErrorOutOfMemory) return e;
   (void)hipGetLastError();
   int device = 0;
-  if (hipGetDevice(&device) == hipSuccess) arena_drop(device);
+  if (hipGetDevice(&device) == hipSuccess) (void)arena_drop(device);
   return hipMalloc(p, bytes);
 }
 
@@ -2287,6 +2294,13 @@ static lbm_status adjoint_sweep(lbm_ctx* ctx, int32_t n_steps, int32_t every, co
   }
   if (hf.stop & ST_DAMAGED) return fail(ctx, LBM_E_DAMAGED, "adjoint: a capsule was damaged along the trajectory");
   if (hf.stop & ST_UNSTABLE) return fail(ctx, LBM_E_UNSTABLE, "adjoint: the trajectory became unstable");
+  return LBM_OK;
+}
+
+extern "C" lbm_status lbm_trim(lbm_ctx* ctx) {
+  if (!ctx) return LBM_E_INVAL;
+  if (ctx->broken) return LBM_E_STATE;
+  CHK(arena_drop(ctx->device));
   return LBM_OK;
 }
 
