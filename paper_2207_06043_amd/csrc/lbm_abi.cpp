@@ -1218,9 +1218,7 @@ static hipError_t enqueue_step(lbm_ctx* ctx, int p, hipStream_t s, hipEvent_t ev
   const bool ib = ctx->nf > 0;
   if (ib) {
     const BodyArgs& b = ctx->bargs[p];
-    if ((e = launch_ib_force(ctx->prec, a, b, ctx->fx[p], ctx->tf[p], ctx->fx[p ^ 1], ctx->tf[p ^ 1],
-                             counter(ctx, 0), s)) != hipSuccess)
-      return e;
+    if ((e = launch_ib_force(ctx->prec, a, b, ctx->fx[p], ctx->tf[p], counter(ctx, 0), s)) != hipSuccess) return e;
     if (b.stage && (e = launch_spread_owner(ctx->g, b, ctx->fx[p], ctx->tf[p], ctx->flags, s)) != hipSuccess)
       return e;
   }
@@ -2118,7 +2116,7 @@ static lbm_status adjoint_sweep(lbm_ctx* ctx, int32_t n_steps, int32_t every, co
     b2.Xcur = from;
     b2.Xnext = to;
     b2.Vel = to + 2 * nv3;
-    if ((e = launch_ib_force(ctx->prec, fa, b2, q.fx[0], q.tf[0], q.fx[1], q.tf[1], q.cnt, s)) != hipSuccess) return e;
+    if ((e = launch_ib_force(ctx->prec, fa, b2, q.fx[0], q.tf[0], q.cnt, s)) != hipSuccess) return e;
     if ((e = launch_adjoint_forward(ctx->prec, fa, hrec, merged, s)) != hipSuccess) return e;
     if ((e = launch_mls_post(ctx->prec, fa, b2, q.fx[1], q.tf[1], s)) != hipSuccess) return e;
     if ((e = launch_body_post(b2, q.flags, 0, s)) != hipSuccess) return e;
@@ -2226,7 +2224,7 @@ static lbm_status adjoint_sweep(lbm_ctx* ctx, int32_t n_steps, int32_t every, co
         b2.Xnext = q.bt[k + 1];  // not written by the forcing launch
         b2.Vel = Pk + 2 * nv3;
         b2.support_tf = q.etf;
-        CHK(launch_ib_force(ctx->prec, fa, b2, q.fx[0], q.tf[0], q.fx[1], q.tf[1], q.cnt, s));
+        CHK(launch_ib_force(ctx->prec, fa, b2, q.fx[0], q.tf[0], q.cnt, s));
         CHK(launch_adjoint_forward(ctx->prec, fa, nullptr, merged, s));
         AdjIB ibp{};
         ibp.aP = A3[0];

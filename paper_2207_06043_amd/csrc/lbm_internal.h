@@ -216,8 +216,7 @@ hipError_t launch_fluid_rec(int prec, const FluidArgs& a, hipStream_t s);
 hipError_t launch_fluid_all(int prec, const FluidArgs& a, hipStream_t s);
 hipError_t launch_close(DevFlags* flags, hipStream_t s);
 hipError_t launch_ib_force(int prec, const FluidArgs& a, const BodyArgs& b, long long* fx_cur,
-                           uint8_t* tf_cur, long long* fx_prev, uint8_t* tf_prev,
-                           unsigned int* counter, hipStream_t s);
+                           uint8_t* tf_cur, unsigned int* counter, hipStream_t s);
 hipError_t launch_mls_post(int prec, const FluidArgs& a, const BodyArgs& b, long long* fxp, uint8_t* tfp,
                            hipStream_t s);
 // close: it also closes the step; else launch_close must follow

@@ -1168,42 +1168,8 @@ __device__ __forceinline__ bool support_node(const Grid& G, const uint8_t* ncls,
 // the 3x3x3 stencil around floor(p + 1/2) every |x_k - p| <= 1.5 sqrt(3)
 // < 2.6, so r <= 1 always holds and W factors into one term per axis:
 // W = w(dx) w(dy) w(dz) with w(d) = exp(-d^2 / (2.6^2 0.09)); the nine
-// per-axis terms of a point are computed once.
+// per-axis terms of a point are computed once (quad_weights).
 constexpr double MLS_K = 1.0 / (2.6 * 2.6 * 0.09);
-
-__device__ __forceinline__ void axis_weights(double p, int base, double (&w)[3]) {
-#pragma unroll
-  for (int i = 0; i < 3; i++) {
-    const double d = (double)(base + i - 1) - p;
-    w[i] = exp(-(d * d) * MLS_K);
-  }
-}
-
-// A += W p p^T with p = (1, dx, dy, dz); A packed a00 a01 a02 a03 a11 a12
-// a13 a22 a23 a33.
-__device__ __forceinline__ void mls_add(double (&A)[10], double W, double dx, double dy, double dz) {
-  const double wx = W * dx, wy = W * dy, wz = W * dz;
-  A[0] += W;
-  A[1] += wx;
-  A[2] += wy;
-  A[3] += wz;
-  A[4] += wx * dx;
-  A[5] += wx * dy;
-  A[6] += wx * dz;
-  A[7] += wy * dy;
-  A[8] += wy * dz;
-  A[9] += wz * dz;
-}
-
-// b += W p f
-__device__ __forceinline__ void mls_rhs(double (&bf)[4], double W, double dx, double dy, double dz,
-                                        double f) {
-  const double wf = W * f;
-  bf[0] += wf;
-  bf[1] += wf * dx;
-  bf[2] += wf * dy;
-  bf[3] += wf * dz;
-}
 
 // Cholesky A = L L^T; singular (a pivot below 1e-10 of the largest
 // diagonal) returns false.  r holds 1/L_ii.
@@ -1350,7 +1316,8 @@ struct RowSums {
   }
 };
 
-// The moment matrix (packed as in mls_add) and the right-hand sides of a fit.
+// The moment matrix sum W p p^T with p = (1, dx, dy, dz), packed a00 a01 a02
+// a03 a11 a12 a13 a22 a23 a33, and the right-hand sides sum W p f of a fit.
 template <int NF>
 struct FitSums {
   double A[10], b[NF][4];
@@ -2231,14 +2198,11 @@ __device__ void membrane_element(const BodyArgs& b, int idx) {
 
 template <class S>
 __device__ __forceinline__ void ib_force_block(const FluidArgs& a, const BodyArgs& b, long long* fxc,
-                                               uint8_t* tfc, long long* fxp, uint8_t* tfp,
-                                               unsigned int* counter, int blk) {
+                                               uint8_t* tfc, unsigned int* counter, int blk) {
   // (not halted(): the check below is of this launch, and a block whose waves
   // saw it at different times would lose some of them before its barriers)
   const unsigned int halt = halted_before(a.flags, a.par);
   const int nmk = b.n_marker_blocks, ndg = b.n_diag_blocks;
-  (void)fxp;
-  (void)tfp;
   // The diagnostics first: their last block waits for all of them.  The short
   // element blocks last, where they fill the places that the markers leave.
   if (blk < ndg) {
@@ -2276,9 +2240,8 @@ __device__ __forceinline__ void ib_force_block(const FluidArgs& a, const BodyArg
 // sphere in FP64 28 -> 18, 16 capsules 110 -> 71, a sweep of ten 43 -> 30.
 template <class S>
 __global__ __launch_bounds__(256, 2) void k_ib_force(FluidArgs a, BodyArgs b, long long* fxc,
-                                                  uint8_t* tfc, long long* fxp, uint8_t* tfp,
-                                                  unsigned int* counter) {
-  ib_force_block<S>(a, b, fxc, tfc, fxp, tfp, counter, blockIdx.x);
+                                                  uint8_t* tfc, unsigned int* counter) {
+  ib_force_block<S>(a, b, fxc, tfc, counter, blockIdx.x);
 }
 
 // Diagnostics of the current positions only (set-up and synchronisation
@@ -2841,7 +2804,7 @@ __global__ __launch_bounds__(256, 2) void kb_ib_force(const BatchItem* items,
                                                                           const int2* map) {
   const int2 m = batch_unit(map);
   const BatchItem& it = batch_item(items, m.x);
-  ib_force_block<S>(it.a, it.b, it.fxc, it.tfc, it.fxp, it.tfp, it.counter, m.y);
+  ib_force_block<S>(it.a, it.b, it.fxc, it.tfc, it.counter, m.y);
 }
 
 // Fluid phase.  Merged form: records and bulk tiles of every instance in
@@ -3163,14 +3126,13 @@ hipError_t launch_close(DevFlags* flags, hipStream_t s) {
 }
 
 hipError_t launch_ib_force(int prec, const FluidArgs& a, const BodyArgs& b, long long* fxc,
-                           uint8_t* tfc, long long* fxp, uint8_t* tfp, unsigned int* counter,
-                           hipStream_t s) {
+                           uint8_t* tfc, unsigned int* counter, hipStream_t s) {
   const unsigned grid = (unsigned)(b.n_marker_blocks + b.n_elem_blocks + b.n_diag_blocks);
   if (grid == 0) return hipSuccess;
   switch (prec) {
-    case 0: k_ib_force<double><<<grid, 256, 0, s>>>(a, b, fxc, tfc, fxp, tfp, counter); break;
-    case 1: k_ib_force<float><<<grid, 256, 0, s>>>(a, b, fxc, tfc, fxp, tfp, counter); break;
-    default: k_ib_force<_Float16><<<grid, 256, 0, s>>>(a, b, fxc, tfc, fxp, tfp, counter); break;
+    case 0: k_ib_force<double><<<grid, 256, 0, s>>>(a, b, fxc, tfc, counter); break;
+    case 1: k_ib_force<float><<<grid, 256, 0, s>>>(a, b, fxc, tfc, counter); break;
+    default: k_ib_force<_Float16><<<grid, 256, 0, s>>>(a, b, fxc, tfc, counter); break;
   }
   return hipGetLastError();
 }
@@ -4162,43 +4124,13 @@ hipError_t launch_spread_noalloc(const Grid& g, const uint8_t* ncls, long long n
 // bodyforce) are applied, each with the derivative of its weights with
 // respect to the moving points.  All in FP64.
 
-// Forward-mode dual numbers (value and N partial derivatives), for the
-// derivatives of the small per-point and per-element functions of the
-// vertex positions.
+// Forward-mode dual numbers (value and N partial derivatives), for the bending
+// force's derivative along a direction (adjb_element).
 template <int N>
 struct Dual {
   double v;
   double d[N];
 };
-
-template <class T>
-struct Scal;
-template <>
-struct Scal<double> {
-  __device__ static double c(double v) { return v; }
-};
-template <int N>
-struct Scal<Dual<N>> {
-  __device__ static Dual<N> c(double v) {
-    Dual<N> r;
-    r.v = v;
-#pragma unroll
-    for (int i = 0; i < N; i++) r.d[i] = 0.0;
-    return r;
-  }
-};
-
-template <int N>
-__device__ __forceinline__ Dual<N> dseed(double v, int k) {
-  Dual<N> r = Scal<Dual<N>>::c(v);
-  r.d[k] = 1.0;
-  return r;
-}
-__device__ __forceinline__ double dval(double x) { return x; }
-template <int N>
-__device__ __forceinline__ double dval(const Dual<N>& x) {
-  return x.v;
-}
 
 #define DUAL_BIN(OP, VEXPR, DEXPR)                                                           \
   template <int N>                                                                           \
@@ -4213,16 +4145,6 @@ DUAL_BIN(-, a.v - b.v, a.d[i] - b.d[i])
 DUAL_BIN(*, a.v * b.v, a.d[i] * b.v + a.v * b.d[i])
 DUAL_BIN(/, a.v / b.v, (a.d[i] * b.v - a.v * b.d[i]) / (b.v * b.v))
 #undef DUAL_BIN
-template <int N>
-__device__ __forceinline__ Dual<N> operator+(const Dual<N>& a, double b) {
-  Dual<N> r = a;
-  r.v += b;
-  return r;
-}
-template <int N>
-__device__ __forceinline__ Dual<N> operator+(double b, const Dual<N>& a) {
-  return a + b;
-}
 template <int N>
 __device__ __forceinline__ Dual<N> operator-(const Dual<N>& a, double b) {
   Dual<N> r = a;
@@ -4251,24 +4173,6 @@ __device__ __forceinline__ Dual<N> operator*(const Dual<N>& a, double b) {
   for (int i = 0; i < N; i++) r.d[i] = a.d[i] * b;
   return r;
 }
-template <int N>
-__device__ __forceinline__ Dual<N> operator*(double b, const Dual<N>& a) {
-  return a * b;
-}
-template <int N>
-__device__ __forceinline__ Dual<N> operator/(const Dual<N>& a, double b) {
-  return a * (1.0 / b);
-}
-template <int N>
-__device__ __forceinline__ Dual<N>& operator+=(Dual<N>& a, const Dual<N>& b) {
-  a = a + b;
-  return a;
-}
-template <int N>
-__device__ __forceinline__ Dual<N>& operator-=(Dual<N>& a, const Dual<N>& b) {
-  a = a - b;
-  return a;
-}
 // chain rule of a scalar function: value f, derivative df at a.v
 template <int N>
 __device__ __forceinline__ Dual<N> dchain(const Dual<N>& a, double f, double df) {
@@ -4278,28 +4182,14 @@ __device__ __forceinline__ Dual<N> dchain(const Dual<N>& a, double f, double df)
   for (int i = 0; i < N; i++) r.d[i] = df * a.d[i];
   return r;
 }
-__device__ __forceinline__ double dsqrt(double a) { return sqrt(a); }
-__device__ __forceinline__ double dexp(double a) { return exp(a); }
-__device__ __forceinline__ double dsin(double a) { return sin(a); }
-__device__ __forceinline__ double dcos(double a) { return cos(a); }
-__device__ __forceinline__ double datan2(double y, double x) { return atan2(y, x); }
 template <int N>
 __device__ __forceinline__ Dual<N> dsqrt(const Dual<N>& a) {
   const double r = sqrt(a.v);
   return dchain(a, r, 0.5 / r);
 }
 template <int N>
-__device__ __forceinline__ Dual<N> dexp(const Dual<N>& a) {
-  const double e = exp(a.v);
-  return dchain(a, e, e);
-}
-template <int N>
 __device__ __forceinline__ Dual<N> dsin(const Dual<N>& a) {
   return dchain(a, sin(a.v), cos(a.v));
-}
-template <int N>
-__device__ __forceinline__ Dual<N> dcos(const Dual<N>& a) {
-  return dchain(a, cos(a.v), -sin(a.v));
 }
 template <int N>
 __device__ __forceinline__ Dual<N> datan2(const Dual<N>& y, const Dual<N>& x) {
