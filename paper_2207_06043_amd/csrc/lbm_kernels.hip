@@ -2236,8 +2236,10 @@ __device__ __forceinline__ void ib_force_block(const FluidArgs& a, const BodyArg
 // at r = 4: 3 passes of the pulls become 2, a train of three 3 become 1), and
 // the diagnostics, whose last block waits for the others, come first in the
 // grid (16 capsules 79 -> 71 us, one 13.7 -> 12.0).  Measured per launch, at
-// first -> now: one capsule 18.7 -> 12.0 us, a train of three 32 -> 17, a small
-// sphere in FP64 28 -> 18, 16 capsules 110 -> 71, a sweep of ten 43 -> 30.
+// first -> now: one capsule of 5120 faces 18.7 -> 11.9 us, a train of three
+// 32 -> 17, 16 capsules 110 -> 72, a sweep of ten 43 -> 30; in FP64 a rigid
+// sphere of 320 faces 28 -> 12.5 in a 48x20x20 pipe (r = 4 in R = 8) and
+// 28 -> 17.5 in a 24x12x12 one (r = 2.5 in R = 4.5: links near every cell).
 template <class S>
 __global__ __launch_bounds__(256, 2) void k_ib_force(FluidArgs a, BodyArgs b, long long* fxc,
                                                   uint8_t* tfc, unsigned int* counter) {
