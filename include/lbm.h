@@ -335,7 +335,7 @@ lbm_status lbm_set_launch_shape(lbm_ctx *ctx, int32_t bulk_v, int32_t block);
  * Batching form: many independent instances (contexts of any size, e.g. the
  * bifurcations of a parameter sweep) advanced together.  Every phase of a
  * coupled step (forcing, stream-collide, probes and vertex velocities,
- * membrane and motion, close) is ONE launch over the work units of all
+ * membrane and motion) is ONE launch over the work units of all
  * instances -- block g takes unit (instance, block of that instance's own
  * launch) from a device map -- and 16 steps are one HIP graph launch.  Each
  * instance computes exactly what its own lbm_step computes (bitwise).

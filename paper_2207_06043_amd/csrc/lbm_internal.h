@@ -324,7 +324,7 @@ hipError_t launch_adj_sum(const double* part, int n, double* out, hipStream_t s)
 
 hipError_t launch_check(const BodyArgs& b, const double* X0, const double* X1, DevFlags* flags,
                         unsigned int* counter, hipStream_t s);
-// Sorts each body's faces into marker slots by the Morton code of their
+// Sorts each body's faces into marker slots by the Hilbert key of their
 // stencil bases at b.Xcur (b.perm); one block of 1024 threads per body.
 hipError_t launch_bin_faces(const BodyArgs& b, hipStream_t s);
 // to[0..nv3) = from[nv3..2 nv3), to[nv3..2 nv3) = from[0..nv3), to[2 nv3..3 nv3)
