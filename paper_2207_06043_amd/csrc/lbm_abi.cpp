@@ -2372,6 +2372,7 @@ extern "C" lbm_status lbm_save(lbm_ctx* ctx, const char* path) {
     bufs[k].resize(secs[k].second);
     CHK(hipMemcpy(bufs[k].data(), secs[k].first, secs[k].second, hipMemcpyDeviceToHost));
   }
+  std::swap(h.overflow, h.check);  // the file's order
   FILE* fp = fopen(path, "wb");
   if (!fp) return fail(ctx, LBM_E_INVAL, std::string("cannot open ") + path);
   bool ok = fwrite(&hd, sizeof hd, 1, fp) == 1 && fwrite(&h, sizeof h, 1, fp) == 1;
@@ -2391,6 +2392,7 @@ extern "C" lbm_status lbm_load(lbm_ctx* ctx, const char* path) {
   CkptHeader hd{};
   DevFlags h{};
   bool ok = fread(&hd, sizeof hd, 1, fp) == 1 && fread(&h, sizeof h, 1, fp) == 1;
+  std::swap(h.overflow, h.check);  // (the file has them in the order overflow, check)
   ok = ok && memcmp(hd.magic, "LBMIB01", 8) == 0 && hd.nx == ctx->g.nx && hd.ny == ctx->g.ny &&
        hd.nz == ctx->g.nz && hd.prec == ctx->prec && hd.nbody == (int)ctx->bodies.size() &&
        hd.nv == ctx->nv && hd.nf == ctx->nf && hd.steps_done == h.steps_done;

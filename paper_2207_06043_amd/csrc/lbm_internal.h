@@ -56,15 +56,19 @@ constexpr int VT_SLOTS = 4 * VT_MAX, VT_SLOTS_LOW = 4 * VT_LOW;  // edges, hinge
 // the positions raises its bits in check, which stop every later launch of the
 // same step (the closing one moves them to stop): no launch reads a word that
 // it may change, so that all waves of a block, and all blocks, decide alike.
-struct DevFlags {
+// The four words that a launch reads come first, in one 16-byte load: every wave
+// starts with it, and a word of its own for check costs the fluid launch 0.15 us
+// on one capsule (14.04 -> 14.19) and 0.25 us on 16.
+struct alignas(16) DevFlags {
   uint32_t stop;      // sticky stop bits
   uint32_t pend0;     // bits raised during a step of parity 0
-  uint32_t overflow;  // a spread contribution exceeded +-1 (also raises ST_UNSTABLE)
+  uint32_t check;     // bits raised by the position check of the current step
   uint32_t pend1;     // bits raised during a step of parity 1
   long long steps_done;
   int mls_singular;
-  uint32_t check;     // bits raised by the position check of the current step
+  uint32_t overflow;  // a spread contribution exceeded +-1 (also raises ST_UNSTABLE)
 };
+static_assert(sizeof(DevFlags) == 32, "a checkpoint holds it");
 
 struct Grid {
   int nx, ny, nz;  // logical sizes

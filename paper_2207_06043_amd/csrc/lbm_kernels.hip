@@ -484,12 +484,14 @@ __device__ __forceinline__ void raise_pending(DevFlags* flags, int par, unsigned
 // Non-zero when the run stopped before this step: a sticky bit, or one that
 // the previous step raised.
 __device__ __forceinline__ unsigned int halted_before(const DevFlags* flags, int par) {
-  return flags->stop | (par ? flags->pend0 : flags->pend1);
+  const uint4 w = *(const uint4*)flags;  // stop, pend0, check, pend1
+  return w.x | (par ? w.y : w.w);
 }
 // The same for the launches after the step's forcing, whose position check may
 // have stopped it as well.
 __device__ __forceinline__ unsigned int halted(const DevFlags* flags, int par) {
-  return halted_before(flags, par) | flags->check;
+  const uint4 w = *(const uint4*)flags;
+  return w.x | w.z | (par ? w.y : w.w);
 }
 
 // Closes a step, by one thread of its last launch (halt: halted() as that
